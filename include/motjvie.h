@@ -96,12 +96,14 @@ typedef struct {
     int32_t z0_solver;        /* the Z_0 solve (eq:MOTInversion) on the symmetrised Z_0 with the Jacobi
                                  preconditioner: 1 CG; 2 Chebyshev iteration on its spectrum, estimated at
                                  mj_create and mj_set_eps (one stencil pass per iteration and no inner
-                                 products: fewer launches, more iterations); 0 Chebyshev up to 2^19 voxels
-                                 (whatever the number of right-hand sides, which share every launch), CG
-                                 above.  Both stop at cg_rtol; cg_maxit bounds their iterations */
-    int32_t z0_graphs;        /* != 0: the Chebyshev passes of a solve (whose arguments depend only on the
-                                 pass index) are captured once per batch shape as HIP graphs and replayed
-                                 on `stream` in later steps; 0: launched one by one */
+                                 products: fewer launches, more iterations); 0 passes that replay the
+                                 coefficients CG took in an earlier step of the march (CG's iteration
+                                 count at the Chebyshev iteration's launches), behind which stands 2
+                                 up to 2^19 voxels and 1 above.  Every solve is tested on its own residual
+                                 and stops at cg_rtol; cg_maxit bounds the iterations */
+    int32_t z0_graphs;        /* != 0: the Chebyshev or replayed passes of a solve (whose arguments depend
+                                 only on the pass index) are captured once per batch shape as HIP graphs
+                                 and launched on `stream` in later steps; 0: launched one by one */
     int32_t outer_overlap;    /* three levels only: 2 forms the outer sums of each outer block over the
                                  sources before the previous block on a second stream of the library's
                                  own (non-blocking, default priority), while the previous block marches,
@@ -136,7 +138,7 @@ const char *mj_last_error(const mj_solver *s);
  *   [11] number of FIR taps  [12] probes  [13] lag window per probe pair
  *   [14] probe pairs  [15] probe kernel generation time (ms)
  *   [16] [17] [18] pencils per block of the x, y and z FFT passes  [19] outer time block (0: none)
- *   [20] Z_0 solver in use (0 Chebyshev, 1 CG)  [21] [22] the bounds of the eigenvalues of the
+ *   [20] Z_0 solver in use, or behind the replayed passes (0 Chebyshev, 1 CG)  [21] [22] the bounds of the eigenvalues of the
  *   Jacobi-preconditioned symmetrised Z_0 that the Chebyshev solve uses (0: not estimated)
  *   [23] 1 if the outer level runs on the second stream (outer_overlap)
  */
@@ -260,7 +262,9 @@ int mj_reset(mj_solver *s);
  *   - the step count n;
  *   - the spectral history ring (the FFT of J_{n-k}, k = 1..ell, Sec. 3);
  *   - the current time block's far-part sums (Sec. 4.1);
- *   - the real-space currents that the FIR stencil, the Z_0 initial guess and the probes read.
+ *   - the real-space currents that the FIR stencil, the Z_0 initial guess and the probes read;
+ *   - the coefficients of the replayed Z_0 passes (a state without them, as earlier versions wrote it, is
+ *     read too: the solve then records them anew, and the march agrees to cg_rtol).
  * The adjoint (mj_adjoint_gradient) keeps its own checkpoints and is not part of it.
  *   mj_get_state: buf host, nullable.  With buf NULL, *bytes receives the size needed.
  *   Otherwise *bytes must be at least that size (else MJ_EINVAL), and it receives the size

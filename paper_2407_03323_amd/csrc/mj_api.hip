@@ -22,8 +22,10 @@ thread_local std::string g_err;
 
 // voxels (per right-hand side) up to which z0_solver = 0 takes the Chebyshev solve
 constexpr long kChebMaxUnknowns = 1L << 19;
-// bytes of solve vectors per group of right-hand sides that the Chebyshev solve takes at once
-constexpr size_t kChebGroupBytes = (size_t)320 << 20;
+// bytes of solve vectors per group of right-hand sides that three-term passes take at once: what they
+// stream (w_k, w_{k-1} and b, 72 bytes per voxel and right-hand side) stays in the 256 MB last-level cache
+// from one pass to the next
+constexpr size_t kPassGroupBytes = 190000000;
 
 // whether outer_overlap = 0 runs the outer level of three on the second stream
 constexpr bool kOverlapDefault = false;
@@ -166,10 +168,11 @@ struct mj_solver {
     int nquad = 16;
     hipStream_t st = nullptr;
     int nloc = 5, rdepth = 6;
-    // degree of the extrapolated initial guess of the Z_0 solve: at 104^3 degree 6 (seven past
-    // steps) takes 11.0 CG iterations, 4 takes 13.0 and 10 takes 12.2 (higher degrees amplify
-    // the rounding noise of the history)
-    int guess_deg = 6;
+    // degree of the extrapolated initial guess of the Z_0 solve (at most; the steps it goes through
+    // are those the taps read anyway, and seven at least).  Iterations with degree 4, 6 and 8: 104^3
+    // 16, 14, 12; 64^3 21, 19, 18; 32^3 24, 23, 23.  At 104^3 degree 10 took more again: higher
+    // degrees amplify the rounding noise of the history
+    int guess_deg = 8;
     // device state
     mj::DevAlloc da;                // hipMalloc, or the caller's allocator (mj_config.alloc)
     size_t bytes = 0;
@@ -194,21 +197,36 @@ struct mj_solver {
     int side_count = 0, side_done = 0;
     double side_ms = 0.0;
     double *S = nullptr, *Jr = nullptr;
-    double *rhs = nullptr, *y = nullptr, *p = nullptr, *q = nullptr;
-    double *u = nullptr, *uy = nullptr;
+    double *y = nullptr, *p = nullptr, *q = nullptr, *u = nullptr;   // CG's vectors
+    double *bh = nullptr;           // right-hand side of the solve, haloed
+    double *wbuf[2] = {};           // w_k and w_{k-1} of the three-term passes, haloed; wbuf[0] starts the solve
+    double *chih = nullptr;         // chi, haloed
+    const double *w_end = nullptr;  // solution of the last solve: a wbuf, or NULL: sqrt(chi) y
     double *parts = nullptr;
+    int part_cap = 0;               // values per right-hand side in parts
     mj::CgScalars *scal = nullptr;
     int cg_guess = 8;
-    // Z_0 solver: 0 Chebyshev iteration (needs spectral bounds of M^-1 A), 1 CG
+    // Z_0 solver: 0 Chebyshev iteration (needs spectral bounds of M^-1 A), 1 CG; with `replays` that one only
+    // stands behind the replayed passes
     int z0_method = 0;
+    bool replays = false;
+    struct Replay {                 // see solve_z0
+        int K = 0;                  // passes before the first test
+        int K0 = 0;                 // ... as CG left it
+        int L = 0;                  // passes with coefficients
+        int learn = 1;              // the next solve takes CG and records it
+        int fails = 0;              // replays in a row that missed the tolerance
+        int hold = 0;               // steps left without replays
+        int unused[2] = {};
+    } rp;
+    double *coef = nullptr;         // recorded coefficients [nrhs][kMaxCoef][2]
+    double *rhist = nullptr;        // and relative residuals [nrhs][kMaxCoef]
+    double *ccoef = nullptr;        // coefficients of the Chebyshev iteration [cg_maxit + 2][2]
     double lam_lo = 0.0, lam_hi = 0.0;   // bounds of the eigenvalues of M^-1 A (0: not estimated)
-    double *e2 = nullptr;                // second buffer of s d for the Chebyshev passes (haloed)
-    int cheb_pred = 0;                   // passes predicted for the next solve (0: none yet)
-    std::vector<double> cheb_rho;        // Chebyshev recurrence scalars by pass index (for lam_lo, lam_hi)
-    bool use_graphs = false;             // replay the Chebyshev batches from captured HIP graphs
+    int cheb_pred = 0;                   // passes predicted for the next Chebyshev solve (0: none yet)
+    bool use_graphs = false;             // launch batches of passes from captured HIP graphs
     hipStream_t cap_st = nullptr;        // the library's own stream, for capturing (never the null stream)
-    std::map<long, hipGraphExec_t> cheb_graphs;   // captured batches by (with init, first pass, passes)
-    double cheb_rho2 = 0.0;              // observed reduction of |r|^2 per pass
+    std::map<long, hipGraphExec_t> pass_graphs;   // captured batches by (group, coefficients, first pass, passes)
     mj::CgStatus *cgstat = nullptr, *cgstat_h = nullptr;
     mj::WaveArg *waves_d = nullptr;
     bool waves_set = false;
@@ -354,12 +372,20 @@ struct mj_solver {
     void offgrid_values(int n, const int *probe, const int *vox, const int *lag, double *out);
     void solve_z0();
     mj::CgArg cg_arg() const;
+    bool run_cg(const mj::CgArg &a, int batch);
+    void solve_cg();
+    void learn();
+    void replay();
+    int group_size() const;
+    void enqueue_passes(bool recorded, int g0, int g1, int T, int K);
+    bool read_status();
     void solve_z0_chebyshev();
     void estimate_spectrum();
+    size_t coef_count() const { return (size_t)nrhs * 2 * mj::kMaxCoef; }
     void clear_graphs()
     {
-        for (auto &kv : cheb_graphs) (void)hipGraphExecDestroy(kv.second);
-        cheb_graphs.clear();
+        for (auto &kv : pass_graphs) (void)hipGraphExecDestroy(kv.second);
+        pass_graphs.clear();
     }
     void history_sum(const double *Jh, int depth, double *P);
 };
@@ -429,19 +455,20 @@ void mj_solver::create(const mj_config &c)
     if (B2 && !(B == 4 || B == 8) ) throw ArgError("outer_block needs time_block 4 or 8");
     if (B2 && !(B2 > B && B2 % B == 0 && B2 >= 8 && B2 <= 16 && B2 % 2 == 0))
         throw ArgError("outer_block must be a multiple of time_block in 8 .. 16 (even), or 0");
-    nloc = std::max(guess_deg + 1, (int)fir.size() - 1);   // the initial guess uses guess_deg + 1 steps
+    // steps kept for the initial guess (7 or more) and the taps; the guess takes up to 9 of them
+    nloc = std::max(7, (int)fir.size() - 1);
     rdepth = nloc + 1;
 
-    // the Z_0 solve: Chebyshev passes cost one launch each against four per CG iteration, which
-    // decides on small grids; on large ones CG's fewer iterations win (104^3: 12.9 CG iterations,
-    // 1.02 ms, against 24 passes, 1.12 ms; 32^3: 0.48 against 0.19 ms).  A batch shares its
-    // launches, so the size that decides is the grid's (16 right-hand sides at 64^3: 26 passes,
-    // 5.98-6.07 ms, against 20 CG iterations, 6.23 ms)
+    // The Z_0 solve.  By default the passes of an earlier step's CG are replayed (solve_z0); behind
+    // them stands the Chebyshev iteration on small grids, whose launches decide (32^3: 4 us a pass
+    // against 20 us per CG iteration of four launches), and CG's fewer iterations on large ones.
     z0_method = c.z0_solver == 1 ? 1 : c.z0_solver == 2 ? 0 : (M <= kChebMaxUnknowns ? 0 : 1);
+    replays = c.z0_solver == 0;
     MJ_CHECK(hipGetDevice(&dev));
     if (use_graphs) MJ_CHECK(hipStreamCreateWithFlags(&cap_st, hipStreamNonBlocking));
     (void)scratch_ptr(dev);   // this device's staging array (mj_kernel_values_noalloc)
     chi = dalloc<double>(M, "chi");
+    chih = dalloc<double>((size_t)(U + 2) * (V + 2) * (W + 2), "chi, haloed");
     schi = dalloc<double>(M, "sqrt chi");
     inv_eps = dalloc<double>(M, "1/eps");
     c0 = dalloc<double>(M, "c0");
@@ -470,7 +497,6 @@ void mj_solver::create(const mj_config &c)
     }
     S = dalloc<double>((size_t)nrhs * 3 * M, "convolution");
     Jr = dalloc<double>((size_t)rdepth * nrhs * 3 * M, "current history");
-    rhs = dalloc<double>((size_t)nrhs * 3 * M, "cg rhs");
     y = dalloc<double>((size_t)nrhs * 3 * M, "cg y");
     p = dalloc<double>((size_t)nrhs * 3 * M, "cg p");
     q = dalloc<double>((size_t)nrhs * 3 * M, "cg q");
@@ -479,14 +505,24 @@ void mj_solver::create(const mj_config &c)
     MJ_CHECK(hipMemset(q, 0, sizeof(double) * nrhs * 3 * M));
     const size_t Mp = (size_t)(U + 2) * (V + 2) * (W + 2);
     u = dalloc<double>((size_t)nrhs * 3 * Mp, "cg u");
-    uy = dalloc<double>((size_t)nrhs * 3 * Mp, "cg uy");
-    e2 = dalloc<double>((size_t)nrhs * 3 * Mp, "chebyshev direction");
-    // the one-voxel halo of u, uy and e2 is never written and stays zero
+    bh = dalloc<double>((size_t)nrhs * 3 * Mp, "solve rhs");
+    // the one-voxel halo of these is never written and stays zero
     MJ_CHECK(hipMemset(u, 0, sizeof(double) * nrhs * 3 * Mp));
-    MJ_CHECK(hipMemset(uy, 0, sizeof(double) * nrhs * 3 * Mp));
-    MJ_CHECK(hipMemset(e2, 0, sizeof(double) * nrhs * 3 * Mp));
+    MJ_CHECK(hipMemset(bh, 0, sizeof(double) * nrhs * 3 * Mp));
+    for (double *&w : wbuf) {
+        w = dalloc<double>((size_t)nrhs * 3 * Mp, "solve vector");
+        MJ_CHECK(hipMemset(w, 0, sizeof(double) * nrhs * 3 * Mp));
+    }
+    coef = dalloc<double>(coef_count(), "recorded coefficients");
+    rhist = dalloc<double>((size_t)nrhs * mj::kMaxCoef, "recorded residuals");
+    ccoef = dalloc<double>(2 * ((size_t)cg_maxit + 2), "Chebyshev coefficients");
     nblk = (int)((M + 255) / 256);
-    parts = dalloc<double>((size_t)3 * nrhs * nblk, "cg partials");
+    part_cap = 3 * nblk;
+    {
+        const int G = group_size();
+        for (int nr = 1; nr <= G; nr++) part_cap = std::max(part_cap, 2 * mj::z0_pass_blocks(U, V, W, nr));
+    }
+    parts = dalloc<double>((size_t)nrhs * part_cap, "solve partials");
     scal = dalloc<mj::CgScalars>(nrhs, "cg scalars");
     cgstat = dalloc<mj::CgStatus>(nrhs, "cg status");
     waves_d = dalloc<mj::WaveArg>(nrhs, "waves");
@@ -527,6 +563,11 @@ void mj_solver::set_material(const double *eps)
     MJ_CHECK(hipMemcpy(schi, schi_h.data(), M * 8, hipMemcpyHostToDevice));
     MJ_CHECK(hipMemcpy(inv_eps, ie_h.data(), M * 8, hipMemcpyHostToDevice));
     MJ_CHECK(hipMemcpy(c0, c0_h.data(), M * 8, hipMemcpyHostToDevice));
+    std::vector<double> ch((size_t)(U + 2) * (V + 2) * (W + 2), 0.0);
+    for (int z = 0; z < W; z++)
+        for (int v = 0; v < V; v++)
+            std::copy_n(&chi_h[((size_t)z * V + v) * U], U, &ch[((size_t)(z + 1) * (V + 2) + (v + 1)) * (U + 2) + 1]);
+    MJ_CHECK(hipMemcpy(chih, ch.data(), ch.size() * 8, hipMemcpyHostToDevice));
 }
 
 void mj_solver::build_spectra()
@@ -617,13 +658,13 @@ mj::CgArg mj_solver::cg_arg() const
     a.Mp = (long)(U + 2) * (V + 2) * (W + 2);
     a.nrhs = nrhs;
     a.nblk = nblk;
-    a.tol2 = cg_rtol * cg_rtol;
+    a.tol2 = a.stop2 = cg_rtol * cg_rtol;
     a.schi = schi;
     a.d0 = fir.empty() ? 0.0 : fir[0];
     a.k0c = K0_27[13 * 6 + 0];
     a.k0 = k0_d;
-    a.rhs = rhs;
-    a.uy = uy;
+    a.b = bh;
+    a.w = wbuf[0];
     a.y = y;
     a.p = p;
     a.q = q;
@@ -634,36 +675,217 @@ mj::CgArg mj_solver::cg_arg() const
     return a;
 }
 
-void mj_solver::solve_z0()
+// CG iterations from the vectors of `a` until every right-hand side has ended or cg_maxit; the first look at
+// the status comes after `batch` of them (kernels after a solve's end return at once).  The solution is left
+// in y.  Returns whether every right-hand side met the tolerance.
+bool mj_solver::run_cg(const mj::CgArg &a, int batch)
 {
-    if (z0_method == 0 && lam_hi > 0.0) {
-        solve_z0_chebyshev();
-        return;
-    }
-    mj::CgArg a = cg_arg();
     mj::launch_cg_init(a, st);   // also clears the status records
-    // enqueue as many iterations as the last solve needed before the first look at the
-    // convergence flags; kernels after convergence return at once
     int it = 0;
-    int batch = std::max(2, std::min(cg_maxit, cg_guess));
-    bool all_done = false;
-    while (it < cg_maxit && !all_done) {
-        int upto = std::min(cg_maxit, it + batch);
+    batch = std::max(2, std::min(cg_maxit, batch));
+    bool ended = false, done = false;
+    while (it < cg_maxit && !ended) {
+        const int upto = std::min(cg_maxit, it + batch);
         for (; it < upto; it++) {
             mj::launch_cg_a(a, it, st);
             mj::launch_cg_b(a, it, st);
         }
-        MJ_CHECK(hipMemcpyAsync(cgstat_h, cgstat, sizeof(mj::CgStatus) * nrhs, hipMemcpyDeviceToHost, st));
-        MJ_CHECK(hipStreamSynchronize(st));
-        all_done = true;
-        for (int i = 0; i < nrhs; i++) all_done = all_done && cgstat_h[i].done;
+        done = read_status();
+        ended = true;
+        for (int i = 0; i < nrhs; i++) ended = ended && cgstat_h[i].ended;
         batch = 2;
     }
     // the last update of y (a no-op for the right-hand sides whose solve already ended)
     mj::launch_cg_end(a, it, st);
+    w_end = nullptr;
+    return done;
+}
+
+void mj_solver::solve_cg()
+{
+    run_cg(cg_arg(), cg_guess);
     int mx = 0;
     for (int i = 0; i < nrhs; i++) mx = std::max(mx, cgstat_h[i].iters);
     cg_guess = mx + 1;
+}
+
+// The status of every right-hand side; true if all met the tolerance.
+bool mj_solver::read_status()
+{
+    MJ_CHECK(hipMemcpyAsync(cgstat_h, cgstat, sizeof(mj::CgStatus) * nrhs, hipMemcpyDeviceToHost, st));
+    MJ_CHECK(hipStreamSynchronize(st));
+    bool done = true;
+    for (int i = 0; i < nrhs; i++) done = done && cgstat_h[i].done;
+    return done;
+}
+
+// Right-hand sides per group of three-term passes.  A group's passes follow each other, so that what
+// they stream (w_k, w_{k-1} and b) stays in the last-level cache; groups are as even as they go.
+int mj_solver::group_size() const
+{
+    const size_t per_rhs = sizeof(double) * 9 * (size_t)(U + 2) * (V + 2) * (W + 2);
+    const int most = (int)std::max<size_t>(1, std::min<size_t>((size_t)nrhs, kPassGroupBytes / per_rhs));
+    const int groups = (nrhs + most - 1) / most;
+    return (nrhs + groups - 1) / groups;
+}
+
+// Passes T .. T + K - 1 of the right-hand sides g0 .. g1 - 1, with the recorded coefficients or those of the
+// Chebyshev iteration; the test of w_{T+K-1} follows the last.  The arguments depend only on these numbers, so
+// a captured batch can be launched again.
+void mj_solver::enqueue_passes(bool recorded, int g0, int g1, int T, int K)
+{
+    auto launch = [&](hipStream_t s_) {
+        mj::PassArg a{};
+        a.px = U + 2;
+        a.py = V + 2;
+        a.pz = W + 2;
+        a.Mp = (long)a.px * a.py * a.pz;
+        a.d0 = fir.empty() ? 0.0 : fir[0];
+        a.k0c = K0_27[13 * 6 + 0];
+        a.tol2 = cg_rtol * cg_rtol;
+        a.chi = chih;
+        a.b = bh;
+        a.k0 = k0_d;
+        a.coef = recorded ? coef : ccoef;
+        a.coef_stride = recorded ? 2 * mj::kMaxCoef : 0;
+        a.coef_len = recorded ? mj::kMaxCoef : cg_maxit + 2;
+        a.rhs0 = g0;
+        a.nr = g1 - g0;
+        a.part = parts;
+        a.part_cap = part_cap;
+        a.stat = cgstat;
+        for (int k = T; k < T + K; k++) {
+            a.k = k;
+            a.first = k == 0;
+            a.want_norm = k == T + K - 1;
+            a.w = wbuf[k & 1];
+            a.v = wbuf[(k + 1) & 1];
+            mj::launch_z0_pass(a, s_);
+        }
+    };
+    if (!use_graphs) {
+        launch(st);
+        return;
+    }
+    const long key = ((long)g0 << 48) | ((long)recorded << 40) | ((long)T << 20) | K;
+    auto it = pass_graphs.find(key);
+    if (it == pass_graphs.end()) {
+        hipGraph_t g = nullptr;
+        hipGraphExec_t ex = nullptr;
+        MJ_CHECK(hipStreamBeginCapture(cap_st, hipStreamCaptureModeRelaxed));
+        try {
+            launch(cap_st);
+        } catch (...) {
+            (void)hipStreamEndCapture(cap_st, &g);
+            if (g) (void)hipGraphDestroy(g);
+            throw;
+        }
+        MJ_CHECK(hipStreamEndCapture(cap_st, &g));
+        const hipError_t e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
+        (void)hipGraphDestroy(g);
+        MJ_CHECK(e);
+        it = pass_graphs.emplace(key, ex).first;
+    }
+    MJ_CHECK(hipGraphLaunch(it->second, st));
+}
+
+// Z_0 J_n = b (eq:MOTInversion) from the extrapolated current in wbuf[0].
+//
+// By default most steps replay the iteration that CG took in an earlier step of the same march: its
+// three-term coefficients, recorded per right-hand side on the device, applied by k_z0_pass without inner
+// products (see there).  CG runs, and is recorded, at steps 1, 2, 4, ..., 64, 128, 192, ... (the
+// residuals change most as the wave enters, and one CG solve in 64 costs little), and
+// after a replay that missed the tolerance.  Every solve is tested on its own residual, so a record that
+// no longer fits costs passes, never accuracy.  What decides which steps run CG, and how many passes a
+// replay takes before its test, depends on the march alone and travels with its state.
+void mj_solver::solve_z0()
+{
+    auto base = [&] {
+        if (z0_method == 0 && lam_hi > 0.0) solve_z0_chebyshev();
+        else solve_cg();
+    };
+    if (!replays) {
+        base();
+        return;
+    }
+    if (rp.hold > 0) {
+        rp.hold--;
+        base();
+        return;
+    }
+    const bool scheduled = n <= 64 ? (n & (n - 1)) == 0 : n % 64 == 0;
+    if (rp.learn || scheduled) learn();
+    else replay();
+}
+
+// A CG solve that records its coefficients.  It runs on to 1/100 of the tolerance, so that replays have
+// a few passes to spare.
+void mj_solver::learn()
+{
+    mj::CgArg a = cg_arg();
+    a.stop2 = 1e-4 * a.tol2;
+    a.coef = coef;
+    a.rhist = rhist;
+    const bool done = run_cg(a, cg_guess);
+    std::vector<double> h((size_t)nrhs * mj::kMaxCoef);
+    MJ_CHECK(hipMemcpyAsync(h.data(), rhist, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
+    MJ_CHECK(hipStreamSynchronize(st));
+    int K = 0, L = 0;
+    for (int i = 0; i < nrhs; i++) {
+        const int its = std::min(cgstat_h[i].iters, mj::kMaxCoef - 1);
+        int k = 0;
+        while (k < its && !(h[(size_t)i * mj::kMaxCoef + k] <= a.tol2)) k++;
+        K = std::max(K, k);
+        L = std::max(L, cgstat_h[i].iters);
+    }
+    cg_guess = L + 1;
+    rp.K = rp.K0 = K;
+    rp.L = std::min(L, mj::kMaxCoef);
+    rp.learn = !done || K < 1;   // nothing to replay: zero right-hand sides, or no convergence
+    if (done && L > mj::kMaxCoef - 4) {   // too long to record
+        rp.learn = 1;
+        rp.hold = 64;
+    }
+}
+
+void mj_solver::replay()
+{
+    const int G = group_size(), K = rp.K;
+    for (int g0 = 0; g0 < nrhs; g0 += G) enqueue_passes(true, g0, std::min(nrhs, g0 + G), 0, K + 1);
+    bool done = read_status();
+    int total = K;
+    // groups that missed go on, two passes at a time, so that the solution stays in the same wbuf
+    for (int more = 0; !done && more < 2 && total + 2 < std::min(rp.L, cg_maxit); more++) {
+        for (int g0 = 0; g0 < nrhs; g0 += G) {
+            const int g1 = std::min(nrhs, g0 + G);
+            bool ok = true;
+            for (int i = g0; i < g1; i++) ok = ok && cgstat_h[i].done;
+            if (!ok) enqueue_passes(true, g0, g1, total + 1, 2);
+        }
+        total += 2;
+        done = read_status();
+    }
+    w_end = wbuf[(total + 1) & 1];
+    if (done) {
+        double res = 0.0;
+        for (int i = 0; i < nrhs; i++) res = std::max(res, cgstat_h[i].res);
+        rp.fails = 0;
+        rp.K = total;
+        if (res <= 0.1 * cg_rtol && K > 1) rp.K = total - 1;   // a pass gains a factor of 2 to 4
+        if (rp.K > rp.K0 + 3) rp.learn = 1;
+        return;
+    }
+    for (int i = 0; i < nrhs; i++)
+        if (!std::isfinite(cgstat_h[i].bb) || cgstat_h[i].bb > 1e200) return;   // the march ends (check_growth)
+    // the record does not fit any more: CG from where the passes ended, and a new record in the next step;
+    // after several misses in a row, some steps without replays
+    mj::CgArg a = cg_arg();
+    a.w = w_end;
+    run_cg(a, cg_guess);
+    for (int i = 0; i < nrhs; i++) cgstat_h[i].iters += total;
+    rp.learn = 1;
+    rp.fails = std::min(rp.fails + 1, 6);
+    if (rp.fails >= 2) rp.hold = 4 << rp.fails;
 }
 
 // Number of eigenvalues below x of the symmetric tridiagonal matrix (diagonal a, off-diagonal
@@ -690,38 +912,36 @@ static int sturm_count(const std::vector<double> &a, const std::vector<double> &
 void mj_solver::estimate_spectrum()
 {
     lam_lo = lam_hi = 0.0;
-    cheb_rho.clear();   // the recurrence scalars and the captured batches hold the old bounds
-    clear_graphs();
     mj::CgArg a = cg_arg();
     a.nrhs = 1;
-    a.tol2 = 0.0;   // run every iteration
+    a.tol2 = a.stop2 = 0.0;   // run every iteration
+    a.coef = coef;
     const size_t Mp = (size_t)(U + 2) * (V + 2) * (W + 2);
-    MJ_CHECK(hipMemsetAsync(uy, 0, sizeof(double) * Mp * 3, st));
-    mj::launch_fill_trial(schi, M, 1, rhs, y, st);
-    mj::launch_cg_init(a, st);
-    std::vector<double> alpha, beta;
-    mj::CgScalars sc{};
-    MJ_CHECK(hipMemcpyAsync(&sc, scal, sizeof sc, hipMemcpyDeviceToHost, st));
-    MJ_CHECK(hipStreamSynchronize(st));
-    const double rz0 = sc.rz[0];
-    if (!(rz0 > 0.0) || !std::isfinite(rz0)) {
-        restart();
-        return;
-    }
+    MJ_CHECK(hipMemsetAsync(wbuf[0], 0, sizeof(double) * Mp * 3, st));
+    mj::launch_fill_trial(schi, U, V, W, bh, st);
     const int m = std::min(40, 3 * (int)std::min<long>(M, 1000));
+    mj::launch_cg_init(a, st);
     for (int it = 0; it < m; it++) {
         mj::launch_cg_a(a, it, st);
         mj::launch_cg_b(a, it, st);
-        MJ_CHECK(hipMemcpyAsync(&sc, scal, sizeof sc, hipMemcpyDeviceToHost, st));
-        MJ_CHECK(hipStreamSynchronize(st));
-        const double rz = sc.rz[it & 1], rzn = sc.rz[(it + 1) & 1], pq = sc.pq;
-        if (!(pq > 0.0) || !std::isfinite(pq) || !(rz > 0.0)) break;
-        alpha.push_back(rz / pq);
-        beta.push_back(rzn / rz);
-        // the Krylov space is exhausted (tiny grids): the residual has vanished
-        if (!(rzn > 1e-28 * rz0)) break;
     }
+    std::vector<double> ab(2 * (size_t)m);
+    MJ_CHECK(hipMemcpyAsync(ab.data(), coef, sizeof(double) * ab.size(), hipMemcpyDeviceToHost, st));
     restart();
+    // alpha_j = a_j and beta_j = b_{j+1} a_j / a_{j+1} of the recorded iterations, up to where the Krylov
+    // space is exhausted (tiny grids: the residual has vanished)
+    std::vector<double> alpha, beta;
+    double rz = 1.0;
+    for (int j = 0; j < m; j++) {
+        if (!(ab[2 * j] > 0.0) || !std::isfinite(ab[2 * j])) break;
+        if (j > 0) {
+            const double bj = ab[2 * j + 1] * ab[2 * j - 2] / ab[2 * j];
+            rz *= bj;
+            if (!(rz > 1e-28)) break;
+            beta.push_back(bj);
+        }
+        alpha.push_back(ab[2 * j]);
+    }
     const size_t k = alpha.size();
     if (k == 0) return;
     std::vector<double> d(k), e(k, 0.0);
@@ -748,152 +968,52 @@ void mj_solver::estimate_spectrum()
     if (!(emin > 0.0) || !(emax >= emin)) return;
     lam_lo = 0.9 * emin;
     lam_hi = 1.05 * emax;
+    // the three-term coefficients of the Chebyshev iteration for these bounds
+    const double theta = 0.5 * (lam_hi + lam_lo), rho = (lam_hi - lam_lo) / (lam_hi + lam_lo);
+    std::vector<double> cc(2 * ((size_t)cg_maxit + 2));
+    double om = 1.0;
+    for (size_t j = 0; j < cc.size() / 2; j++) {
+        om = j == 0 ? 1.0 : j == 1 ? 1.0 / (1.0 - 0.5 * rho * rho) : 1.0 / (1.0 - 0.25 * om * rho * rho);
+        cc[2 * j] = om / theta;
+        cc[2 * j + 1] = om - 1.0;
+    }
+    MJ_CHECK(hipMemcpy(ccoef, cc.data(), sizeof(double) * cc.size(), hipMemcpyHostToDevice));
 }
 
-// The Z_0 solve by Chebyshev iteration (k_cheb_*): one stencil pass per iteration and no inner
-// products, so no reductions inside the iteration.  The passes of a solve are enqueued in
-// batches; only the last pass of a batch computes |r|^2, and the host reads the outcome once per
-// batch.  The first batch has as many passes as the last solve needed, from its observed
-// reduction per pass and its initial residual; without a last solve, the host first reads
-// |r_0| / |b| and uses the convergence factor of the Chebyshev polynomials for the estimated
-// spectrum.
-//
-// Right-hand sides are solved in groups, one group after the other, so that the vectors a pass
-// streams for its group (y, r and the two directions: about 6 x 3 x 8 bytes per voxel and
-// right-hand side) stay within kChebGroupBytes, which the device's last-level cache largely
-// holds from one pass to the next.  At 64^3 the solve per right-hand side took 0.27 ms in a
-// batch of 8 and 0.41 ms in a batch of 16 (0.31 in 4, 0.42 alone).
+// The Z_0 solve by Chebyshev iteration on the estimated spectrum: three-term passes with its
+// coefficients, as many as the last solve needed before the first test, then as many more as the
+// polynomials' convergence factor asks for.  An iteration gains the factor rho, so the next solve takes
+// fewer passes by what this one's residual fell short of the tolerance.
 void mj_solver::solve_z0_chebyshev()
 {
-    mj::ChebArg a{};
-    a.cg = cg_arg();
-    a.r = q;
-    const double theta = 0.5 * (lam_hi + lam_lo), delta = 0.5 * (lam_hi - lam_lo);
-    a.inv_theta = 1.0 / theta;
-    double *ebuf[2] = {u, e2};
     const double kappa = lam_hi / lam_lo;
-    const double rho_th = (std::sqrt(kappa) - 1.0) / (std::sqrt(kappa) + 1.0);
-    const double tol2 = cg_rtol * cg_rtol;
-    // the recurrence scalars by pass index: rho_0 = delta / theta, rho_{k+1} = 1 / (2 theta / delta - rho_k)
-    if ((int)cheb_rho.size() < cg_maxit + 1) {
-        cheb_rho.assign((size_t)cg_maxit + 1, 0.0);
-        cheb_rho[0] = delta / theta;
-        for (int k = 0; k < cg_maxit; k++) cheb_rho[(size_t)k + 1] = 1.0 / (2.0 * theta / delta - cheb_rho[(size_t)k]);
+    const double lrho = std::log((std::sqrt(kappa) - 1.0) / (std::sqrt(kappa) + 1.0));
+    const int G = group_size();
+    auto passes = [&](int T, int K) {
+        for (int g0 = 0; g0 < nrhs; g0 += G) enqueue_passes(false, g0, std::min(nrhs, g0 + G), T, K);
+        return read_status();
+    };
+    auto worst = [&] {
+        double res = 0.0;
+        for (int i = 0; i < nrhs; i++) res = std::max(res, std::isfinite(cgstat_h[i].res) ? cgstat_h[i].res : 0.0);
+        return res;
+    };
+    auto steps = [&](double ratio) { return lrho < 0.0 ? std::log(ratio) / lrho : 1.0; };
+    int total = std::max(1, std::min(cg_maxit, cheb_pred > 0 ? cheb_pred : (int)std::ceil(steps(cg_rtol)) + 1));
+    bool done = passes(0, total + 1);
+    while (!done && total < cg_maxit) {
+        const double res = worst();
+        if (!(res > cg_rtol)) break;   // not finite
+        const int K = std::max(1, std::min(cg_maxit - total, (int)std::ceil(steps(cg_rtol / res)) + 1));
+        done = passes(total + 1, K);
+        total += K;
     }
-    // the kernels of one batch: (the initial residual and) passes T .. T + K - 1, the last with the
-    // check; their arguments depend only on (group, T, K), so a captured batch replays unchanged
-    auto launch_batch = [&](bool with_init, int T, int K, hipStream_t s_) {
-        if (with_init) {
-            a.e_out = ebuf[0];
-            a.passes = 0;
-            mj::launch_cheb_init(a, s_);
-        }
-        for (int j = 0; j < K; j++) {
-            const int k = T + j;
-            a.c1 = cheb_rho[(size_t)k + 1] * cheb_rho[(size_t)k];
-            a.c2 = 2.0 * cheb_rho[(size_t)k + 1] / delta;
-            a.e_in = ebuf[k & 1];
-            a.e_out = ebuf[(k + 1) & 1];
-            a.want_norm = j == K - 1;
-            a.passes = k + 1;
-            mj::launch_cheb_pass(a, s_);
-        }
-    };
-    auto enqueue = [&](bool with_init, int T, int K) {
-        if (!use_graphs) {
-            launch_batch(with_init, T, K, st);
-            return;
-        }
-        const long key = ((long)a.rhs0 << 48) | ((long)with_init << 40) | ((long)T << 20) | K;
-        auto it = cheb_graphs.find(key);
-        if (it == cheb_graphs.end()) {
-            hipGraph_t g = nullptr;
-            hipGraphExec_t ex = nullptr;
-            MJ_CHECK(hipStreamBeginCapture(cap_st, hipStreamCaptureModeRelaxed));
-            try {
-                launch_batch(with_init, T, K, cap_st);
-            } catch (...) {
-                (void)hipStreamEndCapture(cap_st, &g);
-                if (g) (void)hipGraphDestroy(g);
-                throw;
-            }
-            MJ_CHECK(hipStreamEndCapture(cap_st, &g));
-            const hipError_t e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(g);
-            MJ_CHECK(e);
-            it = cheb_graphs.emplace(key, ex).first;
-        }
-        MJ_CHECK(hipGraphLaunch(it->second, st));
-    };
-    // passes to bring |r|^2 from rr to tol^2 bb at a reduction rho2 per pass
-    auto passes_for = [&](double rr, double bb, double rho2) {
-        if (!(rr > tol2 * bb) || !(bb > 0.0)) return 0;
-        const double k = std::log(tol2 * bb / rr) / std::log(rho2);
-        return (int)std::ceil(std::max(1.0, k));
-    };
-    const size_t per_rhs = (size_t)6 * 3 * M * sizeof(double);
-    const int G = (int)std::max<size_t>(1, std::min<size_t>((size_t)nrhs, kChebGroupBytes / per_rhs));
-    int pred_all = 1;
-    bool predicted = false;   // a group that met its initial test at once leaves no prediction
-    for (int g0 = 0; g0 < nrhs; g0 += G) {
-        const int g1 = std::min(nrhs, g0 + G);
-        a.rhs0 = g0;
-        a.nr = g1 - g0;
-        auto read_status = [&] {
-            MJ_CHECK(hipMemcpyAsync(cgstat_h, cgstat, sizeof(mj::CgStatus) * nrhs, hipMemcpyDeviceToHost, st));
-            MJ_CHECK(hipStreamSynchronize(st));
-            bool done = true;
-            for (int i = g0; i < g1; i++) done = done && cgstat_h[i].done;
-            return done;
-        };
-        int K = std::min(cheb_pred, cg_maxit);
-        int total = 0;
-        bool done = false;
-        if (K <= 0) {
-            // no last solve: read |r_0| / |b| first, and use the Chebyshev polynomials' convergence factor
-            enqueue(true, 0, 0);
-            if (read_status()) continue;
-            K = 0;
-            for (int i = g0; i < g1; i++)
-                K = std::max(K, passes_for(cgstat_h[i].rr0, cgstat_h[i].bb, rho_th * rho_th) + 1);
-            K = std::max(1, std::min(K, cg_maxit));
-            enqueue(false, 0, K);
-        } else {
-            enqueue(true, 0, K);
-        }
-        total = K;
-        done = read_status();
-        while (!done && total < cg_maxit) {
-            // more passes, from the residual reached and the reduction seen so far
-            K = 1;
-            for (int i = g0; i < g1; i++) {
-                const mj::CgStatus &c = cgstat_h[i];
-                if (c.done) continue;
-                const double rr = c.res * c.res * c.bb;
-                double rho2 = rho_th * rho_th;
-                if (c.rr0 > 0.0 && rr > 0.0 && rr < c.rr0) rho2 = std::max(rho2, std::pow(rr / c.rr0, 1.0 / total));
-                if (!(rho2 < 1.0)) rho2 = 0.9;
-                K = std::max(K, passes_for(rr, c.bb, rho2) + 1);
-            }
-            K = std::min(K, cg_maxit - total);
-            enqueue(false, total, K);
-            total += K;
-            done = read_status();
-        }
-        // the next solve starts with the passes this one would have needed: its observed
-        // reduction per pass applied to its initial residual
-        predicted = true;
-        for (int i = g0; i < g1; i++) {
-            const mj::CgStatus &c = cgstat_h[i];
-            const double rr = c.res * c.res * c.bb;
-            double rho2 = rho_th * rho_th;
-            if (c.rr0 > 0.0 && rr > 0.0 && rr < c.rr0 && total > 0)
-                rho2 = std::max(rho2 * 0.25, std::pow(rr / c.rr0, 1.0 / total));
-            if (!(rho2 < 1.0)) rho2 = 0.9;
-            pred_all = std::max(pred_all, passes_for(c.rr0, c.bb, rho2));
-        }
-    }
-    if (predicted) cheb_pred = pred_all;
+    w_end = wbuf[(total + 1) & 1];
+    const double res = worst();
+    cheb_pred = total;
+    if (done && res > 0.0 && res < 0.5 * cg_rtol)
+        cheb_pred = std::max(1, total - (int)std::min(1000.0, std::floor(steps(2.0 * res / cg_rtol))));
+    else if (res == 0.0) cheb_pred = 0;
 }
 
 mj::EpiArg mj_solver::epi_arg() const
@@ -931,9 +1051,8 @@ mj::EpiArg mj_solver::epi_arg() const
     e.waves = waves_d;
     gl_half(8, e.glx8, e.glw8);
     e.gl = gl_d;
-    e.rhs = rhs;
-    e.y = y;
-    e.uy = uy;
+    e.b = bh;
+    e.w0 = wbuf[0];
     return e;
 }
 
@@ -1177,11 +1296,10 @@ void mj_solver::step(const StepIO &io)
     if (ev) MJ_CHECK(hipEventRecord(ev[4], st));
     solve_z0();
     double *Jn = Jr + (size_t)slotR(n) * nrhs * 3 * M;
-    mj::launch_cg_finish(y, schi, M, nrhs, Jn, io.Jout, st);
+    mj::launch_cg_finish(y, schi, w_end, U, V, W, nrhs, Jn, io.Jout, st);
     if (ev) MJ_CHECK(hipEventRecord(ev[5], st));
     if (io.adjoint) {
         mj::AdjArg a = adj_arg();
-        a.y = y;
         a.nu = Jn;
         a.bq = bq;
         a.lam = Lr + (size_t)slotR(n) * nrhs * 3 * M;
@@ -1331,13 +1449,14 @@ void mj_solver::restart()
     MJ_CHECK(hipMemsetAsync(p, 0, v, st));
     MJ_CHECK(hipMemsetAsync(q, 0, v, st));
     MJ_CHECK(hipMemsetAsync(y, 0, v, st));
-    // the Chebyshev directions: voxels whose eps changed to 1 must read as zero in the stencil
+    // voxels whose eps changed to 1 must read as zero in the stencil
     const size_t vp = sizeof(double) * (size_t)nrhs * 3 * (U + 2) * (V + 2) * (W + 2);
     MJ_CHECK(hipMemsetAsync(u, 0, vp, st));
-    MJ_CHECK(hipMemsetAsync(e2, 0, vp, st));
+    for (double *w : wbuf) MJ_CHECK(hipMemsetAsync(w, 0, vp, st));
     MJ_CHECK(hipStreamSynchronize(st));
     cg_guess = 8;
     cheb_pred = 0;
+    rp = Replay();
     n = 0;
 }
 
@@ -1594,13 +1713,16 @@ struct StateHeader {
     int32_t version, U, V, W, nrhs, ell, B, rdepth, Nx, Ny, Nz, Hp, B2, cheb_pred;
     int64_t n, ring_bytes, far_bytes, jr_bytes, outer_bytes;
 };
+// version 3 has the replayed passes of the Z_0 solve (their counts and coefficients) after the header;
+// version 2, without them, is read too: the solve then takes CG first
+constexpr int kStateVersion = 3;
 constexpr char kStateMagic[8] = {'M', 'J', 'S', 'T', 'A', 'T', 'E', '2'};
 }  // namespace
 
 size_t mj_solver::state_bytes() const
 {
     const size_t sp = (size_t)spec_plane(), v3 = (size_t)nrhs * 3;
-    return sizeof(StateHeader) + sizeof(double2) * (size_t)ell * v3 * sp +
+    return sizeof(StateHeader) + sizeof(Replay) + sizeof(double) * coef_count() + sizeof(double2) * (size_t)ell * v3 * sp +
            (farbuf ? sizeof(double2) * (size_t)B * v3 * sp : 0) + (gbuf ? sizeof(double2) * (size_t)B2 * v3 * sp : 0) +
            sizeof(double) * (size_t)rdepth * v3 * M;
 }
@@ -1610,7 +1732,7 @@ void mj_solver::get_state(void *buf) const
     const size_t sp = (size_t)spec_plane(), v3 = (size_t)nrhs * 3;
     StateHeader h{};
     std::memcpy(h.magic, kStateMagic, 8);
-    h.version = 2;
+    h.version = kStateVersion;
     h.U = U;
     h.V = V;
     h.W = W;
@@ -1633,6 +1755,10 @@ void mj_solver::get_state(void *buf) const
     std::memcpy(p, &h, sizeof h);
     p += sizeof h;
     MJ_CHECK(hipStreamSynchronize(st));
+    std::memcpy(p, &rp, sizeof rp);
+    p += sizeof rp;
+    MJ_CHECK(hipMemcpy(p, coef, sizeof(double) * coef_count(), hipMemcpyDeviceToHost));
+    p += sizeof(double) * coef_count();
     MJ_CHECK(hipMemcpy(p, ring, (size_t)h.ring_bytes, hipMemcpyDeviceToHost));
     p += h.ring_bytes;
     if (h.far_bytes) MJ_CHECK(hipMemcpy(p, farbuf, (size_t)h.far_bytes, hipMemcpyDeviceToHost));
@@ -1647,18 +1773,32 @@ void mj_solver::set_state(const void *buf, size_t bytes)
     StateHeader h;
     if (bytes < sizeof h) throw ArgError("state buffer too short");
     std::memcpy(&h, buf, sizeof h);
-    if (std::memcmp(h.magic, kStateMagic, 8) != 0 || h.version != 2) throw ArgError("not a march state");
+    if (std::memcmp(h.magic, kStateMagic, 8) != 0 || (h.version != kStateVersion && h.version != 2)) throw ArgError("not a march state");
     if (h.U != U || h.V != V || h.W != W || h.nrhs != nrhs || h.ell != ell || h.B != B || h.B2 != B2 ||
         h.Nx != Nx || h.Ny != Ny || h.Nz != Nz || h.Hp != Hp)
         throw ArgError("state of a solver with another grid, n_rhs, ell or time blocks");
     if (h.rdepth != rdepth) throw ArgError("state of a solver with another history depth (probes differ)");
-    if (bytes < state_bytes() || (size_t)h.ring_bytes + (size_t)h.far_bytes + (size_t)h.jr_bytes +
-                                         (size_t)h.outer_bytes + sizeof h != state_bytes())
+    const size_t solve_bytes = sizeof(Replay) + sizeof(double) * coef_count();
+    const size_t need = state_bytes() - (h.version == 2 ? solve_bytes : 0);
+    if (bytes < need || (size_t)h.ring_bytes + (size_t)h.far_bytes + (size_t)h.jr_bytes + (size_t)h.outer_bytes +
+                                (h.version == 2 ? 0 : solve_bytes) + sizeof h != need)
         throw ArgError("state buffer has the wrong size");
     if (h.n < 0 || h.n > INT32_MAX) throw ArgError("bad step count in the state");
     const char *p = (const char *)buf + sizeof h;
+    Replay rp_new;
+    if (h.version != 2) {
+        std::memcpy(&rp_new, p, sizeof rp_new);
+        if (rp_new.K < 0 || rp_new.K >= mj::kMaxCoef || rp_new.L < 0 || rp_new.L > mj::kMaxCoef || rp_new.fails < 0 ||
+            rp_new.hold < 0 || (rp_new.K < 1 && !rp_new.learn))
+            throw ArgError("bad solve record in the state");
+    }
     drop_side();
     MJ_CHECK(hipStreamSynchronize(st));
+    rp = rp_new;
+    if (h.version != 2) {
+        MJ_CHECK(hipMemcpy(coef, p + sizeof(Replay), sizeof(double) * coef_count(), hipMemcpyHostToDevice));
+        p += solve_bytes;
+    }
     MJ_CHECK(hipMemcpy(ring, p, (size_t)h.ring_bytes, hipMemcpyHostToDevice));
     p += h.ring_bytes;
     if (h.far_bytes) MJ_CHECK(hipMemcpy(farbuf, p, (size_t)h.far_bytes, hipMemcpyHostToDevice));
@@ -1732,8 +1872,27 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
     double *nu_r = (double *)talloc(sizeof(double) * (size_t)rdepth * vec, "adjoint history");
     double *lam_r = (double *)talloc(sizeof(double) * (size_t)rdepth * vec, "adjoint local history");
     MJ_CHECK(hipMemsetAsync(grad_dev, 0, sizeof(double) * M, st));
-    std::vector<int> pred_at((size_t)N + 2, 0);
-    int adj_pred = 0;
+    // what the solve of a segment's first step starts from (passes predicted or recorded), kept so that
+    // a recomputed segment repeats the original arithmetic; the transposed march has its own
+    struct SolveRecord {
+        int cheb_pred = 0;
+        Replay rp;
+    };
+    std::vector<SolveRecord> rec_at((size_t)C);
+    SolveRecord rec_adj;
+    double *coef_at = (double *)talloc(sizeof(double) * (size_t)(C + 1) * coef_count(), "recorded coefficients");
+    auto save_record = [&](SolveRecord &sr, int slot) {
+        sr = SolveRecord{cheb_pred, rp};
+        MJ_CHECK(hipMemcpyAsync(coef_at + (size_t)slot * coef_count(), coef, sizeof(double) * coef_count(),
+                                hipMemcpyDeviceToDevice, st));
+    };
+    auto load_record = [&](const SolveRecord &sr, int slot) {
+        cheb_pred = sr.cheb_pred;
+        rp = sr.rp;
+        if (!rp.learn)
+            MJ_CHECK(hipMemcpyAsync(coef, coef_at + (size_t)slot * coef_count(), sizeof(double) * coef_count(),
+                                    hipMemcpyDeviceToDevice, st));
+    };
     double2 *const ring_f = ring, *const far_f = farbuf, *const g_f = gbuf;
     double *const Jr_f = Jr;
     hipEvent_t tev[3];
@@ -1745,11 +1904,14 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
             if (!cgstat_h[i].done) noconv = true;
     };
     try {
-        // 1. forward; the Chebyshev prediction each step starts from is kept, so that a
-        // recomputed segment takes the same passes as the original steps
+        // 1. forward
         const int last0 = starts[C - 1];
+        int seg = 0;
         for (int t = 1; t <= N; t++) {
-            pred_at[(size_t)t] = cheb_pred;
+            if (seg < C && t == starts[(size_t)seg]) {
+                save_record(rec_at[(size_t)seg], seg);
+                seg++;
+            }
             StepIO io;
             io.Pout = Ehist + (size_t)(t - 1) * nrhs * np * 3;
             io.Bout = t >= last0 ? Bbuf + (size_t)(t - last0) * vec : nullptr;
@@ -1788,7 +1950,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
                             mj::fft3d_forward(fft, src, ring + (size_t)slotS(j) * nrhs * 3 * sp, 3 * nrhs, st);
                     }
                 }
-                cheb_pred = pred_at[(size_t)s0];
+                load_record(rec_at[(size_t)c], c);
                 for (int t = s0; t <= s1; t++) {
                     StepIO io;
                     io.skip_probes = true;
@@ -1806,7 +1968,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
             Lr = lam_r;
             bq = bqb;
             n = n_adj;
-            cheb_pred = adj_pred;
+            load_record(rec_adj, C);
             for (int j = s1; j >= s0; j--) {
                 mj::AdjArg a = adj_arg();
                 a.Ehist = Ehist;
@@ -1823,7 +1985,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
                 check_cg();
             }
             n_adj = n;
-            adj_pred = cheb_pred;
+            save_record(rec_adj, C);
             drop_side();
             ring = ring_f;
             farbuf = far_f;
@@ -1847,6 +2009,8 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
         bq = nullptr;
         for (void *q : tmp) da.put(q);
         for (auto &tv : tev) (void)hipEventDestroy(tv);
+        rp = Replay();
+        cheb_pred = 0;
         n = 0;
         throw;
     }
@@ -1859,6 +2023,8 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
     stat[17] = (double)npool * vec * sizeof(double);
     for (void *q : tmp) da.put(q);
     for (auto &tv : tev) (void)hipEventDestroy(tv);
+    rp = Replay();   // the next march records its own
+    cheb_pred = 0;
     n = 0;
     if (noconv) throw std::range_error("Z_0 solve did not converge");
 }

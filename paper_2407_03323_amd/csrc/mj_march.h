@@ -66,8 +66,8 @@ struct EpiArg {
     const WaveArg *waves;    // [nrhs]
     double glx8[8], glw8[8]; // 8-point rule on [-1/2, 1/2], weights summing to 1
     const double *gl;        // n-point rules on [-1/2, 1/2], n = 1..8: row n holds 8 nodes then 8 weights
-    double *rhs, *y;         // [nrhs][3][M]
-    double *uy;              // sqrt(chi) y0 in the zero-haloed layout [nrhs][3][(W+2)(V+2)(U+2)]
+    double *b;               // right-hand side of the Z_0 system, haloed [nrhs][3][(W+2)(V+2)(U+2)]
+    double *w0;              // extrapolated J_n the solve starts from, same layout
     // transposed march only
     const double *Lring;     // lambda history [depth][nrhs][3][M] (the local terms act on lambda)
     const double *G;         // adjoint source g_j [nrhs][3][M]
@@ -91,7 +91,7 @@ struct AdjArg {
     long npairs;
     double *G;               // out [nrhs][3][M]
     // lambda from the solve
-    const double *y, *schi, *c0, *bq, *nu;   // nu: [nrhs][3][M] of this step
+    const double *schi, *c0, *bq, *nu;   // nu: [nrhs][3][M] of this step
     double *lam;             // out [nrhs][3][M]
     // gradient
     const double *Bj;        // B_j [nrhs][3][M]
@@ -108,50 +108,65 @@ struct CgScalars {
 
 // per right-hand side, read back by the host in one copy
 struct CgStatus {
-    int done;                // converged (set by the first iteration whose test passes)
+    int done;                // the last test passed
+    int ended;               // CG: no further iteration runs (the stopping residual is reached)
     int iters;               // iterations taken
     double res;              // relative residual |r| / |b| at the last test
     double bb;               // |b|^2 of the solve's right-hand side (growth detector)
-    double rr0;              // |r_0|^2 of the initial guess (Chebyshev solve)
 };
+
+// Coefficients of a three-term iteration, (a_k, b_k) per pass k, and the squared relative residual
+// |r_k|^2 / |b|^2 that CG saw before pass k.
+constexpr int kMaxCoef = 192;
 
 struct CgArg {
     long M;
     int U, V, W;
     long Mp;                 // (U+2)(V+2)(W+2): vectors read by the stencil carry a zero halo
     int nrhs, nblk;          // nblk = ceil(M / 256): one voxel per thread
-    double tol2;
+    double tol2;             // squared relative residual of the convergence test
+    double stop2;            // ... at which the iteration ends (<= tol2)
     double d0, k0c;          // delta_0 and K_0^{xx}(0): c_0 and diag(A) follow from sqrt(chi)
     const double *schi;
-    const double *rhs, *uy;  // uy, u: haloed layout [nrhs][3][Mp]
-    double *y, *p, *q, *u;   // u = sqrt(chi) M^-1 r stands for the residual r
+    const double *b, *w;     // right-hand side and the current the solve starts from, haloed [nrhs][3][Mp]
+    double *y, *p, *q, *u;   // u = sqrt(chi) M^-1 r stands for the residual r (haloed)
     double *part;            // [nrhs][3][nblk]
     CgScalars *scal;         // [nrhs]
     CgStatus *stat;          // [nrhs]
+    double *coef;            // [nrhs][kMaxCoef][2]: receives the three-term coefficients of each iteration (or NULL)
+    double *rhist;           // [nrhs][kMaxCoef]: and its relative residuals (or NULL)
     // the solver's K_0(D) on its 27-point support [27][6] in device memory: entry
     // 13 + dx + 3 dy + 9 dz, components xx yy zz xy xz yz; read through the scalar cache
     const double *k0;
 };
 
-// Chebyshev iteration on the symmetrised Z_0 system with the Jacobi preconditioner M (see
-// mj_march.hip): no inner products, one stencil pass per iteration.
-struct ChebArg {
-    CgArg cg;                // geometry, sqrt(chi), rhs, uy = s y0, y, partial sums, status, tol2
-    double *r;               // residual [nrhs][3][M]
-    const double *e_in;      // s d_k in the zero-haloed layout [nrhs][3][Mp]
-    double *e_out;           // s d_{k+1}, same layout (the other of two buffers)
-    double c1, c2;           // d_{k+1} = c1 d_k + c2 M^-1 r_{k+1}
-    double inv_theta;        // d_0 = M^-1 r_0 / theta
-    int want_norm;           // the pass writes partial sums of |r|^2 and the check follows it
-    int passes;              // passes done when this one ends (recorded in the status)
-    int rhs0, nr;            // the right-hand sides rhs0 .. rhs0 + nr - 1 only (nr = 0: all of them)
+// One pass of a three-term iteration on Z_0 J = b with given coefficients (see mj_march.hip): no inner
+// products, one stencil application per pass.
+struct PassArg {
+    int px, py, pz;          // U + 2, V + 2, W + 2
+    long Mp;
+    double d0, k0c, tol2;
+    const double *chi;       // haloed [Mp], zero in the halo
+    const double *b;         // haloed [nrhs][3][Mp]
+    const double *w;         // w_k
+    double *v;               // w_{k-1} in, w_{k+1} out
+    const double *k0;
+    const double *coef;      // (a_k, b_k) of right-hand side r at coef + r coef_stride + 2 k
+    long coef_stride;
+    int coef_len;            // passes that coef holds
+    int k;
+    int first;               // the first pass of a solve: there is no w_{k-1}
+    int want_norm;           // sums |r_k|^2 and |b|^2 of w_k, and the test follows the pass
+    int rhs0, nr;            // the right-hand sides rhs0 .. rhs0 + nr - 1
+    double *part;            // [nrhs][2][blocks]
+    int part_cap;            // values per right-hand side that part holds
+    CgStatus *stat;          // [nrhs]
 };
-// r_0 = rhs - A y0, e_0 = s M^-1 r_0 / theta; reduces |r_0|^2 and |b|^2 into the status
-void launch_cheb_init(const ChebArg &a, hipStream_t st);
-// one iteration; with want_norm also the convergence check |r|^2 <= tol^2 |b|^2
-void launch_cheb_pass(const ChebArg &a, hipStream_t st);
-// pseudo-random right-hand side (zero where sqrt(chi) = 0) and zero initial guess
-void launch_fill_trial(const double *schi, long M, int nrhs, double *rhs, double *y, hipStream_t st);
+// blocks that a pass over nr right-hand sides takes for each of them
+int z0_pass_blocks(int U, int V, int W, int nr);
+void launch_z0_pass(const PassArg &a, hipStream_t st);
+// pseudo-random right-hand side (zero where sqrt(chi) = 0), haloed
+void launch_fill_trial(const double *schi, int U, int V, int W, double *b, hipStream_t st);
 
 // Scattered field at probe points: E^s_p(n) = sum_{k=0}^{ell} sum_s K_k(r_p - r_s) J_{n-k}(s)
 // over the source voxels s of the scatterer.  Pairs (p, s) are stored per probe sorted by the
@@ -198,7 +213,8 @@ void launch_cg_init(const CgArg &a, hipStream_t st);
 void launch_cg_a(const CgArg &a, int it, hipStream_t st);
 void launch_cg_b(const CgArg &a, int it, hipStream_t st);
 void launch_cg_end(const CgArg &a, int it, hipStream_t st);
-void launch_cg_finish(const double *y, const double *schi, long M, int nrhs, double *J, double *Jout,
-                      hipStream_t st);
+// J_n = sqrt(chi) y (w NULL) or w, haloed, into the real-space ring and, if not NULL, Jout
+void launch_cg_finish(const double *y, const double *schi, const double *w, int U, int V, int W, int nrhs, double *J,
+                      double *Jout, hipStream_t st);
 
 }  // namespace mj

@@ -677,9 +677,10 @@ __device__ inline double wave_average(const WaveArg &w, const EpiArg &e, int u, 
 }
 
 // b = E_n - P_{n-1} with P_{n-1} = sum_k c_k J_{n-k} - chi (K (*) J)  (eq:MOTInversion, eq:PnMOT);
-// c_1 = T(dt)/eps + delta_1, c_k = delta_k (k >= 2).  Writes the right-hand side of the
-// symmetrised system (b / sqrt(chi)) and the extrapolated initial guess
-// y0 = sum_{k=1}^{nguess} gx_k y_{n-k}, y = J / sqrt(chi).
+// c_1 = T(dt)/eps + delta_1, c_k = delta_k (k >= 2).  Writes b and the extrapolated current
+// sum_{k=1}^{nguess} gx_k J_{n-k} that the Z_0 solve starts from, both in the zero-haloed layout.
+// Voxels with chi = 0 are skipped: their current is zero, and so are their entries of the solve's
+// vectors (cleared whenever eps changes).
 template <bool CF>
 __global__ void __launch_bounds__(256) k_epilogue(EpiArg e)
 {
@@ -687,26 +688,17 @@ __global__ void __launch_bounds__(256) k_epilogue(EpiArg e)
     const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
     const int r = blockIdx.y;
     if (i >= M) return;
-    const double chi = e.chi[i], sc = e.schi[i];
+    const double chi = e.chi[i];
+    if (chi == 0.0) return;
     const int u = (int)(i % e.U), v = (int)((i / e.U) % e.V), z = (int)(i / ((long)e.U * e.V));
     const long Mp = (long)(e.U + 2) * (e.V + 2) * (e.W + 2);
     const long ip = ((long)(z + 1) * (e.V + 2) + (v + 1)) * (e.U + 2) + (u + 1);
-    if (sc == 0.0) {
-        // vacuum voxel: its current and every term of its row vanish
-        for (int c = 0; c < 3; c++) {
-            const long o = ((long)r * 3 + c) * M + i;
-            e.rhs[o] = 0.0;
-            e.y[o] = 0.0;
-            e.uy[((long)r * 3 + c) * Mp + ip] = 0.0;
-        }
-        return;
-    }
     const WaveArg w = e.waves[r];
     const double avg = wave_average<CF>(w, e, u, v, z, e.n * e.c_dt);
     const double c1 = 0.5 * e.inv_eps[i] + (e.nfir > 1 ? e.fir[1] : 0.0);
     const int kmax = min(e.nloc, e.n - 1);   // lags with a past current
     // initial guess of the Z_0 solve: the polynomial through the last nguess solutions,
-    // evaluated at step n (the current is smooth in time, so this lands close to y_n).  The
+    // evaluated at step n (the current is smooth in time, so this lands close to J_n).  The
     // three components of a past current are read together, eight lags at a time, and the
     // taps come through the scalar cache; each component still sums its lags in order.
     double b[3], g[3] = {0.0, 0.0, 0.0};
@@ -733,11 +725,9 @@ __global__ void __launch_bounds__(256) k_epilogue(EpiArg e)
     }
 #pragma unroll
     for (int c = 0; c < 3; c++) {
-        const long o = ((long)r * 3 + c) * M + i;
-        const double y0 = g[c] / sc;
-        e.rhs[o] = b[c] / sc;
-        e.y[o] = y0;
-        e.uy[((long)r * 3 + c) * Mp + ip] = sc * y0;
+        const long o = ((long)r * 3 + c) * Mp + ip;
+        e.b[o] = b[c];
+        e.w0[o] = g[c];
     }
 }
 
@@ -882,8 +872,11 @@ __device__ inline CgBlock cg_block()
 //   NV = 3 (k_cg_init): rz_0, r.r, b.b and the test at iteration 0
 //   NV = 1 (k_cg_a):    p.q
 //   NV = 2 (k_cg_b):    rz_{it+1}, r.r and the test at iteration it + 1
-// The test |r|^2 <= tol^2 |b|^2 (or b = 0) sets conv to the iteration that passed it.  The
+// |r|^2 <= stop^2 |b|^2 (or b = 0) ends the solve: conv is the iteration that reached it.  The
 // host enqueues iterations in batches, so launches past the end of a solve are routine.
+// With coef set, iteration it leaves its three-term coefficients there (see k_z0_pass):
+//   y_{k+1} = y_k + alpha_k p_k,  p_k = z_k + beta_{k-1} p_{k-1}
+//           = y_k + a_k z_k + b_k (y_k - y_{k-1}),  a_k = alpha_k,  b_k = alpha_k beta_{k-1} / alpha_{k-1}.
 template <int NV>
 __global__ void __launch_bounds__(1024) k_cg_reduce(CgArg a, int it)
 {
@@ -893,6 +886,8 @@ __global__ void __launch_bounds__(1024) k_cg_reduce(CgArg a, int it)
     // k_cg_a and k_cg_b of iteration it wrote no partials once the solve ended at conv <= it;
     // the scalars and the status stay as the end left them
     if (NV != 3 && a.scal[r].conv <= it) return;
+    if (NV == 3 && a.coef)   // passes beyond the last iteration leave w as it is
+        for (int i = threadIdx.x; i < 2 * kMaxCoef; i += 1024) a.coef[(size_t)r * 2 * kMaxCoef + i] = 0.0;
     const double *pr = a.part + (size_t)r * 3 * nb;
     double acc[NV];
 #pragma unroll
@@ -925,16 +920,24 @@ __global__ void __launch_bounds__(1024) k_cg_reduce(CgArg a, int it)
         sc->bb = acc[2];
     } else {
         iter = it + 1;
+        if (a.coef && it < kMaxCoef) {
+            // rz[(it + 1) & 1] still holds rz_{it-1}
+            double *c = a.coef + (size_t)r * 2 * kMaxCoef;
+            const double rz = sc->rz[it & 1], alpha = rz / sc->pq;
+            c[2 * it] = alpha;
+            c[2 * it + 1] = it > 0 ? alpha * (rz / sc->rz[(it + 1) & 1]) / c[2 * (it - 1)] : 0.0;
+        }
         sc->rz[iter & 1] = acc[0];
         sc->rr = acc[1];
     }
     const double rr = sc->rr, bb = sc->bb;
-    const bool pass = rr <= a.tol2 * bb || bb == 0.0;
-    sc->conv = pass ? iter : INT_MAX;
-    a.stat[r] = CgStatus{pass ? 1 : 0, iter, bb > 0.0 ? sqrt(rr / bb) : 0.0, bb, 0.0};
+    const bool pass = rr <= a.tol2 * bb || bb == 0.0, end = rr <= a.stop2 * bb || bb == 0.0;
+    if (a.rhist && iter < kMaxCoef) a.rhist[(size_t)r * kMaxCoef + iter] = bb > 0.0 ? rr / bb : 0.0;
+    sc->conv = end ? iter : INT_MAX;
+    a.stat[r] = CgStatus{pass ? 1 : 0, end ? 1 : 0, iter, bb > 0.0 ? sqrt(rr / bb) : 0.0, bb};
 }
 
-// r = rhs - A y0 (uy = s y0), u = s M^-1 r; partials rz, rr, bb
+// y0 = w / s, r = b / s - A y0, u = s M^-1 r; partials rz, rr, bb
 __global__ void __launch_bounds__(256) k_cg_init(CgArg a)
 {
     const CgBlock cb = cg_block();
@@ -944,24 +947,23 @@ __global__ void __launch_bounds__(256) k_cg_init(CgArg a)
     double v[3] = {0.0, 0.0, 0.0};   // rz, rr, bb
     if (i < M) {
         const double s = a.schi[i];
-        const double c0 = cg_c0(a, s);
-        const double md = s != 0.0 ? cg_md(a, s, c0) : 0.0;
-        double Ay[3] = {0.0, 0.0, 0.0};
         const long ip = haloed(a, i), bp = (long)r * 3 * a.Mp;
         if (s != 0.0) {
-            double Ku[3], ctr[3];
-            stencil_apply(a, a.uy + bp, ip, Ku, ctr);
-            for (int c = 0; c < 3; c++) Ay[c] = c0 * a.y[base + c * M + i] - s * Ku[c];
-        }
-        for (int c = 0; c < 3; c++) {
-            const long o = base + c * M + i;
-            const double b = a.rhs[o];
-            const double rv = s != 0.0 ? b - Ay[c] : 0.0;
-            const double zv = md * rv;
-            a.u[bp + c * a.Mp + ip] = s * zv;
-            v[0] += rv * zv;
-            v[1] += rv * rv;
-            v[2] += b * b;
+            const double c0 = cg_c0(a, s), md = cg_md(a, s, c0), inv_s = 1.0 / s;
+            double Kw[3], wc[3];
+            stencil_apply(a, a.w + bp, ip, Kw, wc);
+            for (int c = 0; c < 3; c++) {
+                const double y = wc[c] * inv_s, b = a.b[bp + c * a.Mp + ip] * inv_s;
+                const double rv = b - (c0 * y - s * Kw[c]);
+                const double zv = md * rv;
+                a.y[base + c * M + i] = y;
+                a.u[bp + c * a.Mp + ip] = s * zv;
+                v[0] += rv * zv;
+                v[1] += rv * rv;
+                v[2] += b * b;
+            }
+        } else {
+            for (int c = 0; c < 3; c++) a.u[bp + c * a.Mp + ip] = 0.0;
         }
     }
     block_partials<3>(v, a.part + (size_t)r * 3 * gridDim.x, gridDim.x, cb.bx);
@@ -1046,19 +1048,24 @@ __global__ void __launch_bounds__(256) k_cg_b(CgArg a, int it)
     block_partials<2>(v, a.part + (size_t)r * 3 * gridDim.x, gridDim.x, cb.bx);
 }
 
-// J_n = sqrt(chi) y into the real-space ring (and optionally the caller's output)
-__global__ void k_cg_finish(const double *__restrict__ y, const double *__restrict__ schi, long M, int nrhs,
-                            double *__restrict__ J, double *__restrict__ Jout)
+// J_n = sqrt(chi) y, or w (haloed) when given, into the real-space ring (and optionally the caller's output)
+__global__ void k_cg_finish(const double *__restrict__ y, const double *__restrict__ schi,
+                            const double *__restrict__ w, int U, int V, int W, int nrhs, double *__restrict__ J,
+                            double *__restrict__ Jout)
 {
+    const long M = (long)U * V * W;
     const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
     if (i >= M) return;
-    const double s = schi[i];
+    const double s = w ? 0.0 : schi[i];
+    const long Mp = (long)(U + 2) * (V + 2) * (W + 2);
+    const int u = (int)(i % U), v = (int)((i / U) % V), z = (int)(i / ((long)U * V));
+    const long ip = ((long)(z + 1) * (V + 2) + (v + 1)) * (U + 2) + (u + 1);
     for (int r = 0; r < nrhs; r++)
         for (int c = 0; c < 3; c++) {
             const long o = ((long)r * 3 + c) * M + i;
-            const double v = s * y[o];
-            J[o] = v;
-            if (Jout) Jout[o] = v;
+            const double x = w ? w[((long)r * 3 + c) * Mp + ip] : s != 0.0 ? s * y[o] : 0.0;
+            J[o] = x;
+            if (Jout) Jout[o] = x;
         }
 }
 
@@ -1091,182 +1098,251 @@ void launch_cg_end(const CgArg &a, int it, hipStream_t st)
     hipLaunchKernelGGL(k_cg_a, dim3(a.nblk, a.nrhs), dim3(256), 0, st, a, it, 1);
     MJ_CHECK(hipGetLastError());
 }
-void launch_cg_finish(const double *y, const double *schi, long M, int nrhs, double *J, double *Jout,
-                      hipStream_t st)
+void launch_cg_finish(const double *y, const double *schi, const double *w, int U, int V, int W, int nrhs, double *J,
+                      double *Jout, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_cg_finish, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, y, schi, M, nrhs, J, Jout);
+    const long M = (long)U * V * W;
+    hipLaunchKernelGGL(k_cg_finish, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, y, schi, w, U, V, W, nrhs, J,
+                       Jout);
     MJ_CHECK(hipGetLastError());
 }
 
-// ---------------------------------------------------------------------------- Chebyshev
-// Chebyshev iteration (the three-term recurrence of Saad, "Iterative Methods for Sparse Linear
-// Systems", Alg. 12.1, with the Jacobi preconditioner) on A y = rhs, for the eigenvalues of
-// M^-1 A in [theta - delta, theta + delta]:
-//   r_0 = rhs - A y_0,  d_0 = M^-1 r_0 / theta,
-//   y_{k+1} = y_k + d_k,  r_{k+1} = r_k - A d_k,  d_{k+1} = c1_k d_k + c2_k M^-1 r_{k+1},
-// with c1_k = rho_{k+1} rho_k, c2_k = 2 rho_{k+1} / delta, rho_0 = delta / theta,
-// rho_{k+1} = 1 / (2 theta / delta - rho_k): scalars that do not depend on the data, so the
-// iteration needs no inner products.  One pass per iteration: A d_k needs d_k at the 26
-// neighbours, so d is kept as e = s d in the zero-haloed stencil layout, in two buffers that
-// the passes alternate.  Voxels with s = 0 stay out (their e is zero and y is zero).
-
-// Both Chebyshev kernels come in two builds.  OCC holds the registers to 7 waves per SIMD
-// (68 VGPRs against 141), which hides more latency once the launch fills the chip (104^3:
-// 1.12 against 1.23 ms per solve; 16 right-hand sides at 64^3: 5.98-6.07 against 6.12-6.36 ms).
-// On small grids, whose few blocks cannot use the waves, the loads each thread keeps in flight
-// matter more (32^3: 0.240 against 0.192 ms, 48^3: 0.272 against 0.258 ms).  The arithmetic is
-// the same.
-constexpr long kChebOccBlocks = 2048;   // blocks per launch from which OCC is used
-
-// r_0, e_0 and the partial sums of |r_0|^2 and |b|^2
-template <bool OCC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC ? 6 : 1))) k_cheb_init(ChebArg a)
+// ---------------------------------------------------------------------------- three-term passes
+// A Krylov or Chebyshev iteration on the Jacobi-preconditioned system can be written without search
+// directions and residuals (Golub & Varga 1961; Rutishauser's three-term form of CG):
+//   y_{k+1} = y_k + a_k M^-1 (b / s - A y_k) + b_k (y_k - y_{k-1}),   s = sqrt(chi).
+// In w = s y, the current itself, no square root is left: with rho_k = b - c_0 w_k + chi (K_0 (*) w_k),
+//   w_{k+1} = w_k + a_k rho_k / (c_0 - chi K_0^{xx}(0)) + b_k (w_k - w_{k-1}).
+// A pass reads w_k (through the stencil), w_{k-1}, b and chi and writes w_{k+1} over w_{k-1}: 104 bytes per
+// voxel, one launch, no inner product, where the two-term Chebyshev pass it replaces moved 152 and a CG
+// iteration 256 bytes in four launches.  The residual is formed anew in every pass, so no recurrence
+// drifts; the test after pass k is that of w_k, and the pass has already gone one update further.
+//
+// The coefficients (a_k, b_k) of each right-hand side come from device memory: those of the Chebyshev
+// iteration on the estimated spectrum, or those that CG took in an earlier step of the same march.
+// The residuals of successive steps weight the spectrum alike, so the residual polynomial that CG found
+// best for one step serves the next ones: at 104^3 13 passes where the Chebyshev iteration needs 24,
+// at 64^3 18 against 26, at 32^3 23 against 29, within one pass of CG itself 32 steps later.
+//
+// What bounds it: memory, at 104 bytes a voxel (104^3: 18.9 us a pass, 6.5 TB/s on data that the
+// last-level cache holds), once the stencil's 81 loads a voxel are out of the way (62 us through L1
+// with one thread a voxel).  Lanes hold consecutive positions of a haloed plane, so x neighbours come by
+// lane shifts; K_0 is even or odd in every axis, so a row's y and x neighbours are folded into sums and
+// differences first and every product serves a pair or a quadruple of them; each thread walks ZT planes
+// and adds a plane's part to the three outputs it touches: 9 loads, 36 products and 26 additions per
+// plane and voxel.  The outermost lanes of a wave only feed their neighbours (62 outputs in 64 lanes).
+__device__ inline double lane_next(double x)   // the value of lane + 1 (0 in the last lane)
 {
-    const CgArg &g = a.cg;
-    const CgBlock cb = cg_block();
-    const int r = cb.r + a.rhs0;
-    const long M = g.M, base = (long)r * 3 * M;
-    const long i = cb.bx * (long)blockDim.x + threadIdx.x;
-    double v[2] = {0.0, 0.0};   // rr, bb
-    if (i < M) {
-        const double s = g.schi[i];
-        const long ip = haloed(g, i), bp = (long)r * 3 * g.Mp;
-        if (s != 0.0) {
-            const double c0 = cg_c0(g, s), md = cg_md(g, s, c0);
-            double Ku[3], ctr[3];
-            stencil_apply(g, g.uy + bp, ip, Ku, ctr);
-            for (int c = 0; c < 3; c++) {
-                const long o = base + c * M + i;
-                const double b = g.rhs[o];
-                const double rv = b - (c0 * g.y[o] - s * Ku[c]);
-                a.r[o] = rv;
-                a.e_out[bp + c * g.Mp + ip] = s * md * rv * a.inv_theta;
-                v[0] += rv * rv;
-                v[1] += b * b;
-            }
-        } else {
-            for (int c = 0; c < 3; c++) {
-                a.r[base + c * M + i] = 0.0;
-                a.e_out[bp + c * g.Mp + ip] = 0.0;
-            }
-        }
-    }
-    block_partials<2>(v, g.part + (size_t)r * 3 * gridDim.x, gridDim.x, cb.bx);
+    const int lo = __double2loint(x), hi = __double2hiint(x);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, 0x130, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, lo, 0x130, 0xf, 0xf, true));
+}
+__device__ inline double lane_prev(double x)   // the value of lane - 1 (0 in the first lane)
+{
+    const int lo = __double2loint(x), hi = __double2hiint(x);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, 0x138, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, lo, 0x138, 0xf, 0xf, true));
 }
 
-// one iteration: y += d, r -= A d, d' = c1 d + c2 M^-1 r (partial |r|^2 when asked)
-template <bool OCC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC ? 6 : 1))) k_cheb_pass(ChebArg a)
+// the (plane, z) tiling of a pass: waves along a haloed plane (positions px + 1 .. plane - px - 2), ZT planes deep
+struct PassTiles {
+    int nq, nz, qg;   // waves along the plane, chunks of planes, blocks along the plane
+    __host__ __device__ PassTiles(int px, int py, int pz, int zt)
+        : nq((px * py - 2 * px - 2 + 61) / 62), nz((pz - 2 + zt - 1) / zt), qg((nq + 3) / 4)
+    {
+    }
+};
+
+template <int ZT, bool NORM>
+__global__ void __launch_bounds__(256) k_z0_pass(PassArg a)
 {
-    const CgArg &g = a.cg;
-    const CgBlock cb = cg_block();
-    const int r = cb.r + a.rhs0;
-    const long M = g.M, base = (long)r * 3 * M;
-    const long i = cb.bx * (long)blockDim.x + threadIdx.x;
-    double v[1] = {0.0};
-    if (i < M) {
-        const double s = g.schi[i];
-        if (s != 0.0) {
-            const long ip = haloed(g, i), bp = (long)r * 3 * g.Mp;
-            double Ke[3], ectr[3];
-            stencil_apply(g, a.e_in + bp, ip, Ke, ectr);
-            const double c0 = cg_c0(g, s), md = cg_md(g, s, c0), inv_s = 1.0 / s;
-            for (int c = 0; c < 3; c++) {
-                const long o = base + c * M + i;
-                const double d = ectr[c] * inv_s;
-                g.y[o] += d;
-                const double rv = a.r[o] - (c0 * d - s * Ke[c]);
-                a.r[o] = rv;
-                a.e_out[bp + c * g.Mp + ip] = s * (a.c1 * d + a.c2 * md * rv);
-                v[0] += rv * rv;
+    const int lane = threadIdx.x & 63;
+    const int px = a.px, plane = px * a.py;
+    const PassTiles tl(px, a.py, a.pz, ZT);
+    unsigned lb = xcd_block(blockIdx.x, gridDim.x);
+    const int bx = lb % (tl.qg * tl.nz), r = a.rhs0 + lb / (tl.qg * tl.nz);
+    const int iq = (bx % tl.qg) * 4 + (threadIdx.x >> 6), z0 = 1 + (bx / tl.qg) * ZT;
+    // every lane loads (the shifts need all of them), from a row that keeps its neighbours inside the plane
+    const int q = px + iq * 62 + lane, ql = min(q, plane - px - 1);
+    const bool mine = iq < tl.nq && lane >= 1 && lane <= 62 && q <= plane - px - 2;
+    const long base = (long)r * 3 * a.Mp;
+    const double *w0 = a.w + base, *w1 = w0 + a.Mp, *w2 = w1 + a.Mp;
+    const double ca = kconst(a.coef)[r * a.coef_stride + 2 * a.k], cb = kconst(a.coef)[r * a.coef_stride + 2 * a.k + 1];
+    kconst_t *K = kconst(a.k0);
+    // K^{c}(dx, dy, dz), dx, dy, dz in {0, 1}
+    auto k = [&](int dx, int dy, int dz, int c) __attribute__((always_inline)) {
+        return K[6 * (13 + dx + 3 * dy + 9 * dz) + c];
+    };
+    double L[2][9], O[2][7];   // rows of the next two planes; chi, b, w_{k-1} of the next two outputs
+    auto load_rows = [&](int z, double(&l)[9]) __attribute__((always_inline)) {
+        const long o = (long)min(z, a.pz - 1) * plane + ql;
+        l[0] = w0[o - px]; l[1] = w0[o]; l[2] = w0[o + px];
+        l[3] = w1[o - px]; l[4] = w1[o]; l[5] = w1[o + px];
+        l[6] = w2[o - px]; l[7] = w2[o]; l[8] = w2[o + px];
+    };
+    auto load_own = [&](int z, double(&l)[7]) __attribute__((always_inline)) {
+        const long o = (long)min(z, a.pz - 1) * plane + ql, j = base + o;
+        l[0] = a.chi[o];
+        l[1] = a.b[j]; l[2] = a.b[j + a.Mp]; l[3] = a.b[j + 2 * a.Mp];
+        if (!a.first) { l[4] = a.v[j]; l[5] = a.v[j + a.Mp]; l[6] = a.v[j + 2 * a.Mp]; }
+        else l[4] = l[5] = l[6] = 0.0;
+    };
+    load_rows(z0 - 1, L[0]);
+    load_rows(z0, L[1]);
+    double P[3] = {0.0, 0.0, 0.0}, Q[3] = {0.0, 0.0, 0.0}, wc[3] = {0.0, 0.0, 0.0};   // sums of planes z - 1 and z; w_k at z - 1
+    double nrm[2] = {0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < ZT + 2; i++) {
+        const int z = z0 - 1 + i;
+        const double xm = L[i & 1][0], x0 = L[i & 1][1], xp = L[i & 1][2];
+        const double ym = L[i & 1][3], y0 = L[i & 1][4], yp = L[i & 1][5];
+        const double zm = L[i & 1][6], zz = L[i & 1][7], zp = L[i & 1][8];
+        if (i + 2 < ZT + 2) load_rows(z + 2, L[i & 1]);
+        if (i >= 1 && i <= ZT) load_own(z, O[i & 1]);
+        __builtin_amdgcn_sched_barrier(0);   // these loads stay ahead of the arithmetic
+        // even (e) and odd (d) part along y; E = left + right, D = right - left along x
+        const double xe = xm + xp, xd = xp - xm, ye = ym + yp, yd = yp - ym, ze = zm + zp, zd = zp - zm;
+        const double x0l = lane_prev(x0), x0r = lane_next(x0), xel = lane_prev(xe), xer = lane_next(xe);
+        const double y0l = lane_prev(y0), y0r = lane_next(y0), yel = lane_prev(ye), yer = lane_next(ye);
+        const double z0l = lane_prev(zz), z0r = lane_next(zz), zel = lane_prev(ze), zer = lane_next(ze);
+        const double ydl = lane_prev(yd), ydr = lane_next(yd), zdl = lane_prev(zd), zdr = lane_next(zd);
+        const double xE0 = x0l + x0r, xE1 = xel + xer, xD0 = x0r - x0l, xD1 = xer - xel;
+        const double xDD = lane_next(xd) - lane_prev(xd);
+        const double yE0 = y0l + y0r, yE1 = yel + yer, yDD = ydr - ydl, yDE = ydl + ydr;
+        const double zE0 = z0l + z0r, zE1 = zel + zer, zD0 = z0r - z0l, zD1 = zer - zel, zDE = zdl + zdr;
+        // this plane's part of its own output (C), and of those above and below: even S, odd T in dz
+        const double C[3] = {k(0, 0, 0, 0) * x0 + k(1, 0, 0, 0) * xE0 + k(0, 1, 0, 0) * xe + k(1, 1, 0, 0) * xE1 +
+                                 k(1, 1, 0, 3) * yDD,
+                             k(0, 0, 0, 1) * y0 + k(1, 0, 0, 1) * yE0 + k(0, 1, 0, 1) * ye + k(1, 1, 0, 1) * yE1 +
+                                 k(1, 1, 0, 3) * xDD,
+                             k(0, 0, 0, 2) * zz + k(1, 0, 0, 2) * zE0 + k(0, 1, 0, 2) * ze + k(1, 1, 0, 2) * zE1};
+        const double S[3] = {k(0, 0, 1, 0) * x0 + k(1, 0, 1, 0) * xE0 + k(0, 1, 1, 0) * xe + k(1, 1, 1, 0) * xE1 +
+                                 k(1, 1, 1, 3) * yDD,
+                             k(0, 0, 1, 1) * y0 + k(1, 0, 1, 1) * yE0 + k(0, 1, 1, 1) * ye + k(1, 1, 1, 1) * yE1 +
+                                 k(1, 1, 1, 3) * xDD,
+                             k(0, 0, 1, 2) * zz + k(1, 0, 1, 2) * zE0 + k(0, 1, 1, 2) * ze + k(1, 1, 1, 2) * zE1};
+        const double T[3] = {k(1, 0, 1, 4) * zD0 + k(1, 1, 1, 4) * zD1, k(0, 1, 1, 5) * zd + k(1, 1, 1, 5) * zDE,
+                             k(1, 0, 1, 4) * xD0 + k(1, 1, 1, 4) * xD1 + k(0, 1, 1, 5) * yd + k(1, 1, 1, 5) * yDE};
+#pragma unroll
+        for (int c = 0; c < 3; c++) P[c] += S[c] + T[c];
+        if (i >= 2) {
+            const double(&l)[7] = O[(i + 1) & 1];   // loaded with the plane before
+            const double chi = l[0];
+            if (mine && z - 1 < a.pz - 1 && chi != 0.0) {
+                const long j = base + (long)(z - 1) * plane + q;
+                const double c0 = 0.5 * (1.0 - chi) + a.d0, f = ca / (c0 - chi * a.k0c);
+                double rr = 0.0, bb = 0.0;
+#pragma unroll
+                for (int c = 0; c < 3; c++) {
+                    const double rho = l[1 + c] - c0 * wc[c] + chi * P[c];
+                    double wn = wc[c] + f * rho;
+                    if (!a.first) wn += cb * (wc[c] - l[4 + c]);
+                    a.v[j + c * a.Mp] = wn;
+                    rr += rho * rho;
+                    bb += l[1 + c] * l[1 + c];
+                }
+                if (NORM) {   // |b / s|^2 and |r|^2 of the symmetrised system
+                    nrm[0] += rr / chi;
+                    nrm[1] += bb / chi;
+                }
             }
         }
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            P[c] = Q[c] + C[c];
+            Q[c] = S[c] - T[c];
+        }
+        wc[0] = x0;
+        wc[1] = y0;
+        wc[2] = zz;
     }
-    if (a.want_norm) block_partials<1>(v, g.part + (size_t)r * 3 * gridDim.x, gridDim.x, cb.bx);
+    if (NORM) block_partials<2>(nrm, a.part + (size_t)r * a.part_cap, tl.qg * tl.nz, bx);
 }
 
-// One block per right-hand side adds the partials in block order.  NV = 2 after the init pass
-// (|r_0|^2, |b|^2), NV = 1 after a pass with want_norm (|r|^2): the status records the test.
-template <int NV>
-__global__ void __launch_bounds__(1024) k_cheb_reduce(ChebArg a)
+// One block per right-hand side adds the partials of |r_k|^2 and |b|^2 in block order and takes the test.
+__global__ void __launch_bounds__(1024) k_z0_test(PassArg a, int nb)
 {
     __shared__ double sm[16];
-    const CgArg &g = a.cg;
-    const int r = blockIdx.x + a.rhs0, nb = g.nblk;
-    const double *pr = g.part + (size_t)r * 3 * nb;
-    double acc[NV];
-#pragma unroll
-    for (int q = 0; q < NV; q++) acc[q] = 0.0;
-    for (int b = threadIdx.x; b < nb; b += 1024)
-#pragma unroll
-        for (int q = 0; q < NV; q++) acc[q] += pr[(size_t)q * nb + b];
-#pragma unroll
-    for (int q = 0; q < NV; q++) acc[q] = block_sum(acc[q], sm);
-    if (threadIdx.x != 0) return;
-    CgScalars *sc = g.scal + r;
-    if constexpr (NV == 2) {
-        sc->rr = acc[0];
-        sc->bb = acc[1];
-        sc->rz[0] = acc[0];   // |r_0|^2, kept for the status of the check
-    } else {
-        sc->rr = acc[0];
+    const int r = blockIdx.x + a.rhs0;
+    const double *pr = a.part + (size_t)r * a.part_cap;
+    double acc[2] = {0.0, 0.0};
+    for (int b = threadIdx.x; b < nb; b += 1024) {
+        acc[0] += pr[b];
+        acc[1] += pr[nb + b];
     }
-    const double rr = sc->rr, bb = sc->bb;
-    const bool pass = rr <= g.tol2 * bb || bb == 0.0;
-    g.stat[r] = CgStatus{pass ? 1 : 0, a.passes, bb > 0.0 ? sqrt(rr / bb) : 0.0, bb, sc->rz[0]};
+    acc[0] = block_sum(acc[0], sm);
+    acc[1] = block_sum(acc[1], sm);
+    if (threadIdx.x != 0) return;
+    const double rr = acc[0], bb = acc[1];
+    const bool pass = rr <= a.tol2 * bb || bb == 0.0;
+    a.stat[r] = CgStatus{pass ? 1 : 0, pass ? 1 : 0, a.k, bb > 0.0 ? sqrt(rr / bb) : 0.0, bb};
 }
 
-// A deterministic pseudo-random right-hand side (values in [-1, 1), zero where s = 0) and a
-// zero initial guess, for the spectral estimate of M^-1 A.
-__global__ void k_fill_trial(const double *__restrict__ schi, long M, int nrhs, double *__restrict__ rhs,
-                             double *__restrict__ y)
+// Planes per thread.  More planes spend less on the two they share with their neighbours, fewer leave more
+// waves; measured per pass with 1, 2 and 4: 32^3 3.9, 4.4, 5.6 us; 48^3 5.1, 4.8, 5.9; 64^3 8.8, 8.6, 8.7;
+// eight right-hand sides at 64^3 46, 42, 31; 104^3 26, 25, 19.  So 4 from one block a compute unit, 2 from
+// three blocks on four of them (48^3 has 240 such blocks), else 1.
+static int pass_depth(int px, int py, int pz, int nr)
 {
-    const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    const bool in = schi[i] != 0.0;
-    for (int r = 0; r < nrhs; r++)
-        for (int c = 0; c < 3; c++) {
-            const long o = ((long)r * 3 + c) * M + i;
-            unsigned long long x = (unsigned long long)o * 0x9E3779B97F4A7C15ull + 0x632BE59BD9B4E019ull;
-            x ^= x >> 31;
-            x *= 0xBF58476D1CE4E5B9ull;
-            x ^= x >> 29;
-            rhs[o] = in ? (double)(x >> 11) * (2.0 / 9007199254740992.0) - 1.0 : 0.0;
-            y[o] = 0.0;
-        }
+    auto blocks = [&](int zt) {
+        const PassTiles t(px, py, pz, zt);
+        return (long)t.qg * t.nz * nr;
+    };
+    return blocks(4) >= 256 ? 4 : blocks(2) >= 192 ? 2 : 1;
 }
 
-void launch_fill_trial(const double *schi, long M, int nrhs, double *rhs, double *y, hipStream_t st)
+int z0_pass_blocks(int U, int V, int W, int nr)
 {
-    hipLaunchKernelGGL(k_fill_trial, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, schi, M, nrhs, rhs, y);
-    MJ_CHECK(hipGetLastError());
+    const PassTiles t(U + 2, V + 2, W + 2, pass_depth(U + 2, V + 2, W + 2, nr));
+    return t.qg * t.nz;
 }
 
-void launch_cheb_init(const ChebArg &a, hipStream_t st)
+void launch_z0_pass(const PassArg &a, hipStream_t st)
 {
-    const int nr = a.nr > 0 ? a.nr : a.cg.nrhs;
-    if (a.rhs0 < 0 || a.rhs0 + nr > a.cg.nrhs) throw ArgError("Chebyshev launch: right-hand sides out of range");
-    if ((long)a.cg.nblk * nr >= kChebOccBlocks)
-        hipLaunchKernelGGL(k_cheb_init<true>, dim3(a.cg.nblk, nr), dim3(256), 0, st, a);
-    else
-        hipLaunchKernelGGL(k_cheb_init<false>, dim3(a.cg.nblk, nr), dim3(256), 0, st, a);
-    MJ_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(k_cheb_reduce<2>, dim3(nr), dim3(1024), 0, st, a);
-    MJ_CHECK(hipGetLastError());
-}
-void launch_cheb_pass(const ChebArg &a, hipStream_t st)
-{
-    const int nr = a.nr > 0 ? a.nr : a.cg.nrhs;
-    if (a.rhs0 < 0 || a.rhs0 + nr > a.cg.nrhs) throw ArgError("Chebyshev launch: right-hand sides out of range");
-    if ((long)a.cg.nblk * nr >= kChebOccBlocks)
-        hipLaunchKernelGGL(k_cheb_pass<true>, dim3(a.cg.nblk, nr), dim3(256), 0, st, a);
-    else
-        hipLaunchKernelGGL(k_cheb_pass<false>, dim3(a.cg.nblk, nr), dim3(256), 0, st, a);
+    const int zt = pass_depth(a.px, a.py, a.pz, a.nr);
+    const PassTiles t(a.px, a.py, a.pz, zt);
+    const long per_rhs = (long)t.qg * t.nz;
+    if (a.nr < 1 || a.k < 0 || a.k >= a.coef_len || (a.want_norm && 2 * per_rhs > a.part_cap))
+        throw std::logic_error("Z_0 pass outside its buffers");
+    const dim3 grid((unsigned)(per_rhs * a.nr)), blk(256);
+    auto go = [&]<int ZT>(std::integral_constant<int, ZT>) {
+        if (a.want_norm) hipLaunchKernelGGL((k_z0_pass<ZT, true>), grid, blk, 0, st, a);
+        else hipLaunchKernelGGL((k_z0_pass<ZT, false>), grid, blk, 0, st, a);
+    };
+    if (zt == 4) go(std::integral_constant<int, 4>{});
+    else if (zt == 2) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 1>{});
     MJ_CHECK(hipGetLastError());
     if (a.want_norm) {
-        hipLaunchKernelGGL(k_cheb_reduce<1>, dim3(nr), dim3(1024), 0, st, a);
+        hipLaunchKernelGGL(k_z0_test, dim3(a.nr), dim3(1024), 0, st, a, (int)per_rhs);
         MJ_CHECK(hipGetLastError());
     }
+}
+
+// A deterministic pseudo-random right-hand side for the spectral estimate of M^-1 A: b = s x in the haloed
+// layout, x in [-1, 1) (zero where s = 0).
+__global__ void k_fill_trial(const double *__restrict__ schi, int U, int V, int W, double *__restrict__ b)
+{
+    const long M = (long)U * V * W, i = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    if (i >= M) return;
+    const double s = schi[i];
+    const long Mp = (long)(U + 2) * (V + 2) * (W + 2);
+    const int u = (int)(i % U), v = (int)((i / U) % V), z = (int)(i / ((long)U * V));
+    const long ip = ((long)(z + 1) * (V + 2) + (v + 1)) * (U + 2) + (u + 1);
+    for (int c = 0; c < 3; c++) {
+        unsigned long long x = (unsigned long long)(c * M + i) * 0x9E3779B97F4A7C15ull + 0x632BE59BD9B4E019ull;
+        x ^= x >> 31;
+        x *= 0xBF58476D1CE4E5B9ull;
+        x ^= x >> 29;
+        b[c * Mp + ip] = s * ((double)(x >> 11) * (2.0 / 9007199254740992.0) - 1.0);
+    }
+}
+
+void launch_fill_trial(const double *schi, int U, int V, int W, double *b, hipStream_t st)
+{
+    const long M = (long)U * V * W;
+    hipLaunchKernelGGL(k_fill_trial, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, schi, U, V, W, b);
+    MJ_CHECK(hipGetLastError());
 }
 
 // ---------------------------------------------------------------------------- probes
@@ -1444,7 +1520,8 @@ __global__ void k_probe_table_by_voxel(const double *__restrict__ table, const i
 }
 
 // b'_j = g_j - sum_{k=1}^{nloc} c_k lambda_{j+k} + sum_{k>=1} K_k (*) nu_{j+k}; the solve takes
-// A mu = sqrt(chi) b' (Z_0^T = D^-1 A D), started from the extrapolation (weights gx) of mu = nu / sqrt(chi).
+// A mu = sqrt(chi) b' (Z_0^T = D^-1 A D) in the form Z_0 nu = chi b', nu = sqrt(chi) mu, started from the
+// extrapolation (weights gx) of nu.
 // The ring slots count the reversed step n' = N + 1 - j, so "n' - k" is step j + k.
 __global__ void __launch_bounds__(256) k_adj_epilogue(EpiArg e)
 {
@@ -1452,7 +1529,7 @@ __global__ void __launch_bounds__(256) k_adj_epilogue(EpiArg e)
     const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
     const int r = blockIdx.y;
     if (i >= M) return;
-    const double sc = e.schi[i];
+    const double chi = e.chi[i];
     const int u = (int)(i % e.U), v = (int)((i / e.U) % e.V), z = (int)(i / ((long)e.U * e.V));
     const double c1 = 0.5 * e.inv_eps[i] + (e.nfir > 1 ? e.fir[1] : 0.0);
     const long Mp = (long)(e.U + 2) * (e.V + 2) * (e.W + 2);
@@ -1467,20 +1544,16 @@ __global__ void __launch_bounds__(256) k_adj_epilogue(EpiArg e)
             b -= ck * e.Lring[(((long)e.slot_of[k] * e.nrhs + r) * 3 + c) * M + i];
         }
         e.bq[o] = b;
-        double y0 = 0.0;
-        if (sc > 0.0) {
-            double g = 0.0;
-            for (int k = 1; k <= e.nguess; k++)
-                if (e.n - k >= 1) g += e.gx[k - 1] * e.Jring[(((long)e.slot_of[k] * e.nrhs + r) * 3 + c) * M + i];
-            y0 = g / sc;
-        }
-        e.rhs[o] = sc * b;
-        e.y[o] = y0;
-        e.uy[((long)r * 3 + c) * Mp + ip] = sc * y0;
+        if (chi == 0.0) continue;   // nu = 0 there, and so are the solve's entries
+        double g = 0.0;
+        for (int k = 1; k <= e.nguess; k++)
+            if (e.n - k >= 1) g += e.gx[k - 1] * e.Jring[(((long)e.slot_of[k] * e.nrhs + r) * 3 + c) * M + i];
+        e.b[((long)r * 3 + c) * Mp + ip] = chi * b;
+        e.w0[((long)r * 3 + c) * Mp + ip] = g;
     }
 }
 
-// lambda_j = mu / sqrt(chi) where chi > 0; where chi = 0 the row of Z_0^T reads
+// lambda_j = nu / chi where chi > 0; where chi = 0 the row of Z_0^T reads
 // c_0 lambda - K_0 (*) nu = b', so lambda = (b' + K_0 (*) nu) / c_0 there.
 __global__ void __launch_bounds__(256) k_adj_lambda(AdjArg a)
 {
@@ -1492,7 +1565,7 @@ __global__ void __launch_bounds__(256) k_adj_lambda(AdjArg a)
     if (sc > 0.0) {
         for (int c = 0; c < 3; c++) {
             const long o = ((long)r * 3 + c) * M + i;
-            a.lam[o] = a.y[o] / sc;
+            a.lam[o] = a.nu[o] / (sc * sc);
         }
         return;
     }

@@ -1,0 +1,98 @@
+"""The Z_0 solve by replayed passes against CG (which the oracle tests pin)."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _problem(U, V, W, nr, n, seed=5):
+    eps = wl.random_eps(U, V, W, seed, 1.5, 12.0)
+    if V > 2:
+        eps[:, V // 2, :] = 1.0
+    waves = [wl.gaussian_wave(U, V, W, k, p, 3.0, 3.0) for k, p in wl.random_directions(nr, seed)]
+    return wl.Problem("z0", U, V, W, eps, waves, n, fir=wl.binomial_highpass(17, 0.01))
+
+
+def _march(torch, prob, n, z0, switch=None, graphs=0):
+    from paper_2407_03323_amd import motjvie
+    s = motjvie.solver_for(prob, z0_solver=z0, z0_graphs=graphs)
+    nr = len(prob.waves)
+    J = torch.zeros((n // 5, nr, 3, prob.W, prob.V, prob.U), dtype=torch.float64, device="cuda")
+    if switch is None:
+        s.run(n, J, j_every=5)
+    else:
+        m = n // 10 * 5
+        s.run(m, J[: m // 5], j_every=5)
+        s.set_plane_waves(switch)
+        s.run(n - m, J[m // 5:], j_every=5)
+    st = s.stats()
+    s.close()
+    assert st["cg_res_max"] <= 1e-13
+    return J
+
+
+# one voxel thick, rows at and beyond the 62 outputs of a wave, and the depths of 1, 2 and 4 planes a
+# thread with planes left over; 12 right-hand sides of the last are two groups
+@pytest.mark.parametrize("U,V,W,nr", [(1, 1, 1, 1), (9, 1, 1, 2), (60, 5, 1, 1), (62, 3, 4, 2), (63, 4, 3, 1),
+                                      (31, 29, 33, 1), (49, 48, 47, 1), (66, 65, 63, 1), (61, 57, 63, 12)])
+def test_replayed_passes_match_cg(torch_cuda, U, V, W, nr):
+    """70 steps with replays (and the CG solves that record them) agree with CG in every step to
+    the solve tolerance."""
+    prob = _problem(U, V, W, nr, 70)
+    print("replay %dx%dx%d, %d waves" % (U, V, W, nr), flush=True)
+    a, b = _march(torch_cuda, prob, 70, 0), _march(torch_cuda, prob, 70, 1)
+    assert float(b.norm()) > 0.0
+    for r in range(nr):
+        assert float((a[:, r] - b[:, r]).norm()) <= 1e-11 * float(b[:, r].norm())
+
+
+@pytest.mark.parametrize("z0", [0, 2])
+def test_solve_survives_a_change_of_waves(torch_cuda, z0):
+    """Other directions and polarisations from step 35 on: the record of the first waves no longer fits, and
+    the solves still meet their tolerance (as does the Chebyshev iteration's prediction)."""
+    prob = _problem(20, 21, 19, 2, 70)
+    other = [wl.gaussian_wave(20, 21, 19, k, p, 1.5, 27.0) for k, p in wl.random_directions(2, 99)]
+    a, b = _march(torch_cuda, prob, 70, z0, other), _march(torch_cuda, prob, 70, 1, other)
+    assert float((a - b).norm()) <= 1e-11 * float(b.norm())
+
+
+def test_replays_from_graphs_match_launches(torch_cuda):
+    prob = _problem(20, 21, 19, 2, 70)
+    assert torch_cuda.equal(_march(torch_cuda, prob, 70, 0), _march(torch_cuda, prob, 70, 0, graphs=1))
+
+
+def test_state_without_solve_record_is_read(torch_cuda):
+    """A state written before the solve's record was part of it (version 2) resumes, to the tolerance."""
+    import struct
+    from paper_2407_03323_amd import motjvie
+    torch = torch_cuda
+    prob = _problem(7, 6, 5, 1, 40)
+    out = []
+    for old in (False, True):
+        s = motjvie.solver_for(prob)
+        s.run(21)
+        st = s.get_state()
+        s.close()
+        if old:
+            head = 8 + 14 * 4 + 5 * 8
+            far = struct.unpack_from("<5q", st.tobytes(), 8 + 14 * 4)
+            rest = sum(far[1:])
+            st = np.concatenate([st[:head], st[len(st) - rest:]])
+            st[8:12] = np.frombuffer(struct.pack("<i", 2), dtype=np.uint8)
+        s = motjvie.solver_for(prob)
+        s.set_state(st)
+        J = torch.zeros((19, 1, 3, 5, 6, 7), dtype=torch.float64, device="cuda")
+        s.run(19, J)
+        s.close()
+        out.append(J)
+    assert float((out[0] - out[1]).norm()) <= 1e-11 * float(out[0].norm())
