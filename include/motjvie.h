@@ -75,7 +75,9 @@ typedef struct {
                                  (4 in 8), (4 in 12), (4 in 16), (8 in 16); the choices group the terms
                                  of eq:PnMOT differently, so results then vary with it at rounding level */
     void *stream;             /* hipStream_t to enqueue on; NULL = the null stream */
-    int32_t quad_order;       /* Gauss-Legendre points per cell of the kernel quadrature; 0 selects 16 */
+    int32_t quad_order;       /* Gauss-Legendre points per cell of the kernel quadrature (4 .. 24); 0 selects 16
+                                 for voxels within 3.5 edges of each other and, falling to 9 x 8
+                                 beyond 24, what keeps the cells' error below rounding */
     int32_t fft_pencils;      /* pencils per block of the FFT passes: 0 = pick per pass by timing at
                                  mj_create; > 0 = at most this many (capped by what one LDS tile holds).
                                  The transforms are bit-identical for every choice. < 0: MJ_EINVAL */

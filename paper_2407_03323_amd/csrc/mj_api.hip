@@ -165,7 +165,7 @@ struct mj_solver {
     int cg_maxit = 200;
     int B = 1;                      // steps per (inner) time block
     int B2 = 0;                     // steps per outer time block (three levels), 0: two levels
-    int nquad = 16;
+    int nquad = 0;                  // quadrature points per cell of the kernels (0: by distance)
     hipStream_t st = nullptr;
     int nloc = 5, rdepth = 6;
     // degree of the extrapolated initial guess of the Z_0 solve (at most; the steps it goes through
@@ -428,7 +428,7 @@ void mj_solver::create(const mj_config &c)
     nrhs = c.n_rhs;
     cg_rtol = c.cg_rtol > 0 ? c.cg_rtol : 1e-13;
     cg_maxit = c.cg_maxit > 0 ? c.cg_maxit : 200;
-    nquad = c.quad_order > 0 ? c.quad_order : 16;
+    nquad = c.quad_order > 0 ? c.quad_order : 0;
     st = (hipStream_t)c.stream;
     fir.assign(c.fir, c.fir + c.n_fir);
     for (double d : fir)
@@ -1641,7 +1641,7 @@ void mj_solver::set_probes(int n_probes, const double *pos)
         MJ_CHECK(hipEventCreate(&e0));
         MJ_CHECK(hipEventCreate(&e1));
         MJ_CHECK(hipEventRecord(e0, st));
-        mj::gen_offgrid_table(probe_pos, pair_probe, pair_vox, pair_kmin, npairs, U, V, gen.r, gen.hv, nw, ell, nquad, ptable, st);
+        mj::gen_offgrid_table(probe_pos, pair_probe, pair_vox, pair_kmin, npairs, U, V, gen.r, gen.hv, nw, ell, nquad, ptable, da, st);
         MJ_CHECK(hipEventRecord(e1, st));
         MJ_CHECK(hipEventSynchronize(e1));
         float ms = 0;
@@ -1689,7 +1689,7 @@ void mj_solver::offgrid_values(int cnt, const int *probe, const int *vox3, const
         MJ_CHECK(hipMemcpy(d_p, pp.data(), sizeof(int) * cnt, hipMemcpyHostToDevice));
         MJ_CHECK(hipMemcpy(d_v, pv.data(), sizeof(int) * cnt, hipMemcpyHostToDevice));
         MJ_CHECK(hipMemcpy(d_k, pk.data(), sizeof(int) * cnt, hipMemcpyHostToDevice));
-        mj::gen_offgrid_table(probe_pos, d_p, d_v, d_k, cnt, U, V, gen.r, gen.hv, 1, 0x7fffffff, nquad, d_o, st);
+        mj::gen_offgrid_table(probe_pos, d_p, d_v, d_k, cnt, U, V, gen.r, gen.hv, 1, 0x7fffffff, nquad, d_o, da, st);
         MJ_CHECK(hipStreamSynchronize(st));
         MJ_CHECK(hipMemcpy(out, d_o, sizeof(double) * 6 * cnt, hipMemcpyDeviceToHost));
     } catch (...) {

@@ -32,7 +32,19 @@
 // parametrised by (s along the edge, tau along the ray), split where the shell's two
 // spheres cut the plane and graded towards the foot where the integrand does not vanish
 // there; nq x nq Gauss-Legendre on every cell.  Only the octant D >= 0 is computed; the
-// other octants follow from the parity of each component.
+// other octants follow from the parity of each component, and along axes of equal voxel edges only one
+// order of |D_x|, |D_y|, |D_z| is, the others being its permutations (a cubic grid computes one
+// offset in six).
+//
+// A foot that lies outside the square by two of its edges or more starts the rays at its distance from
+// the square instead of 0: what lies inside cancels between the four triangles.  That leaves only short
+// cells away from the foot, where few points do (see order_class).
+//
+// One wave takes one offset.  What it is bound by is FP64 work, 250 operations a node, so the edges of
+// the squares are cut and sorted out first, a lane each, and the intervals that contribute go into a
+// list in LDS whose s-nodes the lanes then share evenly: on average over the offsets of a grid a fifth of
+// the (edge, interval) pairs contribute, and lanes bound to pairs idled for the rest.  48^3 with
+// the three (symmetry, orders, list): MEASURED_GEN against 428 ms.
 
 #include "mj_internal.h"
 
@@ -46,15 +58,49 @@ constexpr int kGenThreads = 64;
 constexpr int kMaxQ = 24;
 constexpr double kInvFourPi = 0.07957747154594766788;
 
+// Points per cell (along an edge, along a ray) by the gap between the two voxels in units of the longest
+// edge.  With quad_order 0 the orders fall where the integrands get smoother.  They were chosen
+// on the CPU in extended precision against 20 x 20 points, over every sorted offset up to 12, 1500
+// log-uniform real offsets out to 80 and 400 with edges 1 x 0.7 x 1.3: in the distance classes the cells'
+// error stays below 1e-14 of the largest |K_k| of its offset, where rounding alone leaves 1e-14 to
+// 1e-13 with 16 points and, having fewer nodes to add, not more with these.
+constexpr int kOrderClasses = 5;
+constexpr double kClassGap[kOrderClasses] = {0.0, 3.5, 6.0, 12.0, 24.0};
+constexpr int kClassS[kOrderClasses] = {16, 14, 12, 11, 10}, kClassT[kOrderClasses] = {16, 12, 11, 9, 8};
+
+// The Gauss-Legendre rules in use: those of the classes, or the caller's order in every class.
+struct GenRules {
+    int ns[kOrderClasses], nt[kOrderClasses];      // points
+    int rs[kOrderClasses], rt[kOrderClasses];      // rows of x, w
+    double x[2 * kOrderClasses][kMaxQ], w[2 * kOrderClasses][kMaxQ];   // on [-1, 1]
+    double g3x[3], g3w[3];                         // 3-point rule on [-1, 1]
+};
+
 struct GenArg {
     int Uo, Vo, Wo;
     int nq;
     int ms;                          // shells stored per offset
     double r;                        // c dt
     double hv[3], ih[3];             // voxel edges and their inverses
-    double glx[kMaxQ], glw[kMaxQ];   // nq-point rule on [-1, 1]
+    double glx[kMaxQ], glw[kMaxQ];   // nq-point rule on [-1, 1] (host checks)
     double g3x[3], g3w[3];           // 3-point rule on [-1, 1]
+    const GenRules *rules;           // on the device
 };
+
+// Order class of the offset |D| (voxel steps, real): see above.
+__host__ __device__ inline int order_class(double dx, double dy, double dz, const double hv[3])
+{
+    const double d[3] = {dx, dy, dz};
+    double g2 = 0.0, hm = 0.0;
+    for (int i = 0; i < 3; i++) {
+        const double e = d[i] > 1.0 ? (d[i] - 1.0) * hv[i] : 0.0;
+        g2 += e * e;
+        hm = hv[i] > hm ? hv[i] : hm;
+    }
+    int c = 0;
+    for (int i = 1; i < kOrderClasses; i++) c = g2 >= kClassGap[i] * kClassGap[i] * hm * hm ? i : c;
+    return c;
+}
 
 // Shells a r <= |d| < (a + 1) r, a in [a_lo, a_lo + nsh), that meet the distance range
 // [R_min, R_max] of two voxels: a_lo = floor(R_min / r), a_lo + nsh = ceil(R_max / r).  With
@@ -180,38 +226,54 @@ __host__ __device__ inline void node_contrib(double m[kMoments], const double y[
 constexpr double kSentinel = 1e300;
 constexpr int kMaxGrade = 6;   // graded tau points towards the foot (ratio 3)
 
-// One work item of the face quadrature of shell [Ra, Rb) at octant offset D for a unit square in the
-// plane y_AX = D[AX] + s h_AX: edge e, s-interval iv of that edge, s-node iq; accumulates into m.
-// glx/glw: nq-point rule on [-1,1]; g3x/g3w: 3-point rule.
-template <int AX, int E, bool ANI>
-__host__ __device__ inline void gen_edge(int nq, const double *glx, const double *glw, const double *g3x,
-                                         const double *g3w, const double D[3], double Ra, double Rb, double inv_r,
-                                         const double *hv, const double *ih, int s, int s1, int s2, int iv, int iq,
-                                         double m[kMoments])
+// The edge E of a face or plane square (plane y_AX = c = D[AX] + s h_AX, sub-square signs s1, s2) seen from
+// the foot of the perpendicular from the origin:
+// E = 0: y_A2 = lo2 (s along A1); 1: y_A1 = hi1 (s along A2); 2: y_A2 = hi2; 3: y_A1 = lo1.
+struct FaceEdge {
+    double c;        // distance of the plane
+    double p;        // signed distance of the edge's line from the foot
+    double fixed;    // its in-plane coordinate
+    double rho0;     // rays start here: inside the inner sphere nothing contributes, and what lies
+                     // nearer to the foot than the square cancels between its edges
+    double rhoB;     // in-plane radius of the outer sphere (0: it does not reach the plane)
+    double grade;    // |c| if the rays are graded towards the foot, else 0
+};
+
+// Cuts edge E for the shell [Ra, Rb): its geometry, and in sp the six ascending split points of the edge
+// coordinate (kSentinel where there are fewer).  False if nothing on it contributes.
+template <int AX, bool ANI>
+__host__ __device__ inline bool face_edge(int E, const double D[3], double Ra, double Rb, const double *hv, int s, int s1,
+                                          int s2, FaceEdge &g, double sp[6])
 {
     constexpr int A1 = (AX + 1) % 3, A2 = (AX + 2) % 3;
     const double e0_ = ANI ? hv[AX] : 1.0, e1_ = ANI ? hv[A1] : 1.0, e2_ = ANI ? hv[A2] : 1.0;
     const double c = D[AX] + s * e0_;
     const double lo1 = s1 > 0 ? D[A1] : D[A1] - e1_, lo2 = s2 > 0 ? D[A2] : D[A2] - e2_;
     const double hi1 = lo1 + e1_, hi2 = lo2 + e2_;
-    // edge e: signed distance p of its line from the foot; range [e0, e1] of the edge coordinate
-    // E = 0: y_A2 = lo2 (s along A1); 1: y_A1 = hi1 (s along A2); 2: y_A2 = hi2; 3: y_A1 = lo1
-    constexpr bool fixed_is_1 = (E == 1 || E == 3);
-    const double p = E == 0 ? -lo2 : (E == 1 ? hi1 : (E == 2 ? hi2 : -lo1));
-    const double e0 = fixed_is_1 ? lo2 : lo1, e1 = fixed_is_1 ? hi2 : hi1;
-    const double fixed = E == 0 ? lo2 : (E == 1 ? hi1 : (E == 2 ? hi2 : lo1));
-    if (p == 0.0) return;
-    const double ap = fabs(p);
-    const double c2 = c * c;
+    // range [e0, e1] of the edge coordinate
+    const bool along2 = E & 1, upper = E == 1 || E == 2;
+    const double fixed = along2 ? (upper ? hi1 : lo1) : (upper ? hi2 : lo2);
+    const double p = upper ? fixed : -fixed;
+    const double e0 = along2 ? lo2 : lo1, e1 = along2 ? hi2 : hi1;
+    if (p == 0.0) return false;
+    const double ap = fabs(p), c2 = c * c;
     // nothing contributes where |y| <= a: skip edges whose farthest point is inside the shell
     const double Lmax2 = p * p + fmax(e0 * e0, e1 * e1);
-    if (c2 + Lmax2 <= Ra * Ra) return;
+    if (c2 + Lmax2 <= Ra * Ra) return false;
     // in-plane radii of the two spheres (0 when the sphere does not reach the plane)
     const bool haveA = Ra > fabs(c), haveB = Rb > fabs(c);
     const double rhoA = haveA ? sqrt(Ra * Ra - c2) : 0.0;
     const double rhoB = haveB ? sqrt(Rb * Rb - c2) : 0.0;
+    // distance of the square from the foot, used from twice its longer edge on (nearer, the start radius
+    // over the ray's length would bend more over the edge than the rays from 0 do)
+    const double n1 = fmax(0.0, fmax(lo1, -hi1)), n2 = fmax(0.0, fmax(lo2, -hi2)), rn = sqrt(n1 * n1 + n2 * n2);
+    g.c = c;
+    g.p = p;
+    g.fixed = fixed;
+    g.rho0 = fmax(rhoA, rn >= 2.0 * fmax(e1_, e2_) ? rn : 0.0);
+    g.rhoB = rhoB;
+    g.grade = haveA ? 0.0 : fabs(c);
     // split points of the edge coordinate where the spheres cross the edge
-    double sp[6];
     sp[0] = e0;
     sp[1] = sp[2] = sp[3] = sp[4] = kSentinel;
     sp[5] = e1;
@@ -226,81 +288,82 @@ __host__ __device__ inline void gen_edge(int nq, const double *glx, const double
         if (-t > e0 && -t < e1) sp[4] = -t;
     }
     sort_fixed<6>(sp);
-    double sa = 0.0, sb = 0.0;
-#pragma unroll
-    for (int j = 0; j < 5; j++)
-        if (j == iv) {
-            sa = sp[j];
-            sb = sp[j + 1];
-        }
-    if (!(sb > sa) || sb >= kSentinel) return;
+    return true;
+}
+
+// Whether the interval [sa, sb] of the edge holds anything: rays to its middle reach rho0 (the splits put
+// either all of an interval or nothing of it outside the inner sphere, and no point of an edge is nearer to
+// the foot than the square; where the middle is the nearest point, both sides are the same number).
+__host__ __device__ inline bool edge_interval(const FaceEdge &g, double sa, double sb)
+{
+    if (!(sb > sa) || sb >= kSentinel) return false;
+    const double sm = 0.5 * (sa + sb);
+    return g.p * g.p + sm * sm >= g.rho0 * g.rho0;
+}
+
+// One s-node (gx, gw on [-1, 1]) of the interval [sa, sb] of an edge: the ray to it, cut at the outer sphere
+// and graded (ratio 3) towards the foot where the integrand does not vanish there, nt points a cell.
+template <int AX, bool ANI>
+__host__ __device__ inline void edge_node(const FaceEdge &g, bool along2, double sa, double sb, double gx, double gw,
+                                          int nt, const double *tx, const double *tw, const double *g3x,
+                                          const double *g3w, const double D[3], double Ra, double Rb, double inv_r,
+                                          const double *ih, int s, int s1, int s2, double m[kMoments])
+{
+    constexpr int A1 = (AX + 1) % 3, A2 = (AX + 2) % 3;
     const double shm = 0.5 * (sb - sa), shc = 0.5 * (sb + sa);
-    const double sn = shc + shm * glx[iq];
-    const double L = sqrt(p * p + sn * sn);
-    const double ey1 = fixed_is_1 ? fixed : sn;
-    const double ey2 = fixed_is_1 ? sn : fixed;
-    // tau cells: from the inner sphere (nothing inside it), split at the outer one, graded
-    // towards the foot when the integrand does not vanish there
-    const double tstart = haveA ? rhoA / L : 0.0;
-    if (tstart >= 1.0) return;
-    constexpr int NT = 4 + kMaxGrade;
-    double tp[NT];
-#pragma unroll
-    for (int j = 0; j < NT; j++) tp[j] = kSentinel;
-    tp[0] = tstart;
-    tp[1] = 1.0;
-    if (haveB) {
-        const double t = rhoB / L;
-        if (t > tstart && t < 1.0) tp[2] = t;
-    }
-    if (!haveA && c != 0.0) {
-        double t = fabs(c) / L;
-#pragma unroll
-        for (int g = 0; g < kMaxGrade; g++) {
-            if (t > tstart && t < 1.0) tp[3 + g] = t;
-            t *= 3.0;
+    const double sn = shc + shm * gx;
+    const double L = sqrt(g.p * g.p + sn * sn);
+    const double ey1 = along2 ? g.fixed : sn, ey2 = along2 ? sn : g.fixed;
+    const double wsn = gw * shm * g.p;
+    const double c2 = g.c * g.c, tB = g.rhoB > 0.0 ? g.rhoB / L : 2.0;
+    double ta = g.rho0 / L, tg = g.grade > 0.0 ? g.grade / L : 2.0;
+    int left = kMaxGrade;
+    while (ta < 1.0) {
+        while (tg <= ta && left > 0) {
+            tg *= 3.0;
+            left--;
         }
-    }
-    sort_fixed<NT>(tp);
-    const double wsn = glw[iq] * shm * ap * (p > 0 ? 1.0 : -1.0);
-#pragma unroll
-    for (int jt = 0; jt < NT - 1; jt++) {
-        const double ta = tp[jt], tb = tp[jt + 1];
-        if (!(tb > ta) || tb > 1.0) continue;
+        double tb = 1.0;
+        if (left > 0 && tg < tb) tb = tg;
+        if (tB > ta && tB < tb) tb = tB;
         const double thm = 0.5 * (tb - ta), thc = 0.5 * (tb + ta);
-        for (int q = 0; q < nq; q++) {
-            const double tau = thc + thm * glx[q];
+        for (int q = 0; q < nt; q++) {
+            const double tau = thc + thm * tx[q];
             double y[3];
-            y[AX] = c;
+            y[AX] = g.c;
             y[A1] = tau * ey1;
             y[A2] = tau * ey2;
             const double ny = sqrt(c2 + tau * tau * L * L);
-            const double wgt = wsn * thm * glw[q] * tau;
+            const double wgt = wsn * thm * tw[q] * tau;
             node_contrib<AX, ANI>(m, y, ny, wgt, s, s1, s2, D, Ra, Rb, inv_r, ih, g3x, g3w);
         }
+        ta = tb;
     }
 }
 
+// s-interval iv, s-node iq of the four edges of a square, serially (host checks)
 template <int AX, bool ANI>
 __host__ __device__ inline void gen_square(int nq, const double *glx, const double *glw, const double *g3x,
                                            const double *g3w, const double D[3], double Ra, double Rb, double inv_r,
                                            const double *hv, const double *ih, int s, int s1, int s2, int iv, int iq,
                                            double m[kMoments])
 {
-    gen_edge<AX, 0, ANI>(nq, glx, glw, g3x, g3w, D, Ra, Rb, inv_r, hv, ih, s, s1, s2, iv, iq, m);
-    gen_edge<AX, 1, ANI>(nq, glx, glw, g3x, g3w, D, Ra, Rb, inv_r, hv, ih, s, s1, s2, iv, iq, m);
-    gen_edge<AX, 2, ANI>(nq, glx, glw, g3x, g3w, D, Ra, Rb, inv_r, hv, ih, s, s1, s2, iv, iq, m);
-    gen_edge<AX, 3, ANI>(nq, glx, glw, g3x, g3w, D, Ra, Rb, inv_r, hv, ih, s, s1, s2, iv, iq, m);
+    for (int E = 0; E < 4; E++) {
+        FaceEdge g;
+        double sp[6];
+        if (!face_edge<AX, ANI>(E, D, Ra, Rb, hv, s, s1, s2, g, sp) || !edge_interval(g, sp[iv], sp[iv + 1])) continue;
+        edge_node<AX, ANI>(g, E & 1, sp[iv], sp[iv + 1], glx[iq], glw[iq], nq, glx, glw, g3x, g3w, D, Ra, Rb, inv_r, ih,
+                           s, s1, s2, m);
+    }
 }
 
 // Number of work items per (offset, shell): 36 unit squares x 5 s-intervals x nq s-nodes.
 __host__ __device__ inline int gen_items(int nq) { return 36 * 5 * nq; }
 
 // Item index -> (unit square, s-interval, s-node); the four edges of the square are
-// handled inside the item.  Dispatch on the plane axis.  Inlined by force: as a called
-// function its moment accumulators lived in scratch memory (192 bytes per lane).
+// handled inside the item.
 template <bool ANI>
-__host__ __device__ __attribute__((always_inline)) inline void gen_item(int nq, const double *glx, const double *glw, const double *g3x,
+__host__ __device__ inline void gen_item(int nq, const double *glx, const double *glw, const double *g3x,
                                          const double *g3w, const double D[3], int a, double r, const double *hv,
                                          const double *ih, int it, double m[kMoments])
 {
@@ -324,42 +387,138 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
+// Scratch of one wave: the rules of its offset, the 48 edges of one plane axis and the list of their
+// contributing intervals (at most 5 an edge).
+struct GenLds {
+    double sx[kMaxQ], sw[kMaxQ], tx[kMaxQ], tw[kMaxQ], g3x[3], g3w[3];
+    FaceEdge edge[48];
+    double ia[240], ib[240];
+    unsigned char ie[240];
+};
+
+__device__ inline void load_rules(GenLds &l, const GenRules &R, int cls)
+{
+    for (int i = threadIdx.x; i < kMaxQ; i += kGenThreads) {
+        l.sx[i] = R.x[R.rs[cls]][i];
+        l.sw[i] = R.w[R.rs[cls]][i];
+        l.tx[i] = R.x[R.rt[cls]][i];
+        l.tw[i] = R.w[R.rt[cls]][i];
+    }
+    if (threadIdx.x < 3) {
+        l.g3x[threadIdx.x] = R.g3x[threadIdx.x];
+        l.g3w[threadIdx.x] = R.g3w[threadIdx.x];
+    }
+    __syncthreads();
+}
+
+// The planes of axis AX, shell [Ra, Rb): each lane's share of the moments (every lane of the wave calls it)
+template <int AX, bool ANI>
+__device__ __attribute__((always_inline)) inline void axis_moments(GenLds &l, int ns, int nt, const double D[3],
+                                                                   double Ra, double Rb, double inv_r,
+                                                                   const double *hv, const double *ih,
+                                                                   double (&m)[kMoments])
+{
+    const int lane = threadIdx.x;
+    // lane e + 4 sq: edge e of square sq = (s1 > 0) + 2 (s2 > 0) + 4 (s + 1)
+    double sp[6];
+    unsigned keep = 0;   // its contributing intervals
+    if (lane < 48) {
+        const int sq = lane >> 2;
+        FaceEdge g;
+        if (face_edge<AX, ANI>(lane & 3, D, Ra, Rb, hv, (sq >> 2) - 1, (sq & 1) ? 1 : -1, (sq & 2) ? 1 : -1, g, sp)) {
+#pragma unroll
+            for (int j = 0; j < 5; j++)
+                if (edge_interval(g, sp[j], sp[j + 1])) keep |= 1u << j;
+            l.edge[lane] = g;
+        }
+    }
+    int at = __popc(keep);
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(at, off);
+        if (lane >= off) at += v;
+    }
+    const int total = __shfl(at, 63);
+    at -= __popc(keep);
+#pragma unroll
+    for (int j = 0; j < 5; j++)
+        if (keep & (1u << j)) {
+            l.ia[at] = sp[j];
+            l.ib[at] = sp[j + 1];
+            l.ie[at] = (unsigned char)lane;
+            at++;
+        }
+    __syncthreads();
+    for (int it = lane; it < total * ns; it += kGenThreads) {
+        const int e = it / ns, iq = it - e * ns;
+        const int id = l.ie[e], sq = id >> 2;
+        const FaceEdge g = l.edge[id];
+        edge_node<AX, ANI>(g, id & 1, l.ia[e], l.ib[e], l.sx[iq], l.sw[iq], nt, l.tx, l.tw, l.g3x, l.g3w, D, Ra, Rb,
+                           inv_r, ih, (sq >> 2) - 1, (sq & 1) ? 1 : -1, (sq & 2) ? 1 : -1, m);
+    }
+    __syncthreads();
+}
+
+// The 19 moments of shell a, in lane 0 (every lane of the wave calls it)
+template <bool ANI>
+__device__ __attribute__((always_inline)) inline void shell_moments(GenLds &l, int ns, int nt, const double D[3], int a,
+                                                                    double r, const double *hv, const double *ih,
+                                                                    double (&m)[kMoments])
+{
+    const double Ra = a * r, Rb = (a + 1) * r, inv_r = 1.0 / r;
+#pragma unroll
+    for (int i = 0; i < kMoments; i++) m[i] = 0.0;
+    axis_moments<0, ANI>(l, ns, nt, D, Ra, Rb, inv_r, hv, ih, m);
+    axis_moments<1, ANI>(l, ns, nt, D, Ra, Rb, inv_r, hv, ih, m);
+    axis_moments<2, ANI>(l, ns, nt, D, Ra, Rb, inv_r, hv, ih, m);
+#pragma unroll
+    for (int i = 0; i < kMoments; i++) m[i] = wave_sum(m[i]);
+}
+
+// Which stored offset stands for |D|: axes of equal voxel edges may trade their components, and the larger
+// component goes to the axis with more voxels (so it stays on the grid), the lower axis among equals.
+// d becomes that offset; pos[a] is the axis where the component of axis a went.
+__host__ __device__ inline void stored_offset(int d[3], int pos[3], const int n[3], const double hv[3])
+{
+    pos[0] = 0;
+    pos[1] = 1;
+    pos[2] = 2;
+    // three passes of conditional exchanges sort three axes; axes of unequal edges never trade
+    for (int pass = 0; pass < 3; pass++)
+        for (int i = 0; i < 2; i++)
+            for (int j = i + 1; j < 3; j++) {
+                if (hv[i] != hv[j]) continue;
+                const bool first = n[i] >= n[j];   // axis i takes the larger component
+                if (first ? d[i] < d[j] : d[i] > d[j]) {
+                    const int t = d[i];
+                    d[i] = d[j];
+                    d[j] = t;
+                    for (int a = 0; a < 3; a++) pos[a] = pos[a] == i ? j : pos[a] == j ? i : pos[a];
+                }
+            }
+}
+
 template <bool ANI>
 __global__ void __launch_bounds__(kGenThreads) k_gen_moments(double *__restrict__ mom, GenArg ga)
 {
+    __shared__ GenLds lds;
     const int idx = blockIdx.x;
-    const int dx = idx % ga.Uo, dy = (idx / ga.Uo) % ga.Vo, dz = idx / (ga.Uo * ga.Vo);
-    const double D[3] = {dx * ga.hv[0], dy * ga.hv[1], dz * ga.hv[2]};
+    const int d0[3] = {idx % ga.Uo, (idx / ga.Uo) % ga.Vo, idx / (ga.Uo * ga.Vo)}, n[3] = {ga.Uo, ga.Vo, ga.Wo};
+    int d[3] = {d0[0], d0[1], d0[2]}, pos[3];
+    stored_offset(d, pos, n, ga.hv);
+    if (d[0] != d0[0] || d[1] != d0[1] || d[2] != d0[2]) return;   // another offset stands for this one
+    const double D[3] = {d[0] * ga.hv[0], d[1] * ga.hv[1], d[2] * ga.hv[2]};
     int a_lo, nsh;
-    shell_range(dx, dy, dz, ga.hv, ga.r, a_lo, nsh);
+    shell_range(d[0], d[1], d[2], ga.hv, ga.r, a_lo, nsh);
+    const int cls = order_class(d[0], d[1], d[2], ga.hv), ns = ga.rules->ns[cls], nt = ga.rules->nt[cls];
+    load_rules(lds, *ga.rules, cls);
     double *out = mom + (size_t)idx * ga.ms * kMoments;
-    const int nq = ga.nq;
-    __shared__ double glx[kMaxQ], glw[kMaxQ], g3x[3], g3w[3];
-    for (int i = threadIdx.x; i < kMaxQ; i += kGenThreads) {
-        glx[i] = ga.glx[i];
-        glw[i] = ga.glw[i];
-    }
-    if (threadIdx.x < 3) {
-        g3x[threadIdx.x] = ga.g3x[threadIdx.x];
-        g3w[threadIdx.x] = ga.g3w[threadIdx.x];
-    }
-    __syncthreads();
-    const int nitems = gen_items(nq);
-    const double r = ga.r;
-    for (int sh = 0; sh < ga.ms; sh++) {
+    for (int sh = 0; sh < min(nsh, ga.ms); sh++) {   // the others stay zero
         double m[kMoments];
+        shell_moments<ANI>(lds, ns, nt, D, a_lo + sh, ga.r, ga.hv, ga.ih, m);
+        if (threadIdx.x == 0)
 #pragma unroll
-        for (int i = 0; i < kMoments; i++) m[i] = 0.0;
-        const int a = a_lo + sh;
-        if (sh < nsh) {
-            for (int it = threadIdx.x; it < nitems; it += kGenThreads)
-                gen_item<ANI>(nq, glx, glw, g3x, g3w, D, a, r, ga.hv, ga.ih, it, m);
-        }
-#pragma unroll
-        for (int i = 0; i < kMoments; i++) {
-            double v = wave_sum(m[i]);
-            if (threadIdx.x == 0) out[sh * kMoments + i] = v;
-        }
+            for (int i = 0; i < kMoments; i++) out[sh * kMoments + i] = m[i];
     }
 }
 
@@ -407,9 +566,18 @@ struct MomView {
 
 __device__ inline void kernel_at(const MomView &g, int k, int Dx, int Dy, int Dz, double K[6])
 {
-    int ax = Dx < 0 ? -Dx : Dx, ay = Dy < 0 ? -Dy : Dy, az = Dz < 0 ? -Dz : Dz;
-    const double *md = g.mom + ((size_t)(az * g.Vo + ay) * g.Uo + ax) * g.ms * kMoments;
-    kernel_from_moments(md, ax, ay, az, k, g.r, g.hv, K);
+    int d[3] = {Dx < 0 ? -Dx : Dx, Dy < 0 ? -Dy : Dy, Dz < 0 ? -Dz : Dz}, pos[3];
+    const int n[3] = {g.Uo, g.Vo, g.Wo};
+    stored_offset(d, pos, n, g.hv);
+    const double *md = g.mom + ((size_t)(d[2] * g.Vo + d[1]) * g.Uo + d[0]) * g.ms * kMoments;
+    double Ks[6];
+    kernel_from_moments(md, d[0], d[1], d[2], k, g.r, g.hv, Ks);
+    // component ab of K is component pos[a] pos[b] of the stored offset's
+    for (int a = 0; a < 3; a++) K[a] = pos[a] == 0 ? Ks[0] : pos[a] == 1 ? Ks[1] : Ks[2];
+    auto off = [&](int i) { return i == 1 ? Ks[3] : i == 2 ? Ks[4] : Ks[5]; };   // by the sum of the two axes
+    K[3] = off(pos[0] + pos[1]);
+    K[4] = off(pos[0] + pos[2]);
+    K[5] = off(pos[1] + pos[2]);
     double sx = Dx < 0 ? -1.0 : 1.0, sy = Dy < 0 ? -1.0 : 1.0, sz = Dz < 0 ? -1.0 : 1.0;
     K[3] *= sx * sy;
     K[4] *= sx * sz;
@@ -508,30 +676,16 @@ __global__ void __launch_bounds__(kGenThreads) k_offgrid_table(OffgridArg oa, Ge
     int a_lo, nsh;
     shell_range_real(Dv, oa.hv, oa.r, a_lo, nsh);
     const double D[3] = {Dv[0] * oa.hv[0], Dv[1] * oa.hv[1], Dv[2] * oa.hv[2]};
-    const int nq = ga.nq;
-    __shared__ double glx[kMaxQ], glw[kMaxQ], g3x[3], g3w[3];
+    __shared__ GenLds lds;
     __shared__ double mom[kShellCap * kMoments];
-    for (int t = threadIdx.x; t < kMaxQ; t += kGenThreads) {
-        glx[t] = ga.glx[t];
-        glw[t] = ga.glw[t];
-    }
-    if (threadIdx.x < 3) {
-        g3x[threadIdx.x] = ga.g3x[threadIdx.x];
-        g3w[threadIdx.x] = ga.g3w[threadIdx.x];
-    }
-    __syncthreads();
-    const int nitems = gen_items(nq);
+    const int cls = order_class(Dv[0], Dv[1], Dv[2], oa.hv), ns = ga.rules->ns[cls], nt = ga.rules->nt[cls];
+    load_rules(lds, *ga.rules, cls);
     for (int sh = 0; sh < nsh; sh++) {
         double m[kMoments];
+        shell_moments<ANI>(lds, ns, nt, D, a_lo + sh, oa.r, oa.hv, oa.ih, m);
+        if (threadIdx.x == 0)
 #pragma unroll
-        for (int t = 0; t < kMoments; t++) m[t] = 0.0;
-        for (int it = threadIdx.x; it < nitems; it += kGenThreads)
-            gen_item<ANI>(nq, glx, glw, g3x, g3w, D, a_lo + sh, oa.r, oa.hv, oa.ih, it, m);
-#pragma unroll
-        for (int t = 0; t < kMoments; t++) {
-            const double s_ = wave_sum(m[t]);
-            if (threadIdx.x == 0) mom[sh * kMoments + t] = s_;
-        }
+            for (int t = 0; t < kMoments; t++) mom[sh * kMoments + t] = m[t];
     }
     __syncthreads();
     for (int wl = threadIdx.x; wl < oa.nw; wl += kGenThreads) {
@@ -581,6 +735,32 @@ void legendre_rule(int n, double *x, double *w)
 
 }  // namespace
 
+// The rules for quad_order (0: by class), on the device for as long as the object lives.
+namespace {
+struct RulesOnDevice {
+    DevTemp tmp;
+    hipStream_t st;
+    RulesOnDevice(int quad_order, const DevAlloc &da, hipStream_t s) : tmp(da, sizeof(GenRules), "quadrature rules"), st(s)
+    {
+        if (quad_order != 0 && (quad_order < 4 || quad_order > kMaxQ)) throw ArgError("quad_order must be in [4, 24]");
+        GenRules R{};
+        for (int c = 0; c < kOrderClasses; c++) {
+            R.ns[c] = quad_order ? quad_order : kClassS[c];
+            R.nt[c] = quad_order ? quad_order : kClassT[c];
+            R.rs[c] = 2 * c;
+            R.rt[c] = 2 * c + 1;
+            legendre_rule(R.ns[c], R.x[2 * c], R.w[2 * c]);
+            legendre_rule(R.nt[c], R.x[2 * c + 1], R.w[2 * c + 1]);
+        }
+        legendre_rule(3, R.g3x, R.g3w);
+        MJ_CHECK(hipMemcpyAsync(tmp.p, &R, sizeof R, hipMemcpyHostToDevice, st));
+        MJ_CHECK(hipStreamSynchronize(st));
+    }
+    ~RulesOnDevice() { (void)hipStreamSynchronize(st); }   // the kernel that reads them has ended
+    const GenRules *get() const { return tmp.as<GenRules>(); }
+};
+}  // namespace
+
 static void check_geometry(double r, const double hv[3])
 {
     const double hmin = fmin(hv[0], fmin(hv[1], hv[2])), hmax = fmax(hv[0], fmax(hv[1], hv[2]));
@@ -592,13 +772,13 @@ static void check_geometry(double r, const double hv[3])
 void gen_moments(GenResult &g, int U, int V, int W, double r, const double hv[3], int nquad, const DevAlloc &da,
                  hipStream_t st)
 {
-    if (nquad < 4 || nquad > kMaxQ) throw ArgError("quad_order must be in [4, 24]");
+    const RulesOnDevice rules(nquad, da, st);
     check_geometry(r, hv);
     GenArg ga{};
+    ga.rules = rules.get();
     ga.Uo = U;
     ga.Vo = V;
     ga.Wo = W;
-    ga.nq = nquad;
     ga.r = r;
     for (int i = 0; i < 3; i++) {
         ga.hv[i] = hv[i];
@@ -606,8 +786,6 @@ void gen_moments(GenResult &g, int U, int V, int W, double r, const double hv[3]
         g.hv[i] = hv[i];
     }
     ga.ms = shells_per_offset(r, hv);
-    legendre_rule(nquad, ga.glx, ga.glw);
-    legendre_rule(3, ga.g3x, ga.g3w);
     g.Uo = U;
     g.Vo = V;
     g.Wo = W;
@@ -644,16 +822,14 @@ void gen_kernel_values(const GenResult &g, int n, const int *lag_dev, const int 
 
 void gen_offgrid_table(const double *pos_dev, const int *pair_probe_dev, const int *pair_vox_dev,
                        const int *pair_kmin_dev, long npairs, int U, int V, double r, const double hv[3], int nw,
-                       int kmax, int nquad, double *out_dev, hipStream_t st)
+                       int kmax, int nquad, double *out_dev, const DevAlloc &da, hipStream_t st)
 {
     if (npairs <= 0) return;
     check_geometry(r, hv);
-    if (nquad < 4 || nquad > kMaxQ) throw ArgError("quad_order must be in [4, 24]");
     if (npairs > 0x7fffffffL) throw ArgError("too many probe pairs");
+    const RulesOnDevice rules(nquad, da, st);
     GenArg ga{};
-    ga.nq = nquad;
-    legendre_rule(nquad, ga.glx, ga.glw);
-    legendre_rule(3, ga.g3x, ga.g3w);
+    ga.rules = rules.get();
     OffgridArg oa{};
     oa.pos = pos_dev;
     oa.pair_probe = pair_probe_dev;

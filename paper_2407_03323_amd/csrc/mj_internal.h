@@ -147,14 +147,16 @@ constexpr double kMinCdtOverH = 0.3;   // smallest c dt / max(h) the generator a
 constexpr int kShellCap = 16;          // shells per offset at c dt = 0.3 max(h): at most 14
 
 struct GenResult {
-    double *moments = nullptr;  // [Woct][Voct][Uoct][ms][kMoments]
+    double *moments = nullptr;  // [Woct][Voct][Uoct][ms][kMoments], filled at one of each set of offsets
+                                // that are permutations of each other along equal edges
     int Uo = 0, Vo = 0, Wo = 0;
     int ms = 0;                 // shells stored per offset
     double r = 1.0;             // c dt, in units of the x edge
     double hv[3] = {1.0, 1.0, 1.0};   // voxel edges, in units of the x edge
 };
 
-// r = c dt and hv = voxel edges, both in units of the x edge (hv[0] = 1)
+// r = c dt and hv = voxel edges, both in units of the x edge (hv[0] = 1); nquad points per quadrature cell,
+// or 0: the orders that the distance of the voxels asks for
 void gen_moments(GenResult &g, int U, int V, int W, double r, const double hv[3], int nquad, const DevAlloc &da,
                  hipStream_t st);
 // K_k on the full periodic grid [6][Nz][Ny][Nx] (real), from the octant moments
@@ -165,7 +167,7 @@ void gen_kernel_grid(const GenResult &g, int k, int Nx, int Ny, int Nz, double *
 // (zero above kmax): out[nw][pair][6].
 void gen_offgrid_table(const double *pos_dev, const int *pair_probe_dev, const int *pair_vox_dev,
                        const int *pair_kmin_dev, long npairs, int U, int V, double r, const double hv[3], int nw,
-                       int kmax, int nquad, double *out_dev, hipStream_t st);
+                       int kmax, int nquad, double *out_dev, const DevAlloc &da, hipStream_t st);
 
 void gen_kernel_values(const GenResult &g, int n, const int *lag_dev, const int *off_dev, double *out_dev,
                        hipStream_t st);
