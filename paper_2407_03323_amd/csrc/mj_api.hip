@@ -168,6 +168,8 @@ struct mj_solver {
     int nquad = 0;                  // quadrature points per cell of the kernels (0: by distance)
     hipStream_t st = nullptr;
     int nloc = 5, rdepth = 6;
+    int sdepth = 6;                 // steps of the real-space history that later steps read, and that a state
+                                    // holds (with probes the ring holds kProbeSteps - 1 more)
     // degree of the extrapolated initial guess of the Z_0 solve (at most; the steps it goes through
     // are those the taps read anyway, and seven at least).  Iterations with degree 4, 6 and 8: 104^3
     // 16, 14, 12; 64^3 21, 19, 18; 32^3 24, 23, 23.  At 104^3 degree 10 took more again: higher
@@ -244,9 +246,11 @@ struct mj_solver {
     std::vector<double> eps_h;
     int np = 0, nw = 0;
     long npairs = 0;
-    double *probe_pos = nullptr, *ptable = nullptr, *ppart = nullptr, *pout = nullptr;
-    int *pair_vox = nullptr, *pair_kmin = nullptr, *row_start = nullptr, *pinv = nullptr;
-    int *ck_row = nullptr, *ck_lo = nullptr, *ck_hi = nullptr, *ck_start = nullptr;   // probe row chunks
+    double *probe_pos = nullptr, *ptable = nullptr, *ppart = nullptr;
+    int *pair_vox = nullptr, *pair_kmin = nullptr, *pinv = nullptr;
+    int *ck_lo = nullptr, *ck_hi = nullptr, *ck_start = nullptr;   // chunks of the probes' pairs
+    double *probe_out = nullptr;    // where the probe field of the steps taken but not yet formed goes
+    int probe_n0 = 0, probe_steps = 0;   // those steps
     double *ptable_v = nullptr;   // probe kernel table ordered by voxel (adjoint source)
     int *pkmin_v = nullptr;
     long pnck = 0;
@@ -312,8 +316,9 @@ struct mj_solver {
     struct StepIO {
         hipEvent_t *ev = nullptr;       // 7 events, or NULL
         double *Jout = nullptr;         // forward: J_n copy
-        double *Pout = nullptr;         // forward: probe field of the step (else the internal buffer)
-        bool skip_probes = false;
+        double *Pout = nullptr;         // forward: the probe field of the step goes here (NULL: not formed), once
+                                        // kProbeSteps of them are due or flush_probes is called; those of
+                                        // successive steps follow each other
         double *Bout = nullptr;         // forward: gradient term B_n
         char *far_kind = nullptr;       // 1 far (outer) launch, 2 near launch, 3 middle launch
         bool adjoint = false;           // transposed march
@@ -361,6 +366,15 @@ struct mj_solver {
     }
     mj::AdjArg adj_arg() const;
     void step(const StepIO &io);
+    void flush_probes();
+    void flush_after_failure()
+    {
+        try {
+            flush_probes();
+        } catch (...) {   // the step's own failure is the one to report
+        }
+        probe_steps = 0;
+    }
     void check_growth() const;
     void run(int n_steps, double *Jout, double *Pout, int j_every = 1);
     void restart();
@@ -457,7 +471,7 @@ void mj_solver::create(const mj_config &c)
         throw ArgError("outer_block must be a multiple of time_block in 8 .. 16 (even), or 0");
     // steps kept for the initial guess (7 or more) and the taps; the guess takes up to 9 of them
     nloc = std::max(7, (int)fir.size() - 1);
-    rdepth = nloc + 1;
+    rdepth = sdepth = nloc + 1;
 
     // The Z_0 solve.  By default the passes of an earlier step's CG are replayed (solve_z0); behind
     // them stands the Chebyshev iteration on small grids, whose launches decide (32^3: 4 us a pass
@@ -1310,34 +1324,44 @@ void mj_solver::step(const StepIO &io)
             mj::launch_grad_accum(a, st);
         }
     } else {
-        if (np > 0 && !io.skip_probes) {
-            mj::ProbeStepArg pa{};
-            pa.table = ptable;
-            pa.pair_vox = pair_vox;
-            pa.pair_kmin = pair_kmin;
-            pa.row_start = row_start;
-            pa.np = np;
-            pa.ell = ell;
-            pa.nw = nw;
-            pa.nrhs = nrhs;
-            pa.n = n;
-            pa.M = M;
-            pa.npairs = npairs;
-            pa.Jring = Jr;
-            pa.rdepth = rdepth;
-            pa.part = ppart;
-            pa.ck_row = ck_row;
-            pa.ck_lo = ck_lo;
-            pa.ck_hi = ck_hi;
-            pa.ck_start = ck_start;
-            pa.nck = pnck;
-            pa.out = io.Pout ? io.Pout : pout;
-            mj::launch_probes(pa, st);
+        if (np > 0 && io.Pout) {
+            if (probe_steps == 0) {
+                probe_out = io.Pout;
+                probe_n0 = n;
+            }
+            if (++probe_steps == mj::kProbeSteps) flush_probes();
         }
         if (io.Bout)
             mj::launch_grad_term(e, Jn, n >= 2 ? Jr + (size_t)slotR(n - 1) * nrhs * 3 * M : nullptr, io.Bout, st);
     }
     if (ev) MJ_CHECK(hipEventRecord(ev[6], st));
+}
+
+// Forms the probe field of the steps that wait for it.
+void mj_solver::flush_probes()
+{
+    if (probe_steps == 0) return;
+    mj::ProbeStepArg pa{};
+    pa.table = ptable;
+    pa.pair_vox = pair_vox;
+    pa.pair_kmin = pair_kmin;
+    pa.np = np;
+    pa.nw = nw;
+    pa.nrhs = nrhs;
+    pa.n0 = probe_n0;
+    pa.ntarget = probe_steps;
+    pa.M = M;
+    pa.npairs = npairs;
+    pa.Jring = Jr;
+    pa.rdepth = rdepth;
+    pa.part = ppart;
+    pa.ck_lo = ck_lo;
+    pa.ck_hi = ck_hi;
+    pa.ck_start = ck_start;
+    pa.nck = pnck;
+    pa.out = probe_out;
+    probe_steps = 0;
+    mj::launch_probes(pa, st);
 }
 
 // The march grows without bound (Sec. 5.2 and 6: the alternating mode at f = 1/(2 dt)): stop once the
@@ -1392,8 +1416,13 @@ void mj_solver::run(int n_steps, double *Jout, double *Pout, int j_every)
         io.Jout = (Jout && (s + 1) % j_every == 0) ? Jout + (size_t)((s + 1) / j_every - 1) * nrhs * 3 * M : nullptr;
         io.Pout = Pout ? Pout + (size_t)s * nrhs * np * 3 : nullptr;
         io.far_kind = &step_far[s];
-        step(io);
-        check_growth();
+        try {
+            step(io);
+            check_growth();
+        } catch (...) {
+            flush_after_failure();
+            throw;
+        }
         for (int i = 0; i < nrhs; i++) {
             cg_iter_sum += cgstat_h[i].iters;
             cg_iter_max = std::max(cg_iter_max, (double)cgstat_h[i].iters);
@@ -1401,6 +1430,8 @@ void mj_solver::run(int n_steps, double *Jout, double *Pout, int j_every)
             if (!cgstat_h[i].done) noconv = true;
         }
     }
+    flush_probes();
+    if (n_steps > 0) MJ_CHECK(hipEventRecord(events.ev[(size_t)7 * n_steps - 1], st));   // with the last probes
     MJ_CHECK(hipStreamSynchronize(st));
     double ph[6] = {0, 0, 0, 0, 0, 0}, probe_ms = 0;
     double far_ms = 0, near_ms = 0, mid_ms = 0;
@@ -1457,6 +1488,7 @@ void mj_solver::restart()
     cg_guess = 8;
     cheb_pred = 0;
     rp = Replay();
+    probe_steps = 0;
     n = 0;
 }
 
@@ -1524,12 +1556,9 @@ void mj_solver::set_probes(int n_probes, const double *pos)
     dfree((void *&)probe_pos);
     dfree((void *&)ptable);
     dfree((void *&)ppart);
-    dfree((void *&)pout);
     dfree((void *&)pair_vox);
     dfree((void *&)pair_kmin);
-    dfree((void *&)row_start);
     dfree((void *&)pinv);
-    dfree((void *&)ck_row);
     dfree((void *&)ck_lo);
     dfree((void *&)ck_hi);
     dfree((void *&)ck_start);
@@ -1552,7 +1581,7 @@ void mj_solver::set_probes(int n_probes, const double *pos)
     struct Pair {
         int kmin, vox;
     };
-    std::vector<int> pp, pv, pk, rs((size_t)n_probes * (ell + 2));
+    std::vector<int> pp, pv, pk, clo, chi_, cst;
     int nwin = 1;
     for (int p = 0; p < n_probes; p++) {
         std::vector<Pair> list;
@@ -1574,11 +1603,12 @@ void mj_solver::set_probes(int n_probes, const double *pos)
             list.push_back({kmin, m});
         }
         std::stable_sort(list.begin(), list.end(), [](const Pair &a, const Pair &b) { return a.kmin < b.kmin; });
-        const int base = (int)pp.size();
-        size_t q = 0;
-        for (int kk = 0; kk <= ell + 1; kk++) {
-            while (q < list.size() && list[q].kmin < kk) q++;
-            rs[(size_t)p * (ell + 2) + kk] = base + (int)q;
+        // chunks of at most kProbeChunk pairs, probe by probe
+        const int base = (int)pp.size(), end = base + (int)list.size();
+        cst.push_back((int)clo.size());
+        for (int q = base; q < end; q += mj::kProbeChunk) {
+            clo.push_back(q);
+            chi_.push_back(std::min(end, q + mj::kProbeChunk));
         }
         for (const Pair &x : list) {
             pp.push_back(p);
@@ -1592,7 +1622,6 @@ void mj_solver::set_probes(int n_probes, const double *pos)
     probe_pos = dalloc<double>(P.size(), "probe positions");
     pair_vox = dalloc<int>(std::max<size_t>(pv.size(), 1), "probe pairs");
     pair_kmin = dalloc<int>(std::max<size_t>(pk.size(), 1), "probe windows");
-    row_start = dalloc<int>(rs.size(), "probe rows");
     {
         std::vector<int> inv((size_t)n_probes * M, -1);
         for (size_t q = 0; q < pp.size(); q++) inv[(size_t)pp[q] * M + pv[q]] = (int)q;
@@ -1602,37 +1631,19 @@ void mj_solver::set_probes(int n_probes, const double *pos)
     int *pair_probe = dalloc<int>(std::max<size_t>(pp.size(), 1), "probe pair owners");
     ptable = dalloc<double>((size_t)std::max<long>(npairs, 1) * nw * 6, "probe kernel table");
     {
-        // every row (p, k) cut into chunks of at most kProbeChunk pairs, probe by probe
-        std::vector<int> crow, clo, chi_, cst;
-        for (int p = 0; p < n_probes; p++) {
-            cst.push_back((int)crow.size());
-            for (int kk = 0; kk <= ell; kk++) {
-                const int lo = rs[(size_t)p * (ell + 2) + std::max(0, kk - nwin + 1)];
-                const int hi = rs[(size_t)p * (ell + 2) + kk + 1];
-                for (int q = lo; q < hi; q += mj::kProbeChunk) {
-                    crow.push_back(p * (ell + 1) + kk);
-                    clo.push_back(q);
-                    chi_.push_back(std::min(hi, q + mj::kProbeChunk));
-                }
-            }
-        }
-        cst.push_back((int)crow.size());
-        pnck = (long)crow.size();
-        ck_row = dalloc<int>(std::max<size_t>(crow.size(), 1), "probe chunks");
-        ck_lo = dalloc<int>(std::max<size_t>(crow.size(), 1), "probe chunks");
-        ck_hi = dalloc<int>(std::max<size_t>(crow.size(), 1), "probe chunks");
+        cst.push_back((int)clo.size());
+        pnck = (long)clo.size();
+        ck_lo = dalloc<int>(std::max<size_t>(clo.size(), 1), "probe chunks");
+        ck_hi = dalloc<int>(std::max<size_t>(clo.size(), 1), "probe chunks");
         ck_start = dalloc<int>(cst.size(), "probe chunks");
         if (pnck > 0) {
-            MJ_CHECK(hipMemcpy(ck_row, crow.data(), sizeof(int) * crow.size(), hipMemcpyHostToDevice));
             MJ_CHECK(hipMemcpy(ck_lo, clo.data(), sizeof(int) * clo.size(), hipMemcpyHostToDevice));
             MJ_CHECK(hipMemcpy(ck_hi, chi_.data(), sizeof(int) * chi_.size(), hipMemcpyHostToDevice));
         }
         MJ_CHECK(hipMemcpy(ck_start, cst.data(), sizeof(int) * cst.size(), hipMemcpyHostToDevice));
     }
-    ppart = dalloc<double>((size_t)nrhs * std::max<long>(pnck, 1) * 3, "probe partial sums");
-    pout = dalloc<double>((size_t)nrhs * np * 3, "probe field");
+    ppart = dalloc<double>((size_t)nrhs * std::max<long>(pnck, 1) * mj::kProbeSteps * 3, "probe partial sums");
     MJ_CHECK(hipMemcpy(probe_pos, P.data(), sizeof(double) * P.size(), hipMemcpyHostToDevice));
-    MJ_CHECK(hipMemcpy(row_start, rs.data(), sizeof(int) * rs.size(), hipMemcpyHostToDevice));
     if (npairs > 0) {
         MJ_CHECK(hipMemcpy(pair_vox, pv.data(), sizeof(int) * pv.size(), hipMemcpyHostToDevice));
         MJ_CHECK(hipMemcpy(pair_kmin, pk.data(), sizeof(int) * pk.size(), hipMemcpyHostToDevice));
@@ -1655,10 +1666,11 @@ void mj_solver::set_probes(int n_probes, const double *pos)
     ptable_v = dalloc<double>((size_t)nw * n_probes * M * 6, "probe kernel table by voxel");
     pkmin_v = dalloc<int>((size_t)n_probes * M, "probe windows by voxel");
     mj::launch_probe_table_by_voxel(ptable, pair_kmin, pinv, npairs, n_probes, nw, M, ptable_v, pkmin_v, st);
-    // the probe rows read J_{n-k} for k = 0..ell from the real-space ring
-    if (rdepth < ell + 1) {
+    sdepth = std::max(sdepth, ell + 1);
+    // the probe sums of kProbeSteps steps read J_{n-k} for k = 0..ell from the real-space ring
+    if (rdepth < ell + mj::kProbeSteps) {
         dfree((void *&)Jr);
-        rdepth = ell + 1;
+        rdepth = ell + mj::kProbeSteps;
         Jr = dalloc<double>((size_t)rdepth * nrhs * 3 * M, "current history");
     }
     MJ_CHECK(hipStreamSynchronize(st));
@@ -1724,7 +1736,7 @@ size_t mj_solver::state_bytes() const
     const size_t sp = (size_t)spec_plane(), v3 = (size_t)nrhs * 3;
     return sizeof(StateHeader) + sizeof(Replay) + sizeof(double) * coef_count() + sizeof(double2) * (size_t)ell * v3 * sp +
            (farbuf ? sizeof(double2) * (size_t)B * v3 * sp : 0) + (gbuf ? sizeof(double2) * (size_t)B2 * v3 * sp : 0) +
-           sizeof(double) * (size_t)rdepth * v3 * M;
+           sizeof(double) * (size_t)sdepth * v3 * M;
 }
 
 void mj_solver::get_state(void *buf) const
@@ -1739,7 +1751,7 @@ void mj_solver::get_state(void *buf) const
     h.nrhs = nrhs;
     h.ell = ell;
     h.B = B;
-    h.rdepth = rdepth;
+    h.rdepth = sdepth;
     h.Nx = Nx;
     h.Ny = Ny;
     h.Nz = Nz;
@@ -1749,7 +1761,7 @@ void mj_solver::get_state(void *buf) const
     h.n = n;
     h.ring_bytes = (int64_t)(sizeof(double2) * (size_t)ell * v3 * sp);
     h.far_bytes = farbuf ? (int64_t)(sizeof(double2) * (size_t)B * v3 * sp) : 0;
-    h.jr_bytes = (int64_t)(sizeof(double) * (size_t)rdepth * v3 * M);
+    h.jr_bytes = (int64_t)(sizeof(double) * (size_t)h.rdepth * v3 * M);
     h.outer_bytes = gbuf ? (int64_t)(sizeof(double2) * (size_t)B2 * v3 * sp) : 0;
     char *p = (char *)buf;
     std::memcpy(p, &h, sizeof h);
@@ -1763,7 +1775,16 @@ void mj_solver::get_state(void *buf) const
     p += h.ring_bytes;
     if (h.far_bytes) MJ_CHECK(hipMemcpy(p, farbuf, (size_t)h.far_bytes, hipMemcpyDeviceToHost));
     p += h.far_bytes;
-    MJ_CHECK(hipMemcpy(p, Jr, (size_t)h.jr_bytes, hipMemcpyDeviceToHost));
+    if (h.rdepth == rdepth) {
+        MJ_CHECK(hipMemcpy(p, Jr, (size_t)h.jr_bytes, hipMemcpyDeviceToHost));
+    } else {
+        // step j of the last h.rdepth ones at slot j mod h.rdepth
+        const size_t vec = v3 * M;
+        std::memset(p, 0, (size_t)h.jr_bytes);
+        for (int j = std::max(1, n - h.rdepth + 1); j <= n; j++)
+            MJ_CHECK(hipMemcpy(p + (size_t)(j % h.rdepth) * vec * 8, Jr + (size_t)slotR(j) * vec, vec * 8,
+                               hipMemcpyDeviceToHost));
+    }
     p += h.jr_bytes;
     if (h.outer_bytes) MJ_CHECK(hipMemcpy(p, gbuf, (size_t)h.outer_bytes, hipMemcpyDeviceToHost));
 }
@@ -1777,7 +1798,7 @@ void mj_solver::set_state(const void *buf, size_t bytes)
     if (h.U != U || h.V != V || h.W != W || h.nrhs != nrhs || h.ell != ell || h.B != B || h.B2 != B2 ||
         h.Nx != Nx || h.Ny != Ny || h.Nz != Nz || h.Hp != Hp)
         throw ArgError("state of a solver with another grid, n_rhs, ell or time blocks");
-    if (h.rdepth != rdepth) throw ArgError("state of a solver with another history depth (probes differ)");
+    if (h.rdepth != sdepth) throw ArgError("state of a solver with another history depth (probes differ)");
     const size_t solve_bytes = sizeof(Replay) + sizeof(double) * coef_count();
     const size_t need = state_bytes() - (h.version == 2 ? solve_bytes : 0);
     if (bytes < need || (size_t)h.ring_bytes + (size_t)h.far_bytes + (size_t)h.jr_bytes + (size_t)h.outer_bytes +
@@ -1803,7 +1824,14 @@ void mj_solver::set_state(const void *buf, size_t bytes)
     p += h.ring_bytes;
     if (h.far_bytes) MJ_CHECK(hipMemcpy(farbuf, p, (size_t)h.far_bytes, hipMemcpyHostToDevice));
     p += h.far_bytes;
-    MJ_CHECK(hipMemcpy(Jr, p, (size_t)h.jr_bytes, hipMemcpyHostToDevice));
+    if (h.rdepth == rdepth) {
+        MJ_CHECK(hipMemcpy(Jr, p, (size_t)h.jr_bytes, hipMemcpyHostToDevice));
+    } else {
+        const size_t vec = (size_t)nrhs * 3 * M;
+        for (int j = (int)std::max<int64_t>(1, h.n - h.rdepth + 1); j <= h.n; j++)
+            MJ_CHECK(hipMemcpy(Jr + (size_t)slotR(j) * vec, p + (size_t)(j % h.rdepth) * vec * 8, vec * 8,
+                               hipMemcpyHostToDevice));
+    }
     p += h.jr_bytes;
     if (h.outer_bytes) MJ_CHECK(hipMemcpy(gbuf, p, (size_t)h.outer_bytes, hipMemcpyHostToDevice));
     n = (int)h.n;
@@ -1864,7 +1892,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
     double *Ehist = (double *)talloc(sizeof(double) * (size_t)N * nrhs * np * 3, "probe history");
     double *ckpt = (double *)talloc(sizeof(double) * (size_t)std::max<long>(npool, 1) * vec, "checkpoints");
     double *Bbuf = (double *)talloc(sizeof(double) * (size_t)maxseg * vec, "gradient terms");
-    double *G = (double *)talloc(sizeof(double) * vec, "adjoint source");
+    double *G = (double *)talloc(sizeof(double) * mj::kProbeSteps * vec, "adjoint source");
     double *bqb = (double *)talloc(sizeof(double) * vec, "adjoint rhs");
     double2 *ring_a = (double2 *)talloc(sizeof(double2) * (size_t)ell * nrhs * 3 * sp, "adjoint ring");
     double2 *far_a = B > 1 ? (double2 *)talloc(sizeof(double2) * (size_t)B * nrhs * 3 * sp, "adjoint blocks") : nullptr;
@@ -1922,6 +1950,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
                 MJ_CHECK(hipMemcpyAsync(ckpt + (size_t)pool_of[(size_t)t] * vec, Jr + (size_t)slotR(t) * vec,
                                         sizeof(double) * vec, hipMemcpyDeviceToDevice, st));
         }
+        flush_probes();
         if (probe_hist)
             MJ_CHECK(hipMemcpyAsync(probe_hist, Ehist, sizeof(double) * (size_t)N * nrhs * np * 3,
                                     hipMemcpyDeviceToDevice, st));
@@ -1953,7 +1982,6 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
                 load_record(rec_at[(size_t)c], c);
                 for (int t = s0; t <= s1; t++) {
                     StepIO io;
-                    io.skip_probes = true;
                     io.Bout = Bbuf + (size_t)(t - s0) * vec;
                     step(io);
                     check_cg();
@@ -1970,15 +1998,19 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
             n = n_adj;
             load_record(rec_adj, C);
             for (int j = s1; j >= s0; j--) {
-                mj::AdjArg a = adj_arg();
-                a.Ehist = Ehist;
-                a.N = N;
-                a.j = j;
-                a.G = G;
-                mj::launch_adj_source(a, st);
+                const int at = (s1 - j) % mj::kProbeSteps;   // the source of up to kProbeSteps steps at once
+                if (at == 0) {
+                    mj::AdjArg a = adj_arg();
+                    a.Ehist = Ehist;
+                    a.N = N;
+                    a.j = j;
+                    a.ntarget = std::min(mj::kProbeSteps, j - s0 + 1);
+                    a.G = G;
+                    mj::launch_adj_source(a, st);
+                }
                 StepIO io;
                 io.adjoint = true;
-                io.G = G;
+                io.G = G + (size_t)at * vec;
                 io.Bj = Bbuf + (size_t)(j - s0) * vec;
                 io.grad = grad_dev;
                 step(io);
@@ -2007,6 +2039,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
         Jr = Jr_f;
         Lr = nullptr;
         bq = nullptr;
+        probe_steps = 0;
         for (void *q : tmp) da.put(q);
         for (auto &tv : tev) (void)hipEventDestroy(tv);
         rp = Replay();
@@ -2089,7 +2122,7 @@ int mj_info(const mj_solver *s, double *out, int32_t n)
 {
     if (!s || !out) return MJ_EINVAL;
     double v[24] = {(double)s->ell, (double)s->Nx, (double)s->Ny, (double)s->Nz, (double)s->B,
-                    (double)s->rdepth, (double)s->nrhs, (double)s->n, (double)s->bytes, s->t_gen_ms,
+                    (double)s->sdepth, (double)s->nrhs, (double)s->n, (double)s->bytes, s->t_gen_ms,
                     s->t_spec_ms, (double)s->fir.size(), (double)s->np, (double)s->nw, (double)s->npairs,
                     s->t_probe_ms, (double)s->fft.Px, (double)s->fft.Py, (double)s->fft.Pz, (double)s->B2,
                     (double)s->z0_method, s->lam_lo, s->lam_hi, s->overlap ? 1.0 : 0.0};

@@ -87,9 +87,11 @@ struct AdjArg {
     const double *table_v;   // the same table by voxel: [nw][np][M][6] (zeros where inv < 0)
     const int *kmin_v;       // [np][M] first lag of the pair's window, -1 if no pair
     const double *Ehist;     // [N][nrhs][np][3]
-    int np, nw, N, j;        // j: forward step of this adjoint step
+    int np, nw, N, j;        // j: forward step of this adjoint step (the source: the first of ntarget,
+                             // j, j - 1, ...)
+    int ntarget;             // steps the source is formed for, at most kProbeSteps
     long npairs;
-    double *G;               // out [nrhs][3][M]
+    double *G;               // out [nrhs][3][M]; the source: [ntarget][nrhs][3][M]
     // lambda from the solve
     const double *schi, *c0, *bq, *nu;   // nu: [nrhs][3][M] of this step
     double *lam;             // out [nrhs][3][M]
@@ -169,28 +171,25 @@ void launch_z0_pass(const PassArg &a, hipStream_t st);
 void launch_fill_trial(const double *schi, int U, int V, int W, double *b, hipStream_t st);
 
 // Scattered field at probe points: E^s_p(n) = sum_{k=0}^{ell} sum_s K_k(r_p - r_s) J_{n-k}(s)
-// over the source voxels s of the scatterer.  Pairs (p, s) are stored per probe sorted by the
-// first lag kmin of their window, so the sources that lag k reaches through window slot
-// k - kmin form one contiguous run: row (p, k) = pairs [row_start[p][max(0, k-nw+1)],
-// row_start[p][k+1]).  The host cuts every row into chunks for the waves.
+// over the source voxels s of the scatterer, for the ntarget steps n0 .. n0 + ntarget - 1 at once.  Pairs
+// (p, s) are stored per probe sorted by the first lag kmin of their window of nw lags; the host cuts each
+// probe's pairs into chunks for the waves.
+constexpr int kProbeChunk = 128;    // pairs handled by one wave
+constexpr int kProbeSteps = 8;      // steps taken together
 struct ProbeStepArg {
-    const double *table;     // [nw][npairs][6]
+    const double *table;     // [nw][npairs][6], zero for lags above ell
     const int *pair_vox;     // [npairs]
     const int *pair_kmin;    // [npairs]
-    const int *row_start;    // [np][ell + 2]
-    int np, ell, nw, nrhs, n;
-    // rows cut into chunks of at most kProbeChunk pairs, listed probe by probe: chunk c covers
-    // pairs [ck_lo[c], ck_hi[c]) of row ck_row[c] = p (ell + 1) + k; probe p owns chunks
-    // [ck_start[p], ck_start[p + 1])
-    const int *ck_row, *ck_lo, *ck_hi, *ck_start;
+    int np, nw, nrhs, n0, ntarget;
+    // chunk c covers pairs [ck_lo[c], ck_hi[c]) of one probe; probe p owns chunks [ck_start[p], ck_start[p + 1])
+    const int *ck_lo, *ck_hi, *ck_start;
     long nck;
     long M, npairs;
-    const double *Jring;     // [rdepth][nrhs][3][M]
+    const double *Jring;     // [rdepth][nrhs][3][M], rdepth > ell + ntarget - 1
     int rdepth;
-    double *part;            // [nrhs][nck][3]
-    double *out;             // [nrhs][np][3]
+    double *part;            // [nrhs][nck][kProbeSteps][3]
+    double *out;             // [ntarget][nrhs][np][3]
 };
-constexpr int kProbeChunk = 1024;   // pairs of one row handled by one wave
 
 void launch_mac(const MacArg &a, hipStream_t st);
 void launch_mac_far(const BlockMacArg &a, int tb, hipStream_t st);

@@ -1346,77 +1346,103 @@ void launch_fill_trial(const double *schi, int U, int V, int W, double *b, hipSt
 }
 
 // ---------------------------------------------------------------------------- probes
-// One wave per chunk (at most kProbeChunk pairs of one row (p, k)): the sources whose lag window
-// holds k, each through its window slot k - kmin, against J_{n-k}; lanes take pairs q and q + 64
-// together (two independent gathers in flight), and the wave sums in fixed order.
+// One wave per chunk (at most kProbeChunk pairs of one probe), lanes take its pairs in turn.  Nothing in the
+// march waits for the probe field, so a run forms it for kProbeSteps steps at a time: what bounds it is
+// reading the table (336 bytes a pair with 7 lags), and every record then serves 8 steps.  Along the pair's
+// window the source of step t at lag slot wl is that of step t - 1 at slot wl - 1, so the 8 + nw - 1 currents
+// a pair needs are read once into rotating registers (the slots are compile-time constants, as in k_mac_win).
+// Each step sums its pairs and lags in the same order however many steps share the launch.
+// 32^3, 12 probes, per step: 18 us of kernel against 74 us with the table read in every step; the chunk of 128
+// pairs leaves 3072 waves there (256: 20 us).
+template <int T>
 __global__ void __launch_bounds__(256) k_probe_rows(ProbeStepArg a)
 {
     const int lane = threadIdx.x & 63;
     const long c = blockIdx.x * 4L + (threadIdx.x >> 6);
     const int r = blockIdx.y;
     if (c >= a.nck) return;
-    const int L1 = a.ell + 1;
-    const int k = a.ck_row[c] % L1;
-    double acc[3] = {0.0, 0.0, 0.0};
-    const int j = a.n - k;
-    if (j >= 1) {
-        const int lo = a.ck_lo[c], hi = a.ck_hi[c];
-        const double *J = a.Jring + ((long)(j % a.rdepth) * a.nrhs + r) * 3 * a.M;
-        for (int q0 = lo + lane; q0 < hi; q0 += 128) {
-            const int q1 = q0 + 64;
-            const bool two = q1 < hi;
-            const int qb = two ? q1 : q0;
-            const int wl0 = k - a.pair_kmin[q0], wl1 = k - a.pair_kmin[qb];
-            const long m0 = a.pair_vox[q0], m1 = a.pair_vox[qb];
-            const double *K0 = a.table + ((long)wl0 * a.npairs + q0) * 6;
-            const double *K1 = a.table + ((long)wl1 * a.npairs + qb) * 6;
-            const double x0 = J[m0], y0 = J[a.M + m0], z0 = J[2 * a.M + m0];
-            const double x1 = J[m1], y1 = J[a.M + m1], z1 = J[2 * a.M + m1];
-            const double f = two ? 1.0 : 0.0;
-            acc[0] += K0[0] * x0 + K0[3] * y0 + K0[4] * z0;
-            acc[1] += K0[3] * x0 + K0[1] * y0 + K0[5] * z0;
-            acc[2] += K0[4] * x0 + K0[5] * y0 + K0[2] * z0;
-            acc[0] += f * (K1[0] * x1 + K1[3] * y1 + K1[4] * z1);
-            acc[1] += f * (K1[3] * x1 + K1[1] * y1 + K1[5] * z1);
-            acc[2] += f * (K1[4] * x1 + K1[5] * y1 + K1[2] * z1);
+    double ax[T], ay[T], az[T];
+#pragma unroll
+    for (int t = 0; t < T; t++) ax[t] = ay[t] = az[t] = 0.0;
+    const int hi = a.ck_hi[c];
+    for (int q = a.ck_lo[c] + lane; q < hi; q += 64) {
+        const int j0 = a.n0 - a.pair_kmin[q];   // source of step n0 at the first lag
+        const double *J = a.Jring + (long)r * 3 * a.M + a.pair_vox[q];
+        double jx[T], jy[T], jz[T];
+        // sources before the first step, and those of targets past the last, count as zero
+        auto load = [&](int j, bool ok, double &x, double &y, double &z) __attribute__((always_inline)) {
+            const double *s = J + (long)((ok && j >= 1) ? j % a.rdepth : 0) * a.nrhs * 3 * a.M;
+            const double vx = s[0], vy = s[a.M], vz = s[2 * a.M];
+            x = ok && j >= 1 ? vx : 0.0;
+            y = ok && j >= 1 ? vy : 0.0;
+            z = ok && j >= 1 ? vz : 0.0;
+        };
+#pragma unroll
+        for (int t = 0; t < T; t++) load(j0 + t, t < a.ntarget, jx[t], jy[t], jz[t]);
+        for (int w0 = 0; w0 < a.nw; w0 += T) {
+            [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
+                (
+                    [&] {
+                        if (w0 + I >= a.nw) return;
+                        if (w0 + I > 0) load(j0 - w0 - I, true, jx[(T - I) % T], jy[(T - I) % T], jz[(T - I) % T]);
+                        const double2 *K2 = (const double2 *)(a.table + ((long)(w0 + I) * a.npairs + q) * 6);
+                        const double2 v0 = K2[0], v1 = K2[1], v2 = K2[2];   // xx yy, zz xy, xz yz
+#pragma unroll
+                        for (int t = 0; t < T; t++) {
+                            const double x = jx[(t + T - I) % T], y = jy[(t + T - I) % T], z = jz[(t + T - I) % T];
+                            ax[t] = fma(v2.x, z, fma(v1.y, y, fma(v0.x, x, ax[t])));
+                            ay[t] = fma(v2.y, z, fma(v0.y, y, fma(v1.y, x, ay[t])));
+                            az[t] = fma(v1.x, z, fma(v2.y, y, fma(v2.x, x, az[t])));
+                        }
+                    }(),
+                    ...);
+            }(std::make_integer_sequence<int, T>{});
         }
     }
+    double *o = a.part + ((long)r * a.nck + c) * kProbeSteps * 3;
 #pragma unroll
-    for (int cc = 0; cc < 3; cc++)
-        for (int off = 32; off >= 1; off >>= 1) acc[cc] += __shfl_xor(acc[cc], off);
-    if (lane == 0) {
-        double *o = a.part + ((long)r * a.nck + c) * 3;
-        o[0] = acc[0];
-        o[1] = acc[1];
-        o[2] = acc[2];
+    for (int t = 0; t < T; t++) {
+        for (int off = 32; off >= 1; off >>= 1) {
+            ax[t] += __shfl_xor(ax[t], off);
+            ay[t] += __shfl_xor(ay[t], off);
+            az[t] += __shfl_xor(az[t], off);
+        }
+        if (lane == 0) {
+            o[3 * t] = ax[t];
+            o[3 * t + 1] = ay[t];
+            o[3 * t + 2] = az[t];
+        }
     }
 }
 
-// E^s_p(n) = sum over the chunks of probe p (rows k = 0 .. ell in order): one wave per
-// (rhs, probe), lane l adds chunks l, l + 64, ... in order, then a fixed butterfly.
+// E^s_p(n0 + t) = sum over the chunks of probe p: one wave per (step, rhs, probe), lane l adds chunks
+// l, l + 64, ... in order, then a fixed butterfly.
 __global__ void __launch_bounds__(64) k_probe_sum(ProbeStepArg a)
 {
-    const int r = blockIdx.x / a.np, p = blockIdx.x % a.np;
+    const int p = blockIdx.x % a.np, r = blockIdx.x / a.np % a.nrhs, t = blockIdx.x / a.np / a.nrhs;
     const int lane = threadIdx.x;
-    const double *src = a.part + (long)r * a.nck * 3;
+    const double *src = a.part + ((long)r * a.nck * kProbeSteps + t) * 3;
     double s[3] = {0.0, 0.0, 0.0};
     for (long i = a.ck_start[p] + lane; i < a.ck_start[p + 1]; i += 64)
 #pragma unroll
-        for (int cc = 0; cc < 3; cc++) s[cc] += src[3 * i + cc];
+        for (int cc = 0; cc < 3; cc++) s[cc] += src[i * kProbeSteps * 3 + cc];
 #pragma unroll
     for (int cc = 0; cc < 3; cc++)
         for (int off = 32; off >= 1; off >>= 1) s[cc] += __shfl_xor(s[cc], off);
     if (lane == 0)
-        for (int cc = 0; cc < 3; cc++) a.out[((long)r * a.np + p) * 3 + cc] = s[cc];
+        for (int cc = 0; cc < 3; cc++) a.out[(long)blockIdx.x * 3 + cc] = s[cc];
 }
 
 void launch_probes(const ProbeStepArg &a, hipStream_t st)
 {
+    if (a.ntarget < 1 || a.ntarget > kProbeSteps) throw std::logic_error("probe steps outside their launch");
     if (a.nck > 0) {
-        hipLaunchKernelGGL(k_probe_rows, dim3((unsigned)((a.nck + 3) / 4), a.nrhs), dim3(256), 0, st, a);
+        const dim3 grid((unsigned)((a.nck + 3) / 4), a.nrhs);
+        if (a.ntarget == 1) hipLaunchKernelGGL(k_probe_rows<1>, grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL(k_probe_rows<kProbeSteps>, grid, dim3(256), 0, st, a);
         MJ_CHECK(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_probe_sum, dim3((unsigned)((long)a.nrhs * a.np)), dim3(64), 0, st, a);
+    hipLaunchKernelGGL(k_probe_sum, dim3((unsigned)((long)a.ntarget * a.nrhs * a.np)), dim3(64), 0, st, a);
     MJ_CHECK(hipGetLastError());
 }
 
@@ -1475,28 +1501,63 @@ __global__ void __launch_bounds__(256) k_grad_term(EpiArg e, const double *__res
     }
 }
 
-// g_j(m) = dPhi/dJ_j(m) = 2 sum_p sum_{k=0}^{ell} K_k(r_p - r_m) E^s_p(j + k), E^s_p(n) = 0 for n > N
+// g_j(m) = dPhi/dJ_j(m) = 2 sum_p sum_{k=0}^{ell} K_k(r_p - r_m) E^s_p(j + k), E^s_p(n) = 0 for n > N, for the
+// ntarget steps j, j - 1, ... at once: the probe field is all known before the transposed march starts, and
+// each record of the table, whose reading bounds this kernel, then serves 8 steps.  As in k_probe_rows the
+// field values rotate: step j - t at slot wl reads what step j - t + 1 read at slot wl - 1.
 __global__ void __launch_bounds__(256) k_adj_source(AdjArg a)
 {
+    constexpr int T = kProbeSteps;
     const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
     const int r = blockIdx.y;
     if (i >= a.M) return;
-    double acc[3] = {0.0, 0.0, 0.0};
+    double ax[T], ay[T], az[T];
+#pragma unroll
+    for (int t = 0; t < T; t++) ax[t] = ay[t] = az[t] = 0.0;
     // the voxel-ordered copy of the table: neighbouring lanes read neighbouring records
     for (int p = 0; p < a.np; p++) {
         const int kmin = a.kmin_v[(long)p * a.M + i];
         if (kmin < 0) continue;
-        for (int wl = 0; wl < a.nw; wl++) {
-            const int jj = a.j + kmin + wl;
-            if (jj > a.N) break;
-            const double *K = a.table_v + (((long)wl * a.np + p) * a.M + i) * 6;
-            const double *E = a.Ehist + (((long)(jj - 1) * a.nrhs + r) * a.np + p) * 3;
-            acc[0] += K[0] * E[0] + K[3] * E[1] + K[4] * E[2];
-            acc[1] += K[3] * E[0] + K[1] * E[1] + K[5] * E[2];
-            acc[2] += K[4] * E[0] + K[5] * E[1] + K[2] * E[2];
+        const int j0 = a.j + kmin;   // field of step j at the first lag
+        double ex[T], ey[T], ez[T];
+        auto load = [&](int jj, double &x, double &y, double &z) __attribute__((always_inline)) {
+            const bool ok = jj >= 1 && jj <= a.N;
+            const double *E = a.Ehist + (((long)(ok ? jj - 1 : 0) * a.nrhs + r) * a.np + p) * 3;
+            const double vx = E[0], vy = E[1], vz = E[2];
+            x = ok ? vx : 0.0;
+            y = ok ? vy : 0.0;
+            z = ok ? vz : 0.0;
+        };
+#pragma unroll
+        for (int t = 0; t < T; t++) load(j0 - t, ex[t], ey[t], ez[t]);
+        for (int w0 = 0; w0 < a.nw; w0 += T) {
+            [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
+                (
+                    [&] {
+                        if (w0 + I >= a.nw) return;
+                        if (w0 + I > 0) load(j0 + w0 + I, ex[(T - I) % T], ey[(T - I) % T], ez[(T - I) % T]);
+                        const double2 *K2 = (const double2 *)(a.table_v + (((long)(w0 + I) * a.np + p) * a.M + i) * 6);
+                        const double2 v0 = K2[0], v1 = K2[1], v2 = K2[2];   // xx yy, zz xy, xz yz
+#pragma unroll
+                        for (int t = 0; t < T; t++) {
+                            const double x = ex[(t + T - I) % T], y = ey[(t + T - I) % T], z = ez[(t + T - I) % T];
+                            ax[t] = fma(v2.x, z, fma(v1.y, y, fma(v0.x, x, ax[t])));
+                            ay[t] = fma(v2.y, z, fma(v0.y, y, fma(v1.y, x, ay[t])));
+                            az[t] = fma(v1.x, z, fma(v2.y, y, fma(v2.x, x, az[t])));
+                        }
+                    }(),
+                    ...);
+            }(std::make_integer_sequence<int, T>{});
         }
     }
-    for (int c = 0; c < 3; c++) a.G[((long)r * 3 + c) * a.M + i] = 2.0 * acc[c];
+#pragma unroll
+    for (int t = 0; t < T; t++)
+        if (t < a.ntarget) {
+            double *G = a.G + ((long)t * a.nrhs + r) * 3 * a.M + i;
+            G[0] = 2.0 * ax[t];
+            G[a.M] = 2.0 * ay[t];
+            G[2 * a.M] = 2.0 * az[t];
+        }
 }
 
 __global__ void k_probe_table_by_voxel(const double *__restrict__ table, const int *__restrict__ pair_kmin,
