@@ -1595,22 +1595,38 @@ __global__ void __launch_bounds__(256) k_adj_epilogue(EpiArg e)
     const double c1 = 0.5 * e.inv_eps[i] + (e.nfir > 1 ? e.fir[1] : 0.0);
     const long Mp = (long)(e.U + 2) * (e.V + 2) * (e.W + 2);
     const long ip = ((long)(z + 1) * (e.V + 2) + (v + 1)) * (e.U + 2) + (u + 1);
+    // as in k_epilogue: three components together, eight lags in flight, each component's lags in order
+    const int kmax = min(e.nloc, e.n - 1);
+    double b[3], g[3] = {0.0, 0.0, 0.0};
+#pragma unroll
     for (int c = 0; c < 3; c++) {
         const long o = ((long)r * 3 + c) * M + i;
-        double b = e.G[o] + (e.S ? e.S[o] : 0.0);
-        for (int k = 1; k <= e.nloc; k++) {
-            if (e.n - k < 1) break;
-            const double ck = (k == 1) ? c1 : (k < e.nfir ? e.fir[k] : 0.0);
-            if (ck == 0.0) continue;
-            b -= ck * e.Lring[(((long)e.slot_of[k] * e.nrhs + r) * 3 + c) * M + i];
+        b[c] = e.G[o] + (e.S ? e.S[o] : 0.0);
+    }
+    kconst_t *fir = kconst(e.fir);
+#pragma unroll 8
+    for (int k = 1; k <= kmax; k++) {
+        const long o = ((long)e.slot_of[k] * e.nrhs + r) * 3 * M + i;
+        const double *L = e.Lring + o, *N = e.Jring + o;
+        const double ck = (k == 1) ? c1 : (k < e.nfir ? fir[k] : 0.0);
+        if (k == 1 || k < e.nfir) {
+            b[0] -= ck * L[0];
+            b[1] -= ck * L[M];
+            b[2] -= ck * L[2 * M];
         }
-        e.bq[o] = b;
+        if (k <= e.nguess) {
+            const double gk = e.gx[k - 1];
+            g[0] += gk * N[0];
+            g[1] += gk * N[M];
+            g[2] += gk * N[2 * M];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        e.bq[((long)r * 3 + c) * M + i] = b[c];
         if (chi == 0.0) continue;   // nu = 0 there, and so are the solve's entries
-        double g = 0.0;
-        for (int k = 1; k <= e.nguess; k++)
-            if (e.n - k >= 1) g += e.gx[k - 1] * e.Jring[(((long)e.slot_of[k] * e.nrhs + r) * 3 + c) * M + i];
-        e.b[((long)r * 3 + c) * Mp + ip] = chi * b;
-        e.w0[((long)r * 3 + c) * Mp + ip] = g;
+        e.b[((long)r * 3 + c) * Mp + ip] = chi * b[c];
+        e.w0[((long)r * 3 + c) * Mp + ip] = g[c];
     }
 }
 
