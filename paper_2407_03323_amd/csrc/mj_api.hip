@@ -136,8 +136,7 @@ static int gl_order(double s)
     return 9;
 }
 
-// The averaging plan of a wave with two or more non-zero direction components on voxels of
-// edges (h, hy, hz); see the fields of WaveArg.
+// The averaging plan of a wave on voxels of edges (h, hy, hz); see the fields of WaveArg.
 static void plan_wave(mj::WaveArg &w, double h, double hy, double hz)
 {
     const double kh[3] = {w.k[0] * h, w.k[1] * hy, w.k[2] * hz};
@@ -149,8 +148,49 @@ static void plan_wave(mj::WaveArg &w, double h, double hy, double hz)
         order[i] = gl_order(std::fabs(kh[ax[i]]) / w.width);
         w.nq[i] = std::min(order[i], 8);
     }
-    // an erf pair costs about what 5 exponentials do
-    w.form = order[1] > 8 ? 2 : order[0] >= 6 ? 1 : 0;
+    // the series: c_j up to well beyond what kMaxSeries terms can leave out
+    constexpr int J = 48;
+    std::vector<long double> c(J + 1, 0.0L), f(J + 1), q(J + 1);
+    c[0] = 1.0L;
+    for (int i = 0; i < 3; i++) {
+        const long double a = 0.5L * std::fabs(kh[i]) / w.width;
+        f[0] = 1.0L;
+        for (int m = 1; m <= J; m++) f[m] = f[m - 1] * a * a / ((2.0L * m) * (2.0L * m + 1.0L));
+        for (int j = 0; j <= J; j++) {
+            q[j] = 0.0L;
+            for (int m = 0; m <= j; m++) q[j] += c[m] * f[j - m];
+        }
+        c = q;
+    }
+    // terms left out, largest index first: c_j max|H_2j exp(-x^2)|
+    long double left = 0.0L;
+    int ns = J;
+    for (; ns > 0; ns--) {
+        long double root = 1.0865L;   // sqrt(2^2j (2j)!)
+        for (int i = 1; i <= 2 * ns; i++) root *= std::sqrt(2.0L * i);
+        if (left + c[ns] * root > std::ldexp(1.0L, -53)) break;
+        left += c[ns] * root;
+    }
+    if (ns <= mj::kMaxSeries) {
+        // sum_j c_j H_2j(x) as a polynomial in x^2, H_{n+1} = 2 x H_n - 2 n H_{n-1}
+        std::vector<long double> poly(ns + 1, 0.0L), h0(2 * ns + 2, 0.0L), h1(2 * ns + 2, 0.0L);
+        h0[0] = 1.0L;
+        h1[1] = 2.0L;
+        for (int n = 0; n <= 2 * ns; n++) {   // h0 = H_n, h1 = H_{n+1}
+            if (n % 2 == 0)
+                for (int i = 0; i <= n; i += 2) poly[i / 2] += c[n / 2] * h0[i];
+            std::vector<long double> h2(2 * ns + 2, 0.0L);
+            for (int i = 0; i + 1 < 2 * ns + 2; i++) h2[i + 1] = 2.0L * h1[i];
+            for (int i = 0; i < 2 * ns + 2; i++) h2[i] -= 2.0L * (n + 1) * h0[i];
+            h0 = h1;
+            h1 = h2;
+        }
+        w.form = 3;
+        w.ns = ns;
+        for (int i = 0; i <= ns; i++) w.ser[i] = (double)poly[i];
+        return;
+    }
+    w.form = (kh[0] != 0.0) + (kh[1] != 0.0) + (kh[2] != 0.0) < 2 ? 0 : order[1] > 8 ? 2 : 1;
 }
 
 struct mj_solver {
@@ -1038,8 +1078,9 @@ mj::EpiArg mj_solver::epi_arg() const
 {
     mj::EpiArg e{};
     e.k0 = k0_d;
+    e.series = 1;
     for (const mj::WaveArg &w : waves)
-        if ((w.k[0] != 0.0) + (w.k[1] != 0.0) + (w.k[2] != 0.0) >= 2) e.oblique = 1;
+        if (w.form != 3) e.series = 0;
     e.M = M;
     e.U = U;
     e.V = V;

@@ -35,17 +35,22 @@ struct BlockMacArg {
                                // dropped); its lag loop then starts at nb - jmax
 };
 
+constexpr int kMaxSeries = 16;   // highest power of x^2 in a wave's series
+
 struct WaveArg {
     double k[3], pol[3], rref[3];
     double width, ct0, amp;
-    // How the voxel average of a wave with two or more non-zero direction components is taken
-    // (set by the host from the spreads |k_i| h_i / width): the axes by decreasing spread enter
-    // as their products k_i h_i, each with the Gauss-Legendre order that bounds its error by 2^-53
-    // of the amplitude, and form 0 takes the rule on all three, 1 erf on the widest and the rule
-    // on the other two, 2 the two widest in closed form and the rule on the third.
+    // How the voxel average is taken (set by the host from the spreads |k_i| h_i / width): form 3 a series in
+    // the Gaussian's derivatives, coefficients ser[0 .. ns] of the polynomial in x^2 that multiplies
+    // exp(-x^2); else, with two or more non-zero direction components, the axes by decreasing spread enter as
+    // their products k_i h_i, and form 1 takes erf on the widest and a Gauss-Legendre rule of nq points on
+    // the other two, 2 the two widest in closed form and the rule on the third; form 0 is the 8-point rule
+    // along the one axis of the wave.
     double kh[3];
     int nq[3];
     int form;
+    int ns;
+    double ser[kMaxSeries + 1];
 };
 
 struct EpiArg {
@@ -73,7 +78,7 @@ struct EpiArg {
     const double *G;         // adjoint source g_j [nrhs][3][M]
     double *bq;              // b'_j, kept for the voxels with chi = 0 [nrhs][3][M]
     const double *k0;        // the solver's K_0 stencil (the gradient term B_n)
-    int oblique;             // some wave has two or more non-zero direction components
+    int series;              // every wave takes its average by the series (form 3)
 };
 
 // Adjoint of the probe objective and the eps-gradient (see mj_march.hip).

@@ -576,37 +576,53 @@ typedef __attribute__((address_space(4))) const double kconst_t;
 __device__ inline kconst_t *kconst(const double *p) { return (kconst_t *)p; }
 
 // chi_m times the voxel average of a Gaussian plane wave at c t = n c dt (eq:E).  The average
-// over an axis the wave does not depend on is the identity.  A wave along one axis takes the
-// 8-point Gauss-Legendre rule on it.  A wave with two or three non-zero components follows the
-// plan the host made from its spreads s_i = |k_i| h_i / w (w the pulse width):
-//  * form 0: on each axis the n-point rule with the least n whose remainder bound
-//    (n!)^4 / ((2n + 1) ((2n)!)^3) s^2n max|d^2n/dx^2n exp(-x^2)| (the Gauss-Legendre remainder,
-//    the derivative bounded by Cramer's inequality) stays below 2^-53; at 64^3 with a width of
-//    8.5 voxels that is 4 or 5 points an axis where the oracle's rule takes 8;
-//  * form 1, once the widest axis would need 6 points or more: that axis in closed form,
+// over an axis the wave does not depend on is the identity.  With x = T / w (T the retarded distance of the
+// voxel's centre, w the pulse width) and d the voxel's own spread in units of w, a sum of independent
+// uniform variables of widths s_i = |k_i| h_i / w, the average of exp(-(x + d)^2) is
+//   exp(-x^2) sum_j c_j H_2j(x),   sum_j c_j t^2j = prod_i sinh(s_i t / 2) / (s_i t / 2),
+// since the 2j-th derivative of exp(-x^2) is H_2j(x) exp(-x^2) and c_j is the 2j-th moment of d over (2j)!.
+// The host makes a plan for each wave:
+//  * form 3: that series, cut where the terms left out stay below 2^-53 by Cramer's inequality
+//    (|H_m(x)| exp(-x^2 / 2) <= 1.0865 sqrt(2^m m!)) and written as one polynomial in x^2, whose coefficients
+//    are all positive where at most kMaxSeries are needed (spreads up to 0.7 on three axes, 1.7 on one; a
+//    width of 8.5 voxels takes 6 terms): one exponential a voxel, within 2e-16 of the peak of the 60-digit
+//    average, where the rule on three axes took 64 to 125 of them;
+//  * form 1, beyond it: the widest axis in closed form,
 //    (w sqrt(pi) / (2 k_a h_a)) (erf((T + k_a h_a / 2) / w) - erf((T - k_a h_a / 2) / w)), through
-//    erfc where both arguments lie in one tail, and the rule on the other two;
+//    erfc where both arguments lie in one tail, and on the other two the Gauss-Legendre rule with the least
+//    n whose remainder bound (n!)^4 / ((2n + 1) ((2n)!)^3) s^2n max|d^2n/dx^2n exp(-x^2)| stays below 2^-53;
 //  * form 2, once the second widest spread is beyond what the 8-point rule integrates to 2^-53
 //    (pulses narrower than about 1.4 voxels): the two widest axes in closed form.  With
 //    c_a = k_a h_a / (2w), c_b likewise and t = T / w, their average is (sqrt(pi) / (8 c_a c_b))
 //    times the second difference G(t + c_b + c_a) - G(t + c_b - c_a) - G(t - c_b + c_a)
 //    + G(t - c_b - c_a) of G(z) = z erf(z) + exp(-z^2) / sqrt(pi) = |z| + ierfc(|z|), the
-//    antiderivative of erf, where ierfc(x) = exp(-x^2) / sqrt(pi) - x erfc(x).
-// Each form is within a few units in the last place of the exact average wherever the oracle's
-// 8-point rule is too, and more exact where the rule is not.  CF = false leaves the plan out of
-// the kernel (its registers slow the right-hand side when every wave runs along an axis); a
-// launch takes CF = true whenever one of its waves does not, and a wave along an axis takes the
-// same 8-point rule either way.
-template <bool CF>
-__device__ inline double wave_average(const WaveArg &w, const EpiArg &e, int u, int v, int z, double ct)
+//    antiderivative of erf, where ierfc(x) = exp(-x^2) / sqrt(pi) - x erfc(x);
+//  * form 0: a wave along one axis beyond the series takes the 8-point rule on it.
+// Launches whose waves all take the series have their own build of the right-hand side, which leaves the
+// other forms' registers out: eight oblique waves at 64^3 184 us against 267, one 25 against 45, three at 21 x 13 x 9
+// 7 against 23.
+__device__ inline double wave_series(const WaveArg *w, const EpiArg &e, int u, int v, int z, double ct)
 {
+    kconst_t *k = kconst(w->k), *rr = kconst(w->rref), *ser = kconst(w->ser);
+    const double tc = ct - *kconst(&w->ct0) - ((u + 0.5) * e.h - rr[0]) * k[0] - ((v + 0.5) * e.hy - rr[1]) * k[1] -
+                      ((z + 0.5) * e.hz - rr[2]) * k[2];
+    const double x = tc / *kconst(&w->width), x2 = x * x;
+    if (x2 > 800.0) return 0.0;   // exp underflows
+    double s = 0.0;
+    for (int i = *(__attribute__((address_space(4))) const int *)&w->ns; i >= 0; i--) s = fma(s, x2, ser[i]);
+    return *kconst(&w->amp) * exp(-x2) * s;
+}
+
+__device__ inline double wave_average(const WaveArg *wp, const EpiArg &e, int u, int v, int z, double ct)
+{
+    if (wp->form == 3) return wave_series(wp, e, u, v, z, ct);
+    const WaveArg w = *wp;
     const double tc = ct - w.ct0 - ((u + 0.5) * e.h - w.rref[0]) * w.k[0] - ((v + 0.5) * e.hy - w.rref[1]) * w.k[1] -
                       ((z + 0.5) * e.hz - w.rref[2]) * w.k[2];
     const double iw = 1.0 / w.width;
-    if (CF && (w.k[0] != 0.0) + (w.k[1] != 0.0) + (w.k[2] != 0.0) >= 2) {
-        kconst_t *ga = kconst(e.gl) + 16 * w.nq[0], *gb = kconst(e.gl) + 16 * w.nq[1];
-        kconst_t *gc = kconst(e.gl) + 16 * w.nq[2];
-        const int na = w.nq[0], nb = w.nq[1], nc = w.nq[2];
+    if (w.form != 0) {
+        kconst_t *gb = kconst(e.gl) + 16 * w.nq[1], *gc = kconst(e.gl) + 16 * w.nq[2];
+        const int nb = w.nq[1], nc = w.nq[2];
         if (w.form == 2) {
             const double ca = 0.5 * w.kh[0] * iw, cb = 0.5 * w.kh[1] * iw;
             double sum = 0.0;
@@ -624,39 +640,23 @@ __device__ inline double wave_average(const WaveArg &w, const EpiArg &e, int u, 
             }
             return w.amp * sum * (0.2215567313631895 / (ca * cb));   // sqrt(pi) / 8
         }
-        if (w.form == 1) {
-            const double half = 0.5 * w.kh[0];
-            double sum = 0.0;
-            for (int i = 0; i < nb; i++) {
-                const double o1 = gb[i] * w.kh[1];
-                double sl = 0.0;
-                for (int j = 0; j < nc; j++) {
-                    const double T = tc - o1 - gc[j] * w.kh[2];
-                    const double u1 = (T + half) * iw, u2 = (T - half) * iw;
-                    // erf(u1) - erf(u2), through erfc where both lie in one tail
-                    const double d = (u1 > 0.0 && u2 > 0.0)   ? erfc(u2) - erfc(u1)
-                                     : (u1 < 0.0 && u2 < 0.0) ? erfc(-u1) - erfc(-u2)
-                                                              : erf(u1) - erf(u2);
-                    sl += gc[8 + j] * d;
-                }
-                sum += gb[8 + i] * sl;
-            }
-            return w.amp * sum * (0.8862269254527580 * w.width / w.kh[0]);   // sqrt(pi) / 2
-        }
+        const double half = 0.5 * w.kh[0];
         double sum = 0.0;
-        for (int i = 0; i < na; i++) {
-            const double o0 = ga[i] * w.kh[0];
-            for (int j = 0; j < nb; j++) {
-                const double o1 = o0 + gb[j] * w.kh[1];
-                double sl = 0.0;
-                for (int l = 0; l < nc; l++) {
-                    const double x = (tc - o1 - gc[l] * w.kh[2]) * iw;
-                    sl += gc[8 + l] * exp(-x * x);
-                }
-                sum += ga[8 + i] * gb[8 + j] * sl;
+        for (int i = 0; i < nb; i++) {
+            const double o1 = gb[i] * w.kh[1];
+            double sl = 0.0;
+            for (int j = 0; j < nc; j++) {
+                const double T = tc - o1 - gc[j] * w.kh[2];
+                const double u1 = (T + half) * iw, u2 = (T - half) * iw;
+                // erf(u1) - erf(u2), through erfc where both lie in one tail
+                const double d = (u1 > 0.0 && u2 > 0.0)   ? erfc(u2) - erfc(u1)
+                                 : (u1 < 0.0 && u2 < 0.0) ? erfc(-u1) - erfc(-u2)
+                                                          : erf(u1) - erf(u2);
+                sl += gc[8 + j] * d;
             }
+            sum += gb[8 + i] * sl;
         }
-        return w.amp * sum;
+        return w.amp * sum * (0.8862269254527580 * w.width / w.kh[0]);   // sqrt(pi) / 2
     }
     const int nx = w.k[0] != 0.0 ? 8 : 1, ny = w.k[1] != 0.0 ? 8 : 1, nz = w.k[2] != 0.0 ? 8 : 1;
     double sum = 0.0;
@@ -681,7 +681,7 @@ __device__ inline double wave_average(const WaveArg &w, const EpiArg &e, int u, 
 // sum_{k=1}^{nguess} gx_k J_{n-k} that the Z_0 solve starts from, both in the zero-haloed layout.
 // Voxels with chi = 0 are skipped: their current is zero, and so are their entries of the solve's
 // vectors (cleared whenever eps changes).
-template <bool CF>
+template <bool SERIES>
 __global__ void __launch_bounds__(256) k_epilogue(EpiArg e)
 {
     const long M = e.M;
@@ -693,8 +693,8 @@ __global__ void __launch_bounds__(256) k_epilogue(EpiArg e)
     const int u = (int)(i % e.U), v = (int)((i / e.U) % e.V), z = (int)(i / ((long)e.U * e.V));
     const long Mp = (long)(e.U + 2) * (e.V + 2) * (e.W + 2);
     const long ip = ((long)(z + 1) * (e.V + 2) + (v + 1)) * (e.U + 2) + (u + 1);
-    const WaveArg w = e.waves[r];
-    const double avg = wave_average<CF>(w, e, u, v, z, e.n * e.c_dt);
+    const WaveArg *w = e.waves + r;
+    const double avg = SERIES ? wave_series(w, e, u, v, z, e.n * e.c_dt) : wave_average(w, e, u, v, z, e.n * e.c_dt);
     const double c1 = 0.5 * e.inv_eps[i] + (e.nfir > 1 ? e.fir[1] : 0.0);
     const int kmax = min(e.nloc, e.n - 1);   // lags with a past current
     // initial guess of the Z_0 solve: the polynomial through the last nguess solutions,
@@ -705,7 +705,7 @@ __global__ void __launch_bounds__(256) k_epilogue(EpiArg e)
 #pragma unroll
     for (int c = 0; c < 3; c++) {
         const long o = ((long)r * 3 + c) * M + i;
-        b[c] = chi * (avg * w.pol[c] + (e.S ? e.S[o] : 0.0));
+        b[c] = chi * (avg * kconst(w->pol)[c] + (e.S ? e.S[o] : 0.0));
     }
     kconst_t *fir = kconst(e.fir);
 #pragma unroll 8
@@ -734,7 +734,7 @@ __global__ void __launch_bounds__(256) k_epilogue(EpiArg e)
 void launch_epilogue(const EpiArg &e, hipStream_t st)
 {
     dim3 grd((unsigned)((e.M + 255) / 256), e.nrhs);
-    if (e.oblique) hipLaunchKernelGGL(k_epilogue<true>, grd, dim3(256), 0, st, e);
+    if (e.series) hipLaunchKernelGGL(k_epilogue<true>, grd, dim3(256), 0, st, e);
     else hipLaunchKernelGGL(k_epilogue<false>, grd, dim3(256), 0, st, e);
     MJ_CHECK(hipGetLastError());
 }
@@ -1488,13 +1488,13 @@ __global__ void __launch_bounds__(256) k_grad_term(EpiArg e, const double *__res
     const int r = blockIdx.y;
     if (i >= M) return;
     const int u = (int)(i % e.U), v = (int)((i / e.U) % e.V), w = (int)(i / ((long)e.U * e.V));
-    const WaveArg wa = e.waves[r];
-    const double avg = wave_average<true>(wa, e, u, v, w, e.n * e.c_dt);
+    const WaveArg *wa = e.waves + r;
+    const double avg = wave_average(wa, e, u, v, w, e.n * e.c_dt);
     double k0[3];
     stencil_plain(e.k0, Jn + (long)r * 3 * M, M, e.U, e.V, e.W, u, v, w, k0);
     for (int c = 0; c < 3; c++) {
         const long o = ((long)r * 3 + c) * M + i;
-        double b = avg * wa.pol[c] + 0.5 * Jn[o] + k0[c];   // T(0) = T(dt) = 1/2, T(k dt) = 0 for k >= 2
+        double b = avg * wa->pol[c] + 0.5 * Jn[o] + k0[c];   // T(0) = T(dt) = 1/2, T(k dt) = 0 for k >= 2
         if (Jn1) b += 0.5 * Jn1[o];
         if (e.S) b += e.S[o];
         Bout[o] = b;
