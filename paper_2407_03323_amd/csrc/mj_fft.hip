@@ -6,7 +6,8 @@
 // multiplied point-wise in the spectral domain and transformed back; only the
 // box part of the inverse is kept.
 //
-// Each 1-D pass loads a tile of pencils into LDS, runs a Stockham autosort FFT
+// Lengths that split into two factors of at most 16 are transformed in registers with one exchange
+// through LDS (k_fft2_*).  For the others, each 1-D pass loads a tile of pencils into LDS, runs a Stockham autosort FFT
 // (decimation in time, natural-order output) stage by stage in place (each stage
 // reads its butterflies into registers, synchronises, writes them back), and
 // writes the tile back.  Pencils along y and z are strided in
@@ -377,6 +378,313 @@ __global__ void __launch_bounds__(kThreads) k_fft_strided(const double2 *__restr
     }
 }
 
+
+// ---------------------------------------------------------------------------- two-radix strided pass
+// The strided passes of a length N = R1 R2 with both factors at most 16 keep a butterfly of 16 points a thread
+// in registers and exchange once: a thread loads the R1 points j + r R2 of its pencil straight from memory,
+// transforms them, leaves them in LDS at j R1 + q, and after one barrier takes the R2 points j + r R1,
+// twiddles, transforms and stores j + q R1.  The stage-by-stage kernel below moves every point through LDS
+// once for the load, once per stage (three or four) and once for the store, with a barrier each time, and that,
+// not its arithmetic, kept it at 3 TB/s.  Neighbouring lanes hold neighbouring pencils, so every
+// access of memory and LDS is a run of the pencils' values.  The inverse is the forward transform with real
+// and imaginary parts traded at the load and the store.
+// Per pass, before and after: 104^3 77 -> 50 us, 64^3 26.3 -> 13.3, eight right-hand sides at 64^3 149 -> 90,
+// 80^3 53 -> 24, 48^3 20.3 -> 8.6, 32^3 8.1 -> 4.8 (mean of the y and z passes, both directions).
+
+// cos(2 pi m / R), sin(2 pi m / R)
+template <int R>
+struct Roots;
+template <>
+struct Roots<6> {
+    static constexpr double c[6] = {
+        1.0, 0.5, -0.5, -1.0, -0.5, 0.5};
+    static constexpr double s[6] = {
+        0.0, 0.8660254037844386, 0.8660254037844386, 0.0, -0.8660254037844386, -0.8660254037844386};
+};
+template <>
+struct Roots<8> {
+    static constexpr double c[8] = {
+        1.0, 0.7071067811865476, 0.0, -0.7071067811865476, -1.0, -0.7071067811865476, 0.0,
+        0.7071067811865476};
+    static constexpr double s[8] = {
+        0.0, 0.7071067811865476, 1.0, 0.7071067811865476, 0.0, -0.7071067811865476, -1.0,
+        -0.7071067811865476};
+};
+template <>
+struct Roots<9> {
+    static constexpr double c[9] = {
+        1.0, 0.766044443118978, 0.17364817766693036, -0.5, -0.9396926207859084, -0.9396926207859084,
+        -0.5, 0.17364817766693036, 0.766044443118978};
+    static constexpr double s[9] = {
+        0.0, 0.6427876096865394, 0.984807753012208, 0.8660254037844386, 0.3420201433256687,
+        -0.3420201433256687, -0.8660254037844386, -0.984807753012208, -0.6427876096865394};
+};
+template <>
+struct Roots<10> {
+    static constexpr double c[10] = {
+        1.0, 0.8090169943749475, 0.30901699437494745, -0.30901699437494745, -0.8090169943749475, -1.0,
+        -0.8090169943749475, -0.30901699437494745, 0.30901699437494745, 0.8090169943749475};
+    static constexpr double s[10] = {
+        0.0, 0.5877852522924731, 0.9510565162951535, 0.9510565162951535, 0.5877852522924731, 0.0,
+        -0.5877852522924731, -0.9510565162951535, -0.9510565162951535, -0.5877852522924731};
+};
+template <>
+struct Roots<12> {
+    static constexpr double c[12] = {
+        1.0, 0.8660254037844386, 0.5, 0.0, -0.5, -0.8660254037844386, -1.0, -0.8660254037844386, -0.5,
+        0.0, 0.5, 0.8660254037844386};
+    static constexpr double s[12] = {
+        0.0, 0.5, 0.8660254037844386, 1.0, 0.8660254037844386, 0.5, 0.0, -0.5, -0.8660254037844386,
+        -1.0, -0.8660254037844386, -0.5};
+};
+template <>
+struct Roots<14> {
+    static constexpr double c[14] = {
+        1.0, 0.9009688679024191, 0.6234898018587335, 0.2225209339563144, -0.2225209339563144,
+        -0.6234898018587335, -0.9009688679024191, -1.0, -0.9009688679024191, -0.6234898018587335,
+        -0.2225209339563144, 0.2225209339563144, 0.6234898018587335, 0.9009688679024191};
+    static constexpr double s[14] = {
+        0.0, 0.4338837391175581, 0.7818314824680298, 0.9749279121818236, 0.9749279121818236,
+        0.7818314824680298, 0.4338837391175581, 0.0, -0.4338837391175581, -0.7818314824680298,
+        -0.9749279121818236, -0.9749279121818236, -0.7818314824680298, -0.4338837391175581};
+};
+template <>
+struct Roots<15> {
+    static constexpr double c[15] = {
+        1.0, 0.9135454576426009, 0.6691306063588582, 0.30901699437494745, -0.10452846326765347, -0.5,
+        -0.8090169943749475, -0.9781476007338057, -0.9781476007338057, -0.8090169943749475, -0.5,
+        -0.10452846326765347, 0.30901699437494745, 0.6691306063588582, 0.9135454576426009};
+    static constexpr double s[15] = {
+        0.0, 0.4067366430758002, 0.7431448254773942, 0.9510565162951535, 0.9945218953682733,
+        0.8660254037844386, 0.5877852522924731, 0.20791169081775934, -0.20791169081775934,
+        -0.5877852522924731, -0.8660254037844386, -0.9945218953682733, -0.9510565162951535,
+        -0.7431448254773942, -0.4067366430758002};
+};
+template <>
+struct Roots<16> {
+    static constexpr double c[16] = {
+        1.0, 0.9238795325112867, 0.7071067811865476, 0.3826834323650898, 0.0, -0.3826834323650898,
+        -0.7071067811865476, -0.9238795325112867, -1.0, -0.9238795325112867, -0.7071067811865476,
+        -0.3826834323650898, 0.0, 0.3826834323650898, 0.7071067811865476, 0.9238795325112867};
+    static constexpr double s[16] = {
+        0.0, 0.3826834323650898, 0.7071067811865476, 0.9238795325112867, 1.0, 0.9238795325112867,
+        0.7071067811865476, 0.3826834323650898, 0.0, -0.3826834323650898, -0.7071067811865476,
+        -0.9238795325112867, -1.0, -0.9238795325112867, -0.7071067811865476, -0.3826834323650898};
+};
+
+constexpr bool fft_prime(int R) { return R == 2 || R == 3 || R == 4 || R == 5 || R == 7 || R == 11 || R == 13; }
+constexpr int fft_split(int R)   // first factor of a composite register transform
+{
+    return R == 6 ? 2 : R == 8 ? 2 : R == 9 ? 3 : R == 10 ? 2 : R == 12 ? 4 : R == 14 ? 2 : R == 15 ? 3 : 4;
+}
+
+// In-register forward transform of R points (2 <= R <= 16), v[q] <- sum_t v[t] W_R^{q t}
+template <int R>
+__device__ __attribute__((always_inline)) inline void dft_reg(double2 (&v)[R])
+{
+    if constexpr (fft_prime(R)) {
+        dft_small<R>(v, nullptr, R, false);
+    } else {
+        constexpr int A = fft_split(R), B = R / A;
+        double2 u[R];
+#pragma unroll
+        for (int b = 0; b < B; b++) {
+            double2 x[A];
+#pragma unroll
+            for (int a = 0; a < A; a++) x[a] = v[a * B + b];
+            dft_reg<A>(x);
+#pragma unroll
+            for (int a = 0; a < A; a++) {
+                const int m = a * b % R;
+                u[a * B + b] = m == 0 ? x[a] : cmul(x[a], make_double2(Roots<R>::c[m], -Roots<R>::s[m]));
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < A; a++) {
+            double2 x[B];
+#pragma unroll
+            for (int b = 0; b < B; b++) x[b] = u[a * B + b];
+            dft_reg<B>(x);
+#pragma unroll
+            for (int b = 0; b < B; b++) v[a + A * b] = x[b];
+        }
+    }
+}
+
+template <int R1, int R2>
+__global__ void __launch_bounds__(kThreads) k_fft2_strided(const double2 *__restrict__ in, double2 *__restrict__ out,
+                                                           StridedArg g, const double2 *tw, int P, int inv)
+{
+    constexpr int N = R1 * R2;
+    extern __shared__ double2 sm[];
+    double2 *tw_s = sm, *buf = sm + N;
+    load_twiddles(tw_s, tw, N);
+    const int ntile = (g.Hx + P - 1) / P;
+    const int lb = (int)xcd_block(blockIdx.x, gridDim.x);   // neighbouring tiles share row ends
+    const int tile = lb % ntile;
+    const int grp = lb / ntile;
+    const int c = grp / g.nq, qi = grp - c * g.nq;
+    const int kx0 = tile * P;
+    const FastDiv fP(P);
+    const int b = threadIdx.x, j = fP.div(b), p = b - j * P;
+    const bool live = kx0 + p < g.Hx;
+    if (j < R2) {
+        const double2 *src = in + c * g.cs_in + qi * g.qs_in + kx0 + p;
+        double2 v[R1];
+#pragma unroll
+        for (int r = 0; r < R1; r++) {
+            const int n = j + r * R2;
+            v[r] = live && n < g.n_in ? src[(long)n * g.es_in] : make_double2(0.0, 0.0);
+        }
+        if (inv)
+#pragma unroll
+            for (int r = 0; r < R1; r++) v[r] = make_double2(v[r].y, v[r].x);
+        dft_reg<R1>(v);
+#pragma unroll
+        for (int q = 0; q < R1; q++) buf[(j * R1 + q) * P + p] = v[q];
+    }
+    __syncthreads();
+    if (j < R1) {
+        double2 v[R2];
+#pragma unroll
+        for (int r = 0; r < R2; r++) v[r] = buf[b + r * (R1 * P)];   // point j + r R1
+#pragma unroll
+        for (int r = 1; r < R2; r++) v[r] = cmul(v[r], tw_s[j * r]);
+        dft_reg<R2>(v);
+        if (inv)
+#pragma unroll
+            for (int r = 0; r < R2; r++) v[r] = make_double2(v[r].y, v[r].x);
+        double2 *dst = out + c * g.cs_out + qi * g.qs_out + kx0 + p;
+#pragma unroll
+        for (int q = 0; q < R2; q++) {
+            const int n = j + q * R1;
+            if (live && n < g.n_out) dst[(long)n * g.es_out] = v[q];
+        }
+    }
+}
+
+// The x passes in the same way, two real rows a pencil.  Neighbouring lanes hold neighbouring points of a
+// row (runs of R2 reals at the load, of R1 at the inverse's store); in LDS a pencil's rows of R1 points are
+// one value longer when R1 is even, so that the lanes' writes, R1 values apart, spread over the banks.
+template <int R1, int R2>
+struct XTile {
+    static constexpr int N = R1 * R2, row = R1 + (R1 % 2 == 0 ? 1 : 0), ld = R2 * row;
+};
+
+template <int R1, int R2>
+__global__ void __launch_bounds__(kThreads) k_fft2_x_fwd(const double *__restrict__ x, double2 *__restrict__ X,
+                                                         int nrows, int U, int Hx, int Hp, const double2 *tw, int P)
+{
+    using T = XTile<R1, R2>;
+    constexpr int N = T::N;
+    extern __shared__ double2 sm[];
+    double2 *tw_s = sm, *buf = sm + N;
+    load_twiddles(tw_s, tw, N);
+    const int row0 = (int)xcd_block(blockIdx.x, gridDim.x) * (2 * P);
+    const int b = threadIdx.x;
+    {
+        const int p = b / R2, j = b % R2, ra = row0 + 2 * p;
+        if (p < P) {
+            const double *xa = x + (size_t)ra * U, *xb = xa + U;
+            double2 v[R1];
+#pragma unroll
+            for (int r = 0; r < R1; r++) {
+                const int n = j + r * R2;
+                v[r] = make_double2(n < U && ra < nrows ? xa[n] : 0.0, n < U && ra + 1 < nrows ? xb[n] : 0.0);
+            }
+            dft_reg<R1>(v);
+#pragma unroll
+            for (int q = 0; q < R1; q++) buf[p * T::ld + j * T::row + q] = v[q];
+        }
+    }
+    __syncthreads();
+    const int p = b / R1, j = b % R1;
+    double2 v[R2];
+    if (p < P) {
+#pragma unroll
+        for (int r = 0; r < R2; r++) v[r] = buf[p * T::ld + r * T::row + j];   // point j + r R1
+#pragma unroll
+        for (int r = 1; r < R2; r++) v[r] = cmul(v[r], tw_s[j * r]);
+        dft_reg<R2>(v);
+    }
+    __syncthreads();
+    if (p < P)
+#pragma unroll
+        for (int q = 0; q < R2; q++) buf[p * T::ld + j + q * R1] = v[q];
+    __syncthreads();
+    // separate: Xa[k] = (Z[k] + conj Z[N-k]) / 2, Xb[k] = (Z[k] - conj Z[N-k]) / (2i)
+    const FastDiv fH(Hx);
+    for (int i = threadIdx.x; i < 2 * P * Hx; i += blockDim.x) {
+        const int rr = fH.div(i), k = i - rr * Hx, row = row0 + rr;
+        if (row >= nrows) continue;
+        const double2 *Z = buf + (rr >> 1) * T::ld;
+        const double2 z1 = Z[k], z2 = Z[k == 0 ? 0 : N - k];
+        X[(size_t)row * Hp + k] = (rr & 1) ? make_double2(0.5 * (z1.y + z2.y), -0.5 * (z1.x - z2.x))
+                                           : make_double2(0.5 * (z1.x + z2.x), 0.5 * (z1.y - z2.y));
+    }
+}
+
+template <int R1, int R2>
+__global__ void __launch_bounds__(kThreads) k_fft2_x_inv(const double2 *__restrict__ X, double *__restrict__ y,
+                                                         int nrows, int U, int Hx, int Hp, const double2 *tw, int P)
+{
+    using T = XTile<R1, R2>;
+    constexpr int N = T::N;
+    extern __shared__ double2 sm[];
+    double2 *tw_s = sm, *buf = sm + N;
+    load_twiddles(tw_s, tw, N);
+    const int row0 = (int)xcd_block(blockIdx.x, gridDim.x) * (2 * P);
+    const int b = threadIdx.x;
+    {
+        const int p = b / R2, j = b % R2, ra = row0 + 2 * p;
+        if (p < P) {
+            const double2 *Xa = X + (size_t)ra * Hp, *Xb = Xa + Hp;
+            double2 v[R1];
+            // Z[k] = Xa[k] + i Xb[k] for k <= N/2, Z[N-k] = conj(Xa[k]) + i conj(Xb[k]) for 0 < k < N/2, with
+            // real and imaginary parts traded
+#pragma unroll
+            for (int r = 0; r < R1; r++) {
+                const int n = j + r * R2, k = n <= N / 2 ? n : N - n;
+                const double2 xa = ra < nrows ? Xa[k] : make_double2(0.0, 0.0);
+                const double2 xb = ra + 1 < nrows ? Xb[k] : make_double2(0.0, 0.0);
+                const double sg = n <= N / 2 ? 1.0 : -1.0;
+                v[r] = make_double2(fma(sg, xa.y, xb.x), fma(-sg, xb.y, xa.x));
+            }
+            dft_reg<R1>(v);
+#pragma unroll
+            for (int q = 0; q < R1; q++) buf[p * T::ld + j * T::row + q] = v[q];
+        }
+    }
+    __syncthreads();
+    const int p = b / R1, j = b % R1, ra = row0 + 2 * p;
+    if (p < P) {
+        double2 v[R2];
+#pragma unroll
+        for (int r = 0; r < R2; r++) v[r] = buf[p * T::ld + r * T::row + j];
+#pragma unroll
+        for (int r = 1; r < R2; r++) v[r] = cmul(v[r], tw_s[j * r]);
+        dft_reg<R2>(v);
+        double *ya = y + (size_t)ra * U, *yb = ya + U;
+#pragma unroll
+        for (int q = 0; q < R2; q++) {
+            const int n = j + q * R1;
+            if (n < U && ra < nrows) ya[n] = v[q].y;
+            if (n < U && ra + 1 < nrows) yb[n] = v[q].x;
+        }
+    }
+}
+
+// The lengths with a two-radix pass: every even product of 2, 3, 5, 7, 11 and 13 from 32 to 256 that
+// splits so, with the factors as near each other as they go, the larger one first.
+#define MJ_FFT2_SIZES(X) \
+    X(32, 8, 4) X(36, 6, 6) X(40, 8, 5) X(42, 7, 6) X(44, 11, 4) X(48, 8, 6) X(50, 10, 5) \
+    X(52, 13, 4) X(54, 9, 6) X(56, 8, 7) X(60, 10, 6) X(64, 8, 8) X(66, 11, 6) X(70, 10, 7) \
+    X(72, 9, 8) X(78, 13, 6) X(80, 10, 8) X(84, 12, 7) X(88, 11, 8) X(90, 10, 9) X(96, 12, 8) \
+    X(98, 14, 7) X(100, 10, 10) X(104, 13, 8) X(108, 12, 9) X(110, 11, 10) X(112, 14, 8) X(120, 12, 10) \
+    X(126, 14, 9) X(128, 16, 8) X(130, 13, 10) X(132, 12, 11) X(140, 14, 10) X(144, 12, 12) X(150, 15, 10) \
+    X(154, 14, 11) X(156, 13, 12) X(160, 16, 10) X(168, 14, 12) X(176, 16, 11) X(180, 15, 12) X(182, 14, 13) \
+    X(192, 16, 12) X(196, 14, 14) X(208, 16, 13) X(210, 15, 14) X(224, 16, 14) X(240, 16, 15) X(256, 16, 16)
+
 PlanArg plan_arg(const FftPlan1D &p)
 {
     PlanArg a{};
@@ -480,9 +788,9 @@ void fft3d_free(Fft3D &f)
     f.bufA = f.bufB = nullptr;
 }
 
-// Radix set of a plan, and the kernel instance that serves it: the sets of the usual padded
-// sizes (208 = 13 4 4; powers of two; 3 2^k) have their own instances, any other plan the
-// generic one.
+// Radix set of a plan, and the stage-by-stage kernel instance that serves it where no two-radix pass does
+// (lengths below 32 and above 256, and those with a factor that does not split): powers of two and 3 2^k
+// have their own instances, any other plan the generic one.
 static int plan_mask(const FftPlan1D &p)
 {
     int m = 0;
@@ -503,7 +811,6 @@ static int plan_mask(const FftPlan1D &p)
 #define MJ_FFT_DISPATCH(mask, KERNEL, ...)                                                        \
     do {                                                                                          \
         switch (mask) {                                                                           \
-        case kR4 | kR13: hipLaunchKernelGGL(KERNEL<kR4 | kR13>, __VA_ARGS__); break;              \
         case kR4: hipLaunchKernelGGL(KERNEL<kR4>, __VA_ARGS__); break;                            \
         case kR2 | kR4: hipLaunchKernelGGL(KERNEL<kR2 | kR4>, __VA_ARGS__); break;                \
         case kR3 | kR4: hipLaunchKernelGGL(KERNEL<kR3 | kR4>, __VA_ARGS__); break;                \
@@ -512,11 +819,26 @@ static int plan_mask(const FftPlan1D &p)
         }                                                                                         \
     } while (0)
 
+// threads of a two-radix pass: P pencils (P <= 16) of at most 16 butterflies, in whole waves
+static dim3 two_radix_threads(int P, int R1, int R2) { return dim3((unsigned)((P * std::max(R1, R2) + 63) / 64 * 64)); }
+
 static void launch_strided(const double2 *in, double2 *out, const StridedArg &g, int ncomp, const FftPlan1D &p,
                            int P, bool inv, hipStream_t st)
 {
     int ntile = (g.Hx + P - 1) / P;
     dim3 grid(ncomp * g.nq * ntile);
+    const size_t lds2 = sizeof(double2) * (size_t)p.N * (P + 1);
+    switch (p.N) {
+#define X(N, R1, R2)                                                                                          \
+    case N:                                                                                                   \
+        hipLaunchKernelGGL((k_fft2_strided<R1, R2>), grid, two_radix_threads(P, R1, R2), lds2, st, in, out, g, \
+                           p.tw, P, inv ? 1 : 0);                                                             \
+        MJ_CHECK(hipGetLastError());                                                                          \
+        return;
+        MJ_FFT2_SIZES(X)
+#undef X
+    default: break;
+    }
     MJ_FFT_DISPATCH(plan_mask(p), k_fft_strided, grid, dim3(kThreads), lds_bytes(p.N, P), st, in, out, g,
                     plan_arg(p), p.tw, P, inv ? 1 : 0);
     MJ_CHECK(hipGetLastError());
@@ -528,6 +850,18 @@ static void pass_x_fwd(const Fft3D &f, int ncomp, const double *x, int P, hipStr
 {
     const int nrows = ncomp * f.W * f.V;
     dim3 grid((nrows + 2 * P - 1) / (2 * P));
+    switch (f.Nx) {
+#define X(N, R1, R2)                                                                                          \
+    case N:                                                                                                   \
+        hipLaunchKernelGGL((k_fft2_x_fwd<R1, R2>), grid, two_radix_threads(P, R1, R2),                        \
+                           sizeof(double2) * (N + P * XTile<R1, R2>::ld), st, x, f.bufA, nrows, f.U, f.Hx,     \
+                           f.Hp, f.px.tw, P);                                                                 \
+        MJ_CHECK(hipGetLastError());                                                                          \
+        return;
+        MJ_FFT2_SIZES(X)
+#undef X
+    default: break;
+    }
     MJ_FFT_DISPATCH(plan_mask(f.px), k_fft_x_fwd, grid, dim3(kThreads), lds_bytes(f.Nx, P), st, x, f.bufA, nrows,
                     f.U, f.Hx, f.Hp, plan_arg(f.px), f.px.tw, P);
     MJ_CHECK(hipGetLastError());
@@ -577,6 +911,18 @@ static void pass_x_inv(const Fft3D &f, int ncomp, double *y, int P, hipStream_t 
 {
     const int nrows = ncomp * f.W * f.V;
     dim3 grid((nrows + 2 * P - 1) / (2 * P));
+    switch (f.Nx) {
+#define X(N, R1, R2)                                                                                          \
+    case N:                                                                                                   \
+        hipLaunchKernelGGL((k_fft2_x_inv<R1, R2>), grid, two_radix_threads(P, R1, R2),                        \
+                           sizeof(double2) * (N + P * XTile<R1, R2>::ld), st, f.bufA, y, nrows, f.U, f.Hx,     \
+                           f.Hp, f.px.tw, P);                                                                 \
+        MJ_CHECK(hipGetLastError());                                                                          \
+        return;
+        MJ_FFT2_SIZES(X)
+#undef X
+    default: break;
+    }
     MJ_FFT_DISPATCH(plan_mask(f.px), k_fft_x_inv, grid, dim3(kThreads), lds_bytes(f.Nx, P), st, f.bufA, y, nrows,
                     f.U, f.Hx, f.Hp, plan_arg(f.px), f.px.tw, P);
     MJ_CHECK(hipGetLastError());
