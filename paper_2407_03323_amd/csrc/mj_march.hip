@@ -325,7 +325,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
     }
 }
 
-// Far part with a rotation-free source window.  Targets t = 0 .. TG - 1 are steps n_b + t; each
+// Far part with a rotation-free source window, 4 or 8 targets.  Targets t = 0 .. TG - 1 are steps n_b + t; each
 // sums F[t] = init[t] + sum_k Khat_k Jhat_{n_b + t - k} over the lags k >= t + 1 whose source
 // n_b + t - k is at least jmin (and at least 1) and, if jmax > 0, at most jmax.  One lane = one
 // part (real or imaginary) of one mirror point, as in k_mac_far with one target group.  The lane
@@ -391,28 +391,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
     double k0s[KS], k1s[KS], k2s[KS], k3s[KS], k4s[KS], k5s[KS];   // xx yy zz xy xz yz
 #pragma unroll
     for (int s = 0; s < W; s++) jx[s] = jy[s] = jz[s] = 0.0;   // sources before the first lag are zero
-    // the loads of lag k into a source slot and a kernel slot.  With many lags (UL: 10 targets or
-    // more) every call issues the same six loads, so that the wait before each lag's arithmetic
-    // counts only the loads issued after its own (a load skipped on some path makes the compiler
-    // wait for all of them): lags beyond kmax reload lag kmax, whose values no target uses, and a
-    // source before jlo reads a valid slot and is replaced by zero.  The middle level's short
-    // launches (4 targets, at most 15 lags, 3 of them without a source) skip those loads instead.
-    constexpr bool UL = TG >= 10;
+    // the loads of lag k into a source slot and a kernel slot: none beyond kmax, and no source
+    // before jlo (the middle level's launches have at most 15 lags, 3 of them without a source)
     auto load = [&](int k, double &vx, double &vy, double &vz, double &c0, double &c1, double &c2, double &c3,
                     double &c4, double &c5) __attribute__((always_inline)) {
-        if (!UL && k > kmax) return;
-        const int kk = UL ? min(k, kmax) : k;
-        const int j = nb - kk;
-        const bool ok = j >= jlo;
-        if (UL) {
-            const char *J = Jbase + ring_slot(ok ? j : jlo, a.ring) * slot_bytes + joff;
-            const double x = *(const double *)J;
-            const double y = *(const double *)(J + plane_bytes);
-            const double z = *(const double *)(J + 2 * plane_bytes);
-            vx = ok ? x : 0.0;
-            vy = ok ? y : 0.0;
-            vz = ok ? z : 0.0;
-        } else if (ok) {
+        if (k > kmax) return;
+        const int j = nb - k;
+        if (j >= jlo) {
             const char *J = Jbase + ring_slot(j, a.ring) * slot_bytes + joff;
             vx = *(const double *)J;
             vy = *(const double *)(J + plane_bytes);
@@ -420,7 +405,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
         } else {
             vx = vy = vz = 0.0;
         }
-        const double2 *K2 = (const double2 *)(Kbase + (long)(kk - 1) * klag_bytes + koff);
+        const double2 *K2 = (const double2 *)(Kbase + (long)(k - 1) * klag_bytes + koff);
         const double2 v0 = K2[0], v1 = K2[1], v2 = K2[2];
         c0 = v0.x;
         c1 = v0.y;
@@ -433,14 +418,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
     // sources before lag klo are never loaded and stay zero, which is their value: they lie
     // after jmax.  The UF steps are expanded from a compile-time index sequence, so every slot
     // index is a constant.
-    auto step = [&](auto ic, int k0, bool guard) __attribute__((always_inline)) {
+    auto step = [&](auto ic, int k0) __attribute__((always_inline)) {
         constexpr int i = decltype(ic)::value;
         const int k = k0 + i;
         constexpr int ls = (1 + i + PD) % W, lk = (1 + i + PD) % KS, ck = (1 + i) % KS;
-        if (!UL && guard && k > kmax) return;
+        if (k > kmax) return;
         load(k + PD, jx[ls], jy[ls], jz[ls], k0s[lk], k1s[lk], k2s[lk], k3s[lk], k4s[lk], k5s[lk]);
         __builtin_amdgcn_sched_barrier(0);
-        if (UL && guard && k > kmax) return;
         const double kxx = k0s[ck], kyy = k1s[ck], kzz = k2s[ck];
         const double kxy = k3s[ck] * sy, kxz = k4s[ck] * sz, kyz = k5s[ck] * sy * sz;
         [&]<int... T>(std::integer_sequence<int, T...>) __attribute__((always_inline)) {
@@ -453,24 +437,161 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
              ...);
         }(std::make_integer_sequence<int, TG>{});
     };
-    auto body = [&](int k0, bool guard) __attribute__((always_inline)) {
+    auto body = [&](int k0) __attribute__((always_inline)) {
         [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
-            (step(std::integral_constant<int, I>{}, k0, guard), ...);
+            (step(std::integral_constant<int, I>{}, k0), ...);
         }(std::make_integer_sequence<int, UF>{});
     };
-    (void)body;
 #pragma unroll
     for (int d = 0; d < PD; d++) {
         const int ls = (1 + d) % W, lk = (1 + d) % KS;
         load(klo + d, jx[ls], jy[ls], jz[ls], k0s[lk], k1s[lk], k2s[lk], k3s[lk], k4s[lk], k5s[lk]);
     }
     int k0 = klo;
-    for (; k0 <= kmax; k0 += UF) body(k0, true);
+    for (; k0 <= kmax; k0 += UF) body(k0);
     double *Fd = (double *)a.far + (long)r * 3 * plane2 + joff / 8;
     [&]<int... T>(std::integer_sequence<int, T...>) __attribute__((always_inline)) {
         ((T < a.ntarget ? (Fd[(long)T * a.nrhs * 3 * plane2] = ax[T],
                            Fd[(long)T * a.nrhs * 3 * plane2 + plane2] = ay[T],
                            Fd[(long)T * a.nrhs * 3 * plane2 + 2 * plane2] = az[T], 0)
+                        : 0),
+         ...);
+    }(std::make_integer_sequence<int, TG>{});
+}
+
+// The far part for 10 to 16 targets: the window of k_mac_win, for the outer level's long lag
+// loops (ell lags, 182 at 104^3).  What bounds it is not the ring's or the table's bytes but the
+// latency of a lag's loads against the arithmetic of the lags before it: at 104^3 and 16 targets
+// the arithmetic alone takes 8.2 ms, and one lag of loads in flight at two waves per SIMD leaves
+// 13.3.  So a lag's own instructions are only its loads, 144 multiply-adds and two sign flips:
+//   the signs of the mirror point go onto the source as it joins the window and onto the
+//   finished sums, not onto the kernel values of each lag;
+//   ring slot and lag are running scalar addresses (wave = mirror point, its number made
+//   scalar), where there was a remainder, two products and three selects per lag;
+//   whole groups of lags whose sources all count carry no test; the last lags (sources before
+//   jlo) run a guarded copy of the group.
+// That leaves registers for PD = 2 lags in flight at 16 targets (256 VGPRs, nothing spilled).
+// Per launch of 16 targets, one lag in flight and the earlier lag loop against this one: 13.3 to
+// 12.6 ms at 104^3 (182 lags), 15.4 to 14.4 at 64^3 with 8 right-hand sides (112 lags), 2.31 to
+// 2.02 with one.  This loop with PD = 1: 12.9, 14.8, 2.11.
+// As every lag issues the same six loads, lags beyond kmax load lag kmax again, and the sources
+// of lags before jlo read whatever their ring slot holds and are replaced by zero.
+// W and KS: the source slots are a multiple of the kernel slots, so that W lags make a group.
+template <int TG, int PD>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_mac_deep(BlockMacArg a)
+{
+    constexpr int KS = PD + 1, W = (TG + PD + KS - 1) / KS * KS;
+    const int Nyo = a.Ny / 2 + 1, Nzo = a.Nz / 2 + 1;
+    const long nocts = (long)a.Hp * Nyo * Nzo;
+    const int lane = threadIdx.x & 63;
+    const unsigned lb = xcd_block(blockIdx.x, gridDim.x);
+    const int r = lb % a.nrhs;
+    const long o = (lb / a.nrhs) * 32L + (lane >> 1);
+    const int part = lane & 1;
+    const int m = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (o >= nocts) return;
+    const int kx = (int)(o % a.Hp), qy = (int)((o / a.Hp) % Nyo), qz = (int)(o / ((long)a.Hp * Nyo));
+    const int fy = m & 1, fz = m >> 1;
+    if (kx >= a.Hx) return;   // row padding
+    if ((fy && (qy == 0 || 2 * qy == a.Ny)) || (fz && (qz == 0 || 2 * qz == a.Nz))) return;
+    const int ky = fy ? a.Ny - qy : qy, kz = fz ? a.Nz - qz : qz;
+    const double sy = fy ? -1.0 : 1.0, sz = fz ? -1.0 : 1.0;
+    const long plane2 = 2L * a.Nz * a.Ny * a.Hp;                           // one component, in doubles
+    const unsigned joff = (unsigned)(2 * (((long)kz * a.Ny + ky) * a.Hp + kx) + part) * 8u;
+    const unsigned koff = (unsigned)(o * 48);
+    const long slot_bytes = (long)a.nrhs * 3 * plane2 * 8, plane_bytes = plane2 * 8;
+    const long klag_bytes = 6 * nocts * 8;
+    const int nb = a.nb, jlo = max(1, a.jmin);
+    const int kmax = min(a.nk, nb - jlo + TG - 1);          // largest lag with a term, as in k_mac_win
+    const int klo = a.jmax > 0 ? max(1, nb - a.jmax) : 1;   // smallest (above kmax: none at all)
+
+    double ax[TG], ay[TG], az[TG];
+#pragma unroll
+    for (int t = 0; t < TG; t++) ax[t] = ay[t] = az[t] = 0.0;
+    const long tstride = (long)a.nrhs * 3 * plane2;
+    if (a.init) {
+        const double *I = (const double *)a.init + (long)r * 3 * plane2 + joff / 8;
+        [&]<int... T>(std::integer_sequence<int, T...>) __attribute__((always_inline)) {
+            ((T < a.ntarget ? (ax[T] = I[T * tstride], ay[T] = sy * I[T * tstride + plane2],
+                               az[T] = sz * I[T * tstride + 2 * plane2], 0)
+                            : 0),
+             ...);
+        }(std::make_integer_sequence<int, TG>{});
+    }
+    double jx[W], jy[W], jz[W];
+    double k0s[KS], k1s[KS], k2s[KS], k3s[KS], k4s[KS], k5s[KS];   // xx yy zz xy xz yz
+#pragma unroll
+    for (int s = 0; s < W; s++) jx[s] = jy[s] = jz[s] = 0.0;   // sources before the first lag are zero
+    // the next lag to load, its source's ring slot and its kernel values (a lag that exists, also
+    // where klo > kmax)
+    int kn = klo;
+    const char *const Jlow = (const char *)a.ring_base + (long)r * 3 * plane_bytes;
+    const char *Jn = Jlow + (long)ring_slot(nb - klo, a.ring) * slot_bytes;
+    const long wrap = (long)(a.ring - 1) * slot_bytes;
+    const char *Kn = (const char *)a.Khat + (long)(min(klo, kmax) - 1) * klag_bytes;
+    auto load = [&](double &vx, double &vy, double &vz, double &c0, double &c1, double &c2, double &c3, double &c4,
+                    double &c5) __attribute__((always_inline)) {
+        vx = *(const double *)(Jn + joff);
+        vy = *(const double *)(Jn + plane_bytes + joff);
+        vz = *(const double *)(Jn + 2 * plane_bytes + joff);
+        const double2 v0 = *(const double2 *)(Kn + koff), v1 = *(const double2 *)(Kn + koff + 16u),
+                      v2 = *(const double2 *)(Kn + koff + 32u);
+        c0 = v0.x;
+        c1 = v0.y;
+        c2 = v1.x;
+        c3 = v1.y;
+        c4 = v2.x;
+        c5 = v2.y;
+        const bool more = kn < kmax;
+        kn++;
+        Jn = more ? (Jn == Jlow ? Jn + wrap : Jn - slot_bytes) : Jn;
+        Kn = more ? Kn + klag_bytes : Kn;
+    };
+    // lag k = k0 + i, k0 = klo mod W: the source slot of s_{k - t} is (1 + i - t) mod W
+    auto step = [&](auto ic, int k0, bool guard) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value;
+        const int k = k0 + i;
+        constexpr int ls = (1 + i + PD) % W, lk = (1 + i + PD) % KS, ck = (1 + i) % KS, cs = (1 + i) % W;
+        load(jx[ls], jy[ls], jz[ls], k0s[lk], k1s[lk], k2s[lk], k3s[lk], k4s[lk], k5s[lk]);
+        __builtin_amdgcn_sched_barrier(0);   // the loads are issued before the arithmetic of lag k
+        if (guard) {
+            if (k > kmax) return;
+            const bool ok = nb - k >= jlo;
+            jx[cs] = ok ? jx[cs] : 0.0;
+            jy[cs] = ok ? jy[cs] : 0.0;
+            jz[cs] = ok ? jz[cs] : 0.0;
+        }
+        jy[cs] *= sy;
+        jz[cs] *= sz;
+        const double kxx = k0s[ck], kyy = k1s[ck], kzz = k2s[ck], kxy = k3s[ck], kxz = k4s[ck], kyz = k5s[ck];
+        [&]<int... T>(std::integer_sequence<int, T...>) __attribute__((always_inline)) {
+            ((ax[T] = fma(kxz, jz[(1 + i - T + 4 * W) % W],
+                          fma(kxy, jy[(1 + i - T + 4 * W) % W], fma(kxx, jx[(1 + i - T + 4 * W) % W], ax[T]))),
+              ay[T] = fma(kyz, jz[(1 + i - T + 4 * W) % W],
+                          fma(kyy, jy[(1 + i - T + 4 * W) % W], fma(kxy, jx[(1 + i - T + 4 * W) % W], ay[T]))),
+              az[T] = fma(kzz, jz[(1 + i - T + 4 * W) % W],
+                          fma(kyz, jy[(1 + i - T + 4 * W) % W], fma(kxz, jx[(1 + i - T + 4 * W) % W], az[T])))),
+             ...);
+        }(std::make_integer_sequence<int, TG>{});
+    };
+    auto body = [&](int k0, auto guard) __attribute__((always_inline)) {
+        [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
+            (step(std::integral_constant<int, I>{}, k0, decltype(guard)::value), ...);
+        }(std::make_integer_sequence<int, W>{});
+    };
+#pragma unroll
+    for (int d = 0; d < PD; d++) {
+        const int ls = (1 + d) % W, lk = (1 + d) % KS;
+        load(jx[ls], jy[ls], jz[ls], k0s[lk], k1s[lk], k2s[lk], k3s[lk], k4s[lk], k5s[lk]);
+    }
+    int k0 = klo;
+    const int kfull = min(kmax, nb - jlo);
+    for (; k0 + W - 1 <= kfull; k0 += W) body(k0, std::false_type{});
+    for (; k0 <= kmax; k0 += W) body(k0, std::true_type{});
+    double *Fd = (double *)a.far + (long)r * 3 * plane2 + joff / 8;
+    [&]<int... T>(std::integer_sequence<int, T...>) __attribute__((always_inline)) {
+        ((T < a.ntarget ? (Fd[T * tstride] = ax[T], Fd[T * tstride + plane2] = sy * ay[T],
+                           Fd[T * tstride + 2 * plane2] = sz * az[T], 0)
                         : 0),
          ...);
     }(std::make_integer_sequence<int, TG>{});
@@ -512,7 +633,7 @@ __global__ void __launch_bounds__(256) k_mac_near(BlockMacArg a)
 
 void launch_mac_far(const BlockMacArg &a, int tb, hipStream_t st)
 {
-    // 10 to 16 targets: the windowed kernel; 4, 8 and 32: the grouped one (at 8 targets it ran
+    // 10 to 16 targets: a windowed kernel; 4, 8 and 32: the grouped one (at 8 targets it ran
     // 12.10 against 11.61 ms per launch at 104^3).  Neither takes jmin or init here.
     if (tb >= 10 && tb <= 16 && tb % 2 == 0) {
         launch_mac_win(a, tb, st);
@@ -540,22 +661,20 @@ void launch_mac_win(const BlockMacArg &a, int tb, hipStream_t st, size_t lds_res
     const long nocts = (long)a.Hp * (a.Ny / 2 + 1) * (a.Nz / 2 + 1);
     const dim3 grid((unsigned)((nocts + 31) / 32 * a.nrhs)), blk(256);
     if (lds_reserve > 0 && tb == 16) {
-        MJ_CHECK(hipFuncSetAttribute((const void *)k_mac_win<16, 1, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        MJ_CHECK(hipFuncSetAttribute((const void *)k_mac_deep<16, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds_reserve));
-        hipLaunchKernelGGL((k_mac_win<16, 1, 2>), grid, blk, lds_reserve, st, a);
+        hipLaunchKernelGGL((k_mac_deep<16, 2>), grid, blk, lds_reserve, st, a);
         MJ_CHECK(hipGetLastError());
         return;
     }
-    // second argument: lags in flight; the register file holds two at 8 targets, one above
-    // (166 to 238 VGPRs, two waves per SIMD).  At 16 targets two lags in flight also fit (256
-    // VGPRs) but ran 16.3 against 15.5 ms per launch at 104^3
+    // second argument: lags in flight
     switch (tb) {
     case 4: hipLaunchKernelGGL((k_mac_win<4, 2, 3>), grid, blk, 0, st, a); break;
     case 8: hipLaunchKernelGGL((k_mac_win<8, 2, 2>), grid, blk, 0, st, a); break;
-    case 10: hipLaunchKernelGGL((k_mac_win<10, 1, 2>), grid, blk, 0, st, a); break;
-    case 12: hipLaunchKernelGGL((k_mac_win<12, 1, 2>), grid, blk, 0, st, a); break;
-    case 14: hipLaunchKernelGGL((k_mac_win<14, 1, 2>), grid, blk, 0, st, a); break;
-    case 16: hipLaunchKernelGGL((k_mac_win<16, 1, 2>), grid, blk, 0, st, a); break;
+    case 10: hipLaunchKernelGGL((k_mac_deep<10, 2>), grid, blk, 0, st, a); break;
+    case 12: hipLaunchKernelGGL((k_mac_deep<12, 2>), grid, blk, 0, st, a); break;
+    case 14: hipLaunchKernelGGL((k_mac_deep<14, 2>), grid, blk, 0, st, a); break;
+    case 16: hipLaunchKernelGGL((k_mac_deep<16, 2>), grid, blk, 0, st, a); break;
     default: throw ArgError("unsupported target count of the windowed far kernel (4, 8, 10, 12, 14 or 16)");
     }
     MJ_CHECK(hipGetLastError());
