@@ -1265,22 +1265,22 @@ __device__ inline double lane_prev(double x)   // the value of lane - 1 (0 in th
 
 // the (plane, z) tiling of a pass: waves along a haloed plane (positions px + 1 .. plane - px - 2), ZT planes deep
 struct PassTiles {
-    int nq, nz, qg;   // waves along the plane, chunks of planes, blocks along the plane
-    __host__ __device__ PassTiles(int px, int py, int pz, int zt)
-        : nq((px * py - 2 * px - 2 + 61) / 62), nz((pz - 2 + zt - 1) / zt), qg((nq + 3) / 4)
+    int nq, nz, qg;   // waves along the plane, chunks of planes, blocks (of wb waves) along the plane
+    __host__ __device__ PassTiles(int px, int py, int pz, int zt, int wb)
+        : nq((px * py - 2 * px - 2 + 61) / 62), nz((pz - 2 + zt - 1) / zt), qg((nq + wb - 1) / wb)
     {
     }
 };
 
-template <int ZT, bool NORM>
-__global__ void __launch_bounds__(256) k_z0_pass(PassArg a)
+template <int ZT, int WB, bool NORM>
+__global__ void __launch_bounds__(64 * WB) k_z0_pass(PassArg a)
 {
     const int lane = threadIdx.x & 63;
     const int px = a.px, plane = px * a.py;
-    const PassTiles tl(px, a.py, a.pz, ZT);
+    const PassTiles tl(px, a.py, a.pz, ZT, WB);
     unsigned lb = xcd_block(blockIdx.x, gridDim.x);
     const int bx = lb % (tl.qg * tl.nz), r = a.rhs0 + lb / (tl.qg * tl.nz);
-    const int iq = (bx % tl.qg) * 4 + (threadIdx.x >> 6), z0 = 1 + (bx / tl.qg) * ZT;
+    const int iq = (bx % tl.qg) * WB + (threadIdx.x >> 6), z0 = 1 + (bx / tl.qg) * ZT;
     // every lane loads (the shifts need all of them), from a row that keeps its neighbours inside the plane
     const int q = px + iq * 62 + lane, ql = min(q, plane - px - 1);
     const bool mine = iq < tl.nq && lane >= 1 && lane <= 62 && q <= plane - px - 2;
@@ -1397,43 +1397,53 @@ __global__ void __launch_bounds__(1024) k_z0_test(PassArg a, int nb)
     a.stat[r] = CgStatus{pass ? 1 : 0, pass ? 1 : 0, a.k, bb > 0.0 ? sqrt(rr / bb) : 0.0, bb};
 }
 
-// Planes per thread.  More planes spend less on the two they share with their neighbours, fewer leave more
-// waves; measured per pass with 1, 2 and 4: 32^3 3.9, 4.4, 5.6 us; 48^3 5.1, 4.8, 5.9; 64^3 8.8, 8.6, 8.7;
-// eight right-hand sides at 64^3 46, 42, 31; 104^3 26, 25, 19.  So 4 from one block a compute unit, 2 from
-// three blocks on four of them (48^3 has 240 such blocks), else 1.
-static int pass_depth(int px, int py, int pz, int nr)
+// Planes per thread and waves per block.  More planes spend less on the two they share with their
+// neighbours, fewer leave more waves; and up to about two waves per SIMD, a wave in a block of its own starts
+// sooner than four in one block (8^3, where nothing else is left: 3.61 against 3.08 us a pass).  Measured per
+// pass with 1, 2 and 4 planes, in blocks of one wave: 24^3 3.14, 3.53, 4.53 us; 32^3 3.52, 3.65, 4.52; 48^3
+// 4.97, 4.57, 5.20; 64^3 8.14, 8.15, 7.98; in blocks of four: 32^3 3.78, 4.4, 5.6; 48^3 5.1, 4.58, 5.9; 64^3
+// 9.04, 8.6, 8.7; eight right-hand sides at 64^3 46, 42, 31 (36 with 4 planes and one wave); 104^3 26, 25, 19.
+// So 4 planes from 1024 waves, 2 from 768 on 4 of them (48^3 has 960 such waves), else 1; blocks of one wave
+// up to 2048 waves.
+struct PassShape {
+    int zt, wb, blocks;   // blocks per right-hand side
+};
+static PassShape pass_shape(int px, int py, int pz, int nr)
 {
-    auto blocks = [&](int zt) {
-        const PassTiles t(px, py, pz, zt);
+    auto waves = [&](int zt) {
+        const PassTiles t(px, py, pz, zt, 1);
         return (long)t.qg * t.nz * nr;
     };
-    return blocks(4) >= 256 ? 4 : blocks(2) >= 192 ? 2 : 1;
+    const int zt = waves(4) >= 1024 ? 4 : waves(2) >= 768 ? 2 : 1, wb = waves(zt) <= 2048 ? 1 : 4;
+    const PassTiles t(px, py, pz, zt, wb);
+    return {zt, wb, t.qg * t.nz};
 }
 
-int z0_pass_blocks(int U, int V, int W, int nr)
-{
-    const PassTiles t(U + 2, V + 2, W + 2, pass_depth(U + 2, V + 2, W + 2, nr));
-    return t.qg * t.nz;
-}
+int z0_pass_blocks(int U, int V, int W, int nr) { return pass_shape(U + 2, V + 2, W + 2, nr).blocks; }
 
 void launch_z0_pass(const PassArg &a, hipStream_t st)
 {
-    const int zt = pass_depth(a.px, a.py, a.pz, a.nr);
-    const PassTiles t(a.px, a.py, a.pz, zt);
-    const long per_rhs = (long)t.qg * t.nz;
-    if (a.nr < 1 || a.k < 0 || a.k >= a.coef_len || (a.want_norm && 2 * per_rhs > a.part_cap))
+    const PassShape sh = pass_shape(a.px, a.py, a.pz, a.nr);
+    if (a.nr < 1 || a.k < 0 || a.k >= a.coef_len || (a.want_norm && 2L * sh.blocks > a.part_cap))
         throw std::logic_error("Z_0 pass outside its buffers");
-    const dim3 grid((unsigned)(per_rhs * a.nr)), blk(256);
-    auto go = [&]<int ZT>(std::integral_constant<int, ZT>) {
-        if (a.want_norm) hipLaunchKernelGGL((k_z0_pass<ZT, true>), grid, blk, 0, st, a);
-        else hipLaunchKernelGGL((k_z0_pass<ZT, false>), grid, blk, 0, st, a);
+    const dim3 grid((unsigned)((long)sh.blocks * a.nr)), blk(64 * sh.wb);
+    auto go = [&]<int ZT, int WB>() {
+        if (a.want_norm) hipLaunchKernelGGL((k_z0_pass<ZT, WB, true>), grid, blk, 0, st, a);
+        else hipLaunchKernelGGL((k_z0_pass<ZT, WB, false>), grid, blk, 0, st, a);
     };
-    if (zt == 4) go(std::integral_constant<int, 4>{});
-    else if (zt == 2) go(std::integral_constant<int, 2>{});
-    else go(std::integral_constant<int, 1>{});
+    if (sh.wb == 4) {
+        if (sh.zt == 4) go.template operator()<4, 4>();
+        else throw std::logic_error("no such pass");   // 2048 waves of 1 or 2 planes are 1024 of 4
+    } else if (sh.zt == 4) {
+        go.template operator()<4, 1>();
+    } else if (sh.zt == 2) {
+        go.template operator()<2, 1>();
+    } else {
+        go.template operator()<1, 1>();
+    }
     MJ_CHECK(hipGetLastError());
     if (a.want_norm) {
-        hipLaunchKernelGGL(k_z0_test, dim3(a.nr), dim3(1024), 0, st, a, (int)per_rhs);
+        hipLaunchKernelGGL(k_z0_test, dim3(a.nr), dim3(1024), 0, st, a, sh.blocks);
         MJ_CHECK(hipGetLastError());
     }
 }
