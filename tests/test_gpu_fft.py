@@ -75,3 +75,16 @@ def _check(torch, s, info, UVW):
     assert np.linalg.norm(got - ref) <= 2e-15 * np.linalg.norm(ref), (info["Nx"], Ny, Nz)
     back = y.cpu().numpy() / (info["Nx"] * Ny * Nz)
     assert np.linalg.norm(back - x) <= 2e-15 * np.linalg.norm(x), (info["Nx"], Ny, Nz)
+
+
+# the shortest lengths, where a radix is 2 or 3; one of 6 points (no two-radix pass) beside them
+@pytest.mark.parametrize("N", [6, 8, 10, 12, 14, 16, 18, 20, 22, 24, 26, 28, 30])
+@pytest.mark.parametrize("cap", [0, 3])
+def test_short_lengths(torch_cuda, N, cap):
+    from paper_2407_03323_amd import motjvie
+    for U, V, W in ((N // 2, 5, 4), (4, N // 2, 3), (3, 4, N // 2)):
+        s = motjvie.Solver(U, V, W, np.full((W, V, U), 2.0), quad_order=4, fft_pencils=cap, time_block=1)
+        info = s.info()
+        assert (info["Nx"], info["Ny"], info["Nz"]) == (2 * U, 2 * V, 2 * W)
+        _check(torch_cuda, s, info, (U, V, W))
+        s.close()
