@@ -9,6 +9,18 @@
 
 namespace mj {
 
+// Position of item i of a grid of rows of X, Y of them a plane.  Grids have fewer than 2^32 points (a lag's
+// kernel spectra are addressed in 32 bits), and a 64-bit division is some hundred instructions: with three
+// of them per voxel, index arithmetic was much of an elementwise kernel (see k_epilogue).
+struct GridIndex {
+    int x, y, z;
+};
+__device__ inline GridIndex grid_index(long i, int X, int Y)
+{
+    const unsigned n = (unsigned)i, row = n / (unsigned)X, z = row / (unsigned)Y;
+    return {(int)(n - row * (unsigned)X), (int)(row - z * (unsigned)Y), (int)z};
+}
+
 // ---------------------------------------------------------------------------- MAC
 // S^(xi) = sum_{k=1}^{nk} Khat_k(xi) Jhat_{n-k}(xi)   (eq:PnFFTMOT in the spectral domain).
 // Khat_k is real and has a definite parity in every frequency axis (K^aa even, K^ab odd in
@@ -24,10 +36,8 @@ __global__ void __launch_bounds__(256) k_mac(MacArg a)
     const long npt = (long)Hp * Nyo * Nzo;
     const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
     if (t >= npt) return;
-    const int kx = (int)(t % Hp);
+    const auto [kx, qy, qz] = grid_index(t, Hp, Nyo);
     if (kx >= a.Hx) return;   // row padding
-    const int qy = (int)((t / Hp) % Nyo);
-    const int qz = (int)(t / ((long)Hp * Nyo));
     const int r0 = blockIdx.y * G;
     // mirror points
     int ys[2] = {qy, a.Ny - qy}, zs[2] = {qz, a.Nz - qz};
@@ -137,7 +147,7 @@ __device__ inline MirrorPoint mirror_point(int Hx, int Hp, int Ny, int Nz, long 
     const int m = (threadIdx.x >> 6) & 3;
     mp.valid = o < nocts;
     if (!mp.valid) return mp;
-    const int kx = (int)(o % Hp), qy = (int)((o / Hp) % Nyo), qz = (int)(o / ((long)Hp * Nyo));
+    const auto [kx, qy, qz] = grid_index(o, Hp, Nyo);
     const int fy = m & 1, fz = m >> 1;
     if (kx >= Hx) mp.valid = false;   // row padding
     if (fy && (qy == 0 || 2 * qy == Ny)) mp.valid = false;
@@ -213,7 +223,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
     const int part = li & 1;
     const int m = threadIdx.x >> 6;
     if (o >= nocts) return;
-    const int kx = (int)(o % a.Hp), qy = (int)((o / a.Hp) % Nyo), qz = (int)(o / ((long)a.Hp * Nyo));
+    const auto [kx, qy, qz] = grid_index(o, a.Hp, Nyo);
     const int fy = m & 1, fz = m >> 1;
     if (kx >= a.Hx) return;   // row padding
     if ((fy && (qy == 0 || 2 * qy == a.Ny)) || (fz && (qz == 0 || 2 * qz == a.Nz))) return;
@@ -352,7 +362,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
     const int part = lane & 1;
     const int m = threadIdx.x >> 6;
     if (o >= nocts) return;
-    const int kx = (int)(o % a.Hp), qy = (int)((o / a.Hp) % Nyo), qz = (int)(o / ((long)a.Hp * Nyo));
+    const auto [kx, qy, qz] = grid_index(o, a.Hp, Nyo);
     const int fy = m & 1, fz = m >> 1;
     if (kx >= a.Hx) return;   // row padding
     if ((fy && (qy == 0 || 2 * qy == a.Ny)) || (fz && (qz == 0 || 2 * qz == a.Nz))) return;
@@ -490,7 +500,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     const int part = lane & 1;
     const int m = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (o >= nocts) return;
-    const int kx = (int)(o % a.Hp), qy = (int)((o / a.Hp) % Nyo), qz = (int)(o / ((long)a.Hp * Nyo));
+    const auto [kx, qy, qz] = grid_index(o, a.Hp, Nyo);
     const int fy = m & 1, fz = m >> 1;
     if (kx >= a.Hx) return;   // row padding
     if ((fy && (qy == 0 || 2 * qy == a.Ny)) || (fz && (qz == 0 || 2 * qz == a.Nz))) return;
@@ -800,6 +810,8 @@ __device__ inline double wave_average(const WaveArg *wp, const EpiArg &e, int u,
 // sum_{k=1}^{nguess} gx_k J_{n-k} that the Z_0 solve starts from, both in the zero-haloed layout.
 // Voxels with chi = 0 are skipped: their current is zero, and so are their entries of the solve's
 // vectors (cleared whenever eps changes).
+constexpr int kFirstLags = 9;   // past currents the default guess extrapolates
+
 template <bool SERIES>
 __global__ void __launch_bounds__(256) k_epilogue(EpiArg e)
 {
@@ -809,28 +821,34 @@ __global__ void __launch_bounds__(256) k_epilogue(EpiArg e)
     if (i >= M) return;
     const double chi = e.chi[i];
     if (chi == 0.0) return;
-    const int u = (int)(i % e.U), v = (int)((i / e.U) % e.V), z = (int)(i / ((long)e.U * e.V));
+    const auto [u, v, z] = grid_index(i, e.U, e.V);
     const long Mp = (long)(e.U + 2) * (e.V + 2) * (e.W + 2);
     const long ip = ((long)(z + 1) * (e.V + 2) + (v + 1)) * (e.U + 2) + (u + 1);
+    const int kmax = min(e.nloc, e.n - 1);   // lags with a past current
+    // every load before the arithmetic: the kFirstLags most recent currents (all there are without a long
+    // filter), three components each; lags beyond kmax read one that is there and are not used
+    double jv[kFirstLags][3], s[3];
+#pragma unroll
+    for (int k = 1; k <= kFirstLags; k++) {
+        const double *J = e.Jring + ((long)e.slot_of[max(1, min(k, kmax))] * e.nrhs + r) * 3 * M + i;
+#pragma unroll
+        for (int c = 0; c < 3; c++) jv[k - 1][c] = J[c * M];
+    }
+#pragma unroll
+    for (int c = 0; c < 3; c++) s[c] = e.S ? e.S[((long)r * 3 + c) * M + i] : 0.0;
+    const double ie = e.inv_eps[i];
+    __builtin_amdgcn_sched_barrier(0);
     const WaveArg *w = e.waves + r;
     const double avg = SERIES ? wave_series(w, e, u, v, z, e.n * e.c_dt) : wave_average(w, e, u, v, z, e.n * e.c_dt);
-    const double c1 = 0.5 * e.inv_eps[i] + (e.nfir > 1 ? e.fir[1] : 0.0);
-    const int kmax = min(e.nloc, e.n - 1);   // lags with a past current
+    const double c1 = 0.5 * ie + (e.nfir > 1 ? e.fir[1] : 0.0);
     // initial guess of the Z_0 solve: the polynomial through the last nguess solutions,
     // evaluated at step n (the current is smooth in time, so this lands close to J_n).  The
-    // three components of a past current are read together, eight lags at a time, and the
-    // taps come through the scalar cache; each component still sums its lags in order.
+    // taps come through the scalar cache; each component sums its lags in order.
     double b[3], g[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-    for (int c = 0; c < 3; c++) {
-        const long o = ((long)r * 3 + c) * M + i;
-        b[c] = chi * (avg * kconst(w->pol)[c] + (e.S ? e.S[o] : 0.0));
-    }
+    for (int c = 0; c < 3; c++) b[c] = chi * (avg * kconst(w->pol)[c] + s[c]);
     kconst_t *fir = kconst(e.fir);
-#pragma unroll 8
-    for (int k = 1; k <= kmax; k++) {
-        const double *J = e.Jring + ((long)e.slot_of[k] * e.nrhs + r) * 3 * M + i;
-        const double j0 = J[0], j1 = J[M], j2 = J[2 * M];
+    auto add = [&](int k, double j0, double j1, double j2) __attribute__((always_inline)) {
         const double ck = (k == 1) ? c1 : (k < e.nfir ? fir[k] : 0.0);
         b[0] -= ck * j0;
         b[1] -= ck * j1;
@@ -841,6 +859,14 @@ __global__ void __launch_bounds__(256) k_epilogue(EpiArg e)
             g[1] += gk * j1;
             g[2] += gk * j2;
         }
+    };
+#pragma unroll
+    for (int k = 1; k <= kFirstLags; k++)
+        if (k <= kmax) add(k, jv[k - 1][0], jv[k - 1][1], jv[k - 1][2]);
+#pragma unroll 8
+    for (int k = kFirstLags + 1; k <= kmax; k++) {
+        const double *J = e.Jring + ((long)e.slot_of[k] * e.nrhs + r) * 3 * M + i;
+        add(k, J[0], J[M], J[2 * M]);
     }
 #pragma unroll
     for (int c = 0; c < 3; c++) {
@@ -850,11 +876,20 @@ __global__ void __launch_bounds__(256) k_epilogue(EpiArg e)
     }
 }
 
+// Threads per block of an elementwise kernel over M points, ny of them side by side: a block of one wave
+// starts sooner and spreads over more compute units while there are few (as in the three-term passes).
+static dim3 point_block(long M, long ny) { return dim3(M * ny <= 64 * 2048 ? 64 : 256); }
+
+static dim3 voxel_grid(long M, int nrhs, dim3 blk = dim3(256))
+{
+    return dim3((unsigned)((M + blk.x - 1) / blk.x), nrhs);
+}
+
 void launch_epilogue(const EpiArg &e, hipStream_t st)
 {
-    dim3 grd((unsigned)((e.M + 255) / 256), e.nrhs);
-    if (e.series) hipLaunchKernelGGL(k_epilogue<true>, grd, dim3(256), 0, st, e);
-    else hipLaunchKernelGGL(k_epilogue<false>, grd, dim3(256), 0, st, e);
+    const dim3 blk = point_block(e.M, e.nrhs), grd = voxel_grid(e.M, e.nrhs, blk);
+    if (e.series) hipLaunchKernelGGL(k_epilogue<true>, grd, blk, 0, st, e);
+    else hipLaunchKernelGGL(k_epilogue<false>, grd, blk, 0, st, e);
     MJ_CHECK(hipGetLastError());
 }
 
@@ -945,7 +980,7 @@ __device__ inline double cg_md(const CgArg &a, double s, double c0) { return 1.0
 
 __device__ inline long haloed(const CgArg &a, long i)
 {
-    const int x = (int)(i % a.U), y = (int)((i / a.U) % a.V), z = (int)(i / ((long)a.U * a.V));
+    const auto [x, y, z] = grid_index(i, a.U, a.V);
     return ((long)(z + 1) * (a.V + 2) + (y + 1)) * (a.U + 2) + (x + 1);
 }
 
@@ -1169,23 +1204,24 @@ __global__ void __launch_bounds__(256) k_cg_b(CgArg a, int it)
 
 // J_n = sqrt(chi) y, or w (haloed) when given, into the real-space ring (and optionally the caller's output)
 __global__ void k_cg_finish(const double *__restrict__ y, const double *__restrict__ schi,
-                            const double *__restrict__ w, int U, int V, int W, int nrhs, double *__restrict__ J,
+                            const double *__restrict__ w, int U, int V, int W, double *__restrict__ J,
                             double *__restrict__ Jout)
 {
     const long M = (long)U * V * W;
     const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    const int rc = blockIdx.y;   // right-hand side and component
     if (i >= M) return;
-    const double s = w ? 0.0 : schi[i];
-    const long Mp = (long)(U + 2) * (V + 2) * (W + 2);
-    const int u = (int)(i % U), v = (int)((i / U) % V), z = (int)(i / ((long)U * V));
-    const long ip = ((long)(z + 1) * (V + 2) + (v + 1)) * (U + 2) + (u + 1);
-    for (int r = 0; r < nrhs; r++)
-        for (int c = 0; c < 3; c++) {
-            const long o = ((long)r * 3 + c) * M + i;
-            const double x = w ? w[((long)r * 3 + c) * Mp + ip] : s != 0.0 ? s * y[o] : 0.0;
-            J[o] = x;
-            if (Jout) Jout[o] = x;
-        }
+    const long o = rc * M + i;
+    double x;
+    if (w) {
+        const auto [u, v, z] = grid_index(i, U, V);
+        x = w[rc * ((long)(U + 2) * (V + 2) * (W + 2)) + ((long)(z + 1) * (V + 2) + (v + 1)) * (U + 2) + (u + 1)];
+    } else {
+        const double s = schi[i];
+        x = s != 0.0 ? s * y[o] : 0.0;
+    }
+    J[o] = x;
+    if (Jout) Jout[o] = x;
 }
 
 template <int NV>
@@ -1221,8 +1257,9 @@ void launch_cg_finish(const double *y, const double *schi, const double *w, int 
                       double *Jout, hipStream_t st)
 {
     const long M = (long)U * V * W;
-    hipLaunchKernelGGL(k_cg_finish, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, y, schi, w, U, V, W, nrhs, J,
-                       Jout);
+    const dim3 blk = point_block(M, 3L * nrhs);
+    hipLaunchKernelGGL(k_cg_finish, dim3((unsigned)((M + blk.x - 1) / blk.x), 3 * nrhs), blk, 0, st, y, schi, w, U, V,
+                       W, J, Jout);
     MJ_CHECK(hipGetLastError());
 }
 
@@ -1456,7 +1493,7 @@ __global__ void k_fill_trial(const double *__restrict__ schi, int U, int V, int 
     if (i >= M) return;
     const double s = schi[i];
     const long Mp = (long)(U + 2) * (V + 2) * (W + 2);
-    const int u = (int)(i % U), v = (int)((i / U) % V), z = (int)(i / ((long)U * V));
+    const auto [u, v, z] = grid_index(i, U, V);
     const long ip = ((long)(z + 1) * (V + 2) + (v + 1)) * (U + 2) + (u + 1);
     for (int c = 0; c < 3; c++) {
         unsigned long long x = (unsigned long long)(c * M + i) * 0x9E3779B97F4A7C15ull + 0x632BE59BD9B4E019ull;
@@ -1591,12 +1628,17 @@ __device__ inline void stencil_plain(const double *K0, const double *__restrict_
                                      int u, int v, int w, double out[3])
 {
     double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+    // a neighbour outside the grid reads the centre and counts as zero: no branch, so that the loads of
+    // all 27 are in flight together
+    const long i = ((long)w * V + v) * U + u;
+#pragma unroll
     for (int o = 0; o < 27; o++) {
         const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
         const int su = u - dx, sv = v - dy, sw = w - dz;
-        if (su < 0 || su >= U || sv < 0 || sv >= V || sw < 0 || sw >= W) continue;
-        const long j = ((long)sw * V + sv) * U + su;
-        const double x0 = x[j], x1 = x[M + j], x2 = x[2 * M + j];
+        const bool in = su >= 0 && su < U && sv >= 0 && sv < V && sw >= 0 && sw < W;
+        const long j = in ? i - dx - (long)U * dy - (long)U * V * dz : i;
+        const double c0 = x[j], c1 = x[M + j], c2 = x[2 * M + j];
+        const double x0 = in ? c0 : 0.0, x1 = in ? c1 : 0.0, x2 = in ? c2 : 0.0;
         kconst_t *k = kconst(K0) + o * 6;
         a0 += k[0] * x0 + k[3] * x1 + k[4] * x2;
         a1 += k[3] * x0 + k[1] * x1 + k[5] * x2;
@@ -1609,6 +1651,7 @@ __device__ inline void stencil_plain(const double *K0, const double *__restrict_
 
 // B_n for every voxel (forward steps of the gradient run).  Jn, Jn1: J_n and J_{n-1}
 // ([nrhs][3][M], Jn1 NULL at n = 1); e.S holds sum_{k>=1} K_k (*) J_{n-k} of this step.
+template <bool SERIES>
 __global__ void __launch_bounds__(256) k_grad_term(EpiArg e, const double *__restrict__ Jn,
                                                    const double *__restrict__ Jn1, double *__restrict__ Bout)
 {
@@ -1616,9 +1659,9 @@ __global__ void __launch_bounds__(256) k_grad_term(EpiArg e, const double *__res
     const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
     const int r = blockIdx.y;
     if (i >= M) return;
-    const int u = (int)(i % e.U), v = (int)((i / e.U) % e.V), w = (int)(i / ((long)e.U * e.V));
+    const auto [u, v, w] = grid_index(i, e.U, e.V);
     const WaveArg *wa = e.waves + r;
-    const double avg = wave_average(wa, e, u, v, w, e.n * e.c_dt);
+    const double avg = SERIES ? wave_series(wa, e, u, v, w, e.n * e.c_dt) : wave_average(wa, e, u, v, w, e.n * e.c_dt);
     double k0[3];
     stencil_plain(e.k0, Jn + (long)r * 3 * M, M, e.U, e.V, e.W, u, v, w, k0);
     for (int c = 0; c < 3; c++) {
@@ -1720,35 +1763,47 @@ __global__ void __launch_bounds__(256) k_adj_epilogue(EpiArg e)
     const int r = blockIdx.y;
     if (i >= M) return;
     const double chi = e.chi[i];
-    const int u = (int)(i % e.U), v = (int)((i / e.U) % e.V), z = (int)(i / ((long)e.U * e.V));
+    const auto [u, v, z] = grid_index(i, e.U, e.V);
     const double c1 = 0.5 * e.inv_eps[i] + (e.nfir > 1 ? e.fir[1] : 0.0);
     const long Mp = (long)(e.U + 2) * (e.V + 2) * (e.W + 2);
     const long ip = ((long)(z + 1) * (e.V + 2) + (v + 1)) * (e.U + 2) + (u + 1);
-    // as in k_epilogue: three components together, eight lags in flight, each component's lags in order
+    // as in k_epilogue: the most recent lags' loads before the arithmetic, each component's lags in order
     const int kmax = min(e.nloc, e.n - 1);
-    double b[3], g[3] = {0.0, 0.0, 0.0};
+    const double *L = e.Lring + (long)r * 3 * M + i, *N = e.Jring + (long)r * 3 * M + i;
+    const long slot = (long)e.nrhs * 3 * M;
+    double nv[kFirstLags][3], b[3], g[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 1; k <= kFirstLags; k++)
+#pragma unroll
+        for (int c = 0; c < 3; c++) nv[k - 1][c] = N[e.slot_of[max(1, min(k, kmax))] * slot + c * M];
 #pragma unroll
     for (int c = 0; c < 3; c++) {
         const long o = ((long)r * 3 + c) * M + i;
+        const double l = L[e.slot_of[1] * slot + c * M];
         b[c] = e.G[o] + (e.S ? e.S[o] : 0.0);
+        if (kmax >= 1) b[c] -= c1 * l;
     }
     kconst_t *fir = kconst(e.fir);
 #pragma unroll 8
-    for (int k = 1; k <= kmax; k++) {
-        const long o = ((long)e.slot_of[k] * e.nrhs + r) * 3 * M + i;
-        const double *L = e.Lring + o, *N = e.Jring + o;
-        const double ck = (k == 1) ? c1 : (k < e.nfir ? fir[k] : 0.0);
-        if (k == 1 || k < e.nfir) {
-            b[0] -= ck * L[0];
-            b[1] -= ck * L[M];
-            b[2] -= ck * L[2 * M];
-        }
-        if (k <= e.nguess) {
-            const double gk = e.gx[k - 1];
-            g[0] += gk * N[0];
-            g[1] += gk * N[M];
-            g[2] += gk * N[2 * M];
-        }
+    for (int k = 2; k <= min(kmax, e.nfir - 1); k++) {
+        const double *l = L + e.slot_of[k] * slot;
+        const double ck = fir[k];
+        b[0] -= ck * l[0];
+        b[1] -= ck * l[M];
+        b[2] -= ck * l[2 * M];
+    }
+#pragma unroll
+    for (int k = 1; k <= kFirstLags; k++)
+        if (k <= min(kmax, e.nguess))
+#pragma unroll
+            for (int c = 0; c < 3; c++) g[c] += e.gx[k - 1] * nv[k - 1][c];
+#pragma unroll 4
+    for (int k = kFirstLags + 1; k <= min(kmax, e.nguess); k++) {
+        const double *l = N + e.slot_of[k] * slot;
+        const double gk = e.gx[k - 1];
+        g[0] += gk * l[0];
+        g[1] += gk * l[M];
+        g[2] += gk * l[2 * M];
     }
 #pragma unroll
     for (int c = 0; c < 3; c++) {
@@ -1775,7 +1830,7 @@ __global__ void __launch_bounds__(256) k_adj_lambda(AdjArg a)
         }
         return;
     }
-    const int u = (int)(i % a.U), v = (int)((i / a.U) % a.V), w = (int)(i / ((long)a.U * a.V));
+    const auto [u, v, w] = grid_index(i, a.U, a.V);
     double kn[3];
     stencil_plain(a.k0, a.nu + (long)r * 3 * M, M, a.U, a.V, a.W, u, v, w, kn);
     for (int c = 0; c < 3; c++) {
@@ -1799,11 +1854,11 @@ __global__ void __launch_bounds__(256) k_grad_accum(AdjArg a)
     a.grad[i] += s * ie * ie;
 }
 
-static dim3 voxel_grid(long M, int nrhs) { return dim3((unsigned)((M + 255) / 256), nrhs); }
-
 void launch_grad_term(const EpiArg &e, const double *Jn, const double *Jn1, double *Bout, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_grad_term, voxel_grid(e.M, e.nrhs), dim3(256), 0, st, e, Jn, Jn1, Bout);
+    const dim3 blk = point_block(e.M, e.nrhs), grd = voxel_grid(e.M, e.nrhs, blk);
+    if (e.series) hipLaunchKernelGGL(k_grad_term<true>, grd, blk, 0, st, e, Jn, Jn1, Bout);
+    else hipLaunchKernelGGL(k_grad_term<false>, grd, blk, 0, st, e, Jn, Jn1, Bout);
     MJ_CHECK(hipGetLastError());
 }
 void launch_probe_table_by_voxel(const double *table, const int *pair_kmin, const int *inv, long npairs, int np,
@@ -1822,12 +1877,14 @@ void launch_adj_source(const AdjArg &a, hipStream_t st)
 }
 void launch_adj_epilogue(const EpiArg &e, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_adj_epilogue, voxel_grid(e.M, e.nrhs), dim3(256), 0, st, e);
+    const dim3 blk = point_block(e.M, e.nrhs);
+    hipLaunchKernelGGL(k_adj_epilogue, voxel_grid(e.M, e.nrhs, blk), blk, 0, st, e);
     MJ_CHECK(hipGetLastError());
 }
 void launch_adj_lambda(const AdjArg &a, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_adj_lambda, voxel_grid(a.M, a.nrhs), dim3(256), 0, st, a);
+    const dim3 blk = point_block(a.M, a.nrhs);
+    hipLaunchKernelGGL(k_adj_lambda, voxel_grid(a.M, a.nrhs, blk), blk, 0, st, a);
     MJ_CHECK(hipGetLastError());
 }
 void launch_grad_accum(const AdjArg &a, hipStream_t st)
