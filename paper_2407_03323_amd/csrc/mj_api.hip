@@ -27,6 +27,8 @@ constexpr long kChebMaxUnknowns = 1L << 19;
 // from one pass to the next
 constexpr size_t kPassGroupBytes = 190000000;
 
+constexpr int kStepEvents = 9;   // events of a timed step (see StepIO)
+
 // whether outer_overlap = 0 runs the outer level of three on the second stream
 constexpr bool kOverlapDefault = false;
 // LDS each block of the second stream's launch claims: above half of a CU's 160 KB, so that a
@@ -270,6 +272,7 @@ struct mj_solver {
     hipStream_t cap_st = nullptr;        // the library's own stream, for capturing (never the null stream)
     std::map<long, hipGraphExec_t> pass_graphs;   // captured batches by (group, coefficients, first pass, passes)
     mj::CgStatus *cgstat = nullptr, *cgstat_h = nullptr;
+    hipEvent_t ev_status = nullptr;
     mj::WaveArg *waves_d = nullptr;
     bool waves_set = false;
     std::vector<mj::WaveArg> waves;
@@ -331,6 +334,7 @@ struct mj_solver {
         da.put(gen.moments);
         for (void *a : allocs) da.put(a);
         if (cgstat_h) (void)hipHostFree(cgstat_h);
+        if (ev_status) (void)hipEventDestroy(ev_status);
     }
 
     void dfree(void *&ptr)
@@ -354,13 +358,18 @@ struct mj_solver {
     void build_spectra();
     void set_material(const double *eps);
     struct StepIO {
-        hipEvent_t *ev = nullptr;       // 7 events, or NULL
+        // kStepEvents events, or NULL: 0 - 1 forward transform, 7 - 2 history sum, 2 - 3 inverse transform, 3 - 4
+        // right-hand side, 4 - 5 solve and J_n, 8 - 6 probes (recorded if they run)
+        hipEvent_t *ev = nullptr;
+        bool more = false;              // another step follows in this call, on the same rings; its events are
+                                        // ev + kStepEvents
         double *Jout = nullptr;         // forward: J_n copy
         double *Pout = nullptr;         // forward: the probe field of the step goes here (NULL: not formed), once
                                         // kProbeSteps of them are due or flush_probes is called; those of
                                         // successive steps follow each other
         double *Bout = nullptr;         // forward: gradient term B_n
         char *far_kind = nullptr;       // 1 far (outer) launch, 2 near launch, 3 middle launch
+        char *probes_ran = nullptr;     // set to 1 if the probe field was formed (events 8 and 6 recorded)
         bool adjoint = false;           // transposed march
         const double *G = nullptr;      // adjoint: source g_j
         const double *Bj = nullptr;     // adjoint: B_j for the gradient (NULL: none)
@@ -406,6 +415,11 @@ struct mj_solver {
     }
     mj::AdjArg adj_arg() const;
     void step(const StepIO &io);
+    void follow(const StepIO &io, const double *w);
+    void transform(int j, hipEvent_t *ev);
+    const StepIO *cur = nullptr;          // the step whose solve runs
+    const double *followed = nullptr;     // the solution that follow() last took for it
+    int transformed = -1;                 // see step
     void flush_probes();
     void flush_after_failure()
     {
@@ -432,7 +446,7 @@ struct mj_solver {
     void replay();
     int group_size() const;
     void enqueue_passes(bool recorded, int g0, int g1, int T, int K);
-    bool read_status();
+    bool read_status(const double *w = nullptr);
     void solve_z0_chebyshev();
     void estimate_spectrum();
     size_t coef_count() const { return (size_t)nrhs * 2 * mj::kMaxCoef; }
@@ -586,6 +600,7 @@ void mj_solver::create(const mj_config &c)
         gl_d = dalloc<double>(9 * 16, "quadrature rules");
         MJ_CHECK(hipMemcpy(gl_d, rules, sizeof rules, hipMemcpyHostToDevice));
     }
+    MJ_CHECK(hipEventCreateWithFlags(&ev_status, hipEventDisableTiming));
     MJ_CHECK(hipHostMalloc((void **)&cgstat_h, sizeof(mj::CgStatus) * nrhs, hipHostMallocDefault));
     mj::fft3d_init(fft, U, V, W, 3 * nrhs, Nx, Ny, Nz, da);
     bytes += sizeof(double2) * ((size_t)3 * nrhs * W * V * Hp + (size_t)3 * nrhs * W * Ny * Hp);
@@ -763,11 +778,20 @@ void mj_solver::solve_cg()
     cg_guess = mx + 1;
 }
 
-// The status of every right-hand side; true if all met the tolerance.
-bool mj_solver::read_status()
+// The status of every right-hand side; true if all met the tolerance.  w (or NULL): the solution if they
+// did.  What follows the solve is then enqueued before the host waits for the status, so that the device
+// works on while the host wakes up; if some right-hand side goes on, it is enqueued again with the final
+// solution (follow writes only what it will write again).
+bool mj_solver::read_status(const double *w)
 {
     MJ_CHECK(hipMemcpyAsync(cgstat_h, cgstat, sizeof(mj::CgStatus) * nrhs, hipMemcpyDeviceToHost, st));
-    MJ_CHECK(hipStreamSynchronize(st));
+    MJ_CHECK(hipEventRecord(ev_status, st));
+    followed = nullptr;
+    if (w && cur) {
+        follow(*cur, w);
+        followed = w;
+    }
+    MJ_CHECK(hipEventSynchronize(ev_status));
     bool done = true;
     for (int i = 0; i < nrhs; i++) done = done && cgstat_h[i].done;
     return done;
@@ -910,7 +934,7 @@ void mj_solver::replay()
 {
     const int G = group_size(), K = rp.K;
     for (int g0 = 0; g0 < nrhs; g0 += G) enqueue_passes(true, g0, std::min(nrhs, g0 + G), 0, K + 1);
-    bool done = read_status();
+    bool done = read_status(wbuf[(K + 1) & 1]);
     int total = K;
     // groups that missed go on, two passes at a time, so that the solution stays in the same wbuf
     for (int more = 0; !done && more < 2 && total + 2 < std::min(rp.L, cg_maxit); more++) {
@@ -921,7 +945,7 @@ void mj_solver::replay()
             if (!ok) enqueue_passes(true, g0, g1, total + 1, 2);
         }
         total += 2;
-        done = read_status();
+        done = read_status(wbuf[(total + 1) & 1]);
     }
     w_end = wbuf[(total + 1) & 1];
     if (done) {
@@ -1049,7 +1073,7 @@ void mj_solver::solve_z0_chebyshev()
     const int G = group_size();
     auto passes = [&](int T, int K) {
         for (int g0 = 0; g0 < nrhs; g0 += G) enqueue_passes(false, g0, std::min(nrhs, g0 + G), T, K);
-        return read_status();
+        return read_status(wbuf[(T + K) & 1]);
     };
     auto worst = [&] {
         double res = 0.0;
@@ -1323,19 +1347,41 @@ void mj_solver::mac_autotune()
 // history sum (plain or time-blocked), inverse FFT, right-hand side, Z_0 solve, and the
 // outputs asked for.  io.adjoint runs the transposed march instead (sources nu, local
 // history lambda in Lr, right-hand side from io.G).
+// What follows the solve of step n whatever comes next: J_n = w (haloed; NULL: s y) into the real ring, and
+// the forward transform that the next step starts with.
+void mj_solver::follow(const StepIO &io, const double *w)
+{
+    double *Jn = Jr + (size_t)slotR(n) * nrhs * 3 * M;
+    mj::launch_cg_finish(y, schi, w, U, V, W, nrhs, Jn, io.Jout, st);
+    if (io.ev) MJ_CHECK(hipEventRecord(io.ev[5], st));
+    if (io.more) transform(n, io.ev ? io.ev + kStepEvents : nullptr);
+}
+
+// Jhat_j of a past current, into the spectral ring.
+void mj_solver::transform(int j, hipEvent_t *ev)
+{
+    if (ev) MJ_CHECK(hipEventRecord(ev[0], st));
+    mj::fft3d_forward(fft, Jr + (size_t)slotR(j) * nrhs * 3 * M, ring + (size_t)slotS(j) * nrhs * 3 * spec_plane(),
+                      3 * nrhs, st);
+    if (ev) MJ_CHECK(hipEventRecord(ev[1], st));
+    transformed = j;
+}
+
+// `transformed` holds the last step whose transform was enqueued by the step itself; a call that starts
+// or moves the march forgets it, so it never outlives the rings' contents.
 void mj_solver::step(const StepIO &io)
 {
     const long sp = spec_plane();
     hipEvent_t *ev = io.ev;
-    if (ev) MJ_CHECK(hipEventRecord(ev[0], st));
     n += 1;
     const bool hist = n >= 2;
-    if (hist) {
-        const int j = n - 1;
-        mj::fft3d_forward(fft, Jr + (size_t)slotR(j) * nrhs * 3 * M, ring + (size_t)slotS(j) * nrhs * 3 * sp,
-                          3 * nrhs, st);
+    if (hist && transformed != n - 1) transform(n - 1, ev);
+    transformed = -1;
+    if (ev && !hist) {
+        MJ_CHECK(hipEventRecord(ev[0], st));
+        MJ_CHECK(hipEventRecord(ev[1], st));
     }
-    if (ev) MJ_CHECK(hipEventRecord(ev[1], st));
+    if (ev) MJ_CHECK(hipEventRecord(ev[7], st));
     int far_kind = 0;
     const double2 *spec = hist ? mac(n, &far_kind) : Shat;
     if (io.far_kind) *io.far_kind = (char)far_kind;
@@ -1353,10 +1399,18 @@ void mj_solver::step(const StepIO &io)
         mj::launch_epilogue(e, st);
     }
     if (ev) MJ_CHECK(hipEventRecord(ev[4], st));
-    solve_z0();
+    cur = &io;
+    followed = nullptr;
+    try {
+        solve_z0();
+    } catch (...) {
+        cur = nullptr;
+        transformed = -1;
+        throw;
+    }
+    cur = nullptr;
+    if (!followed || followed != w_end) follow(io, w_end);
     double *Jn = Jr + (size_t)slotR(n) * nrhs * 3 * M;
-    mj::launch_cg_finish(y, schi, w_end, U, V, W, nrhs, Jn, io.Jout, st);
-    if (ev) MJ_CHECK(hipEventRecord(ev[5], st));
     if (io.adjoint) {
         mj::AdjArg a = adj_arg();
         a.nu = Jn;
@@ -1374,12 +1428,16 @@ void mj_solver::step(const StepIO &io)
                 probe_out = io.Pout;
                 probe_n0 = n;
             }
-            if (++probe_steps == mj::kProbeSteps) flush_probes();
+            if (++probe_steps == mj::kProbeSteps) {
+                if (ev) MJ_CHECK(hipEventRecord(ev[8], st));
+                flush_probes();
+                if (ev) MJ_CHECK(hipEventRecord(ev[6], st));
+                if (io.probes_ran) *io.probes_ran = 1;
+            }
         }
         if (io.Bout)
             mj::launch_grad_term(e, Jn, n >= 2 ? Jr + (size_t)slotR(n - 1) * nrhs * 3 * M : nullptr, io.Bout, st);
     }
-    if (ev) MJ_CHECK(hipEventRecord(ev[6], st));
 }
 
 // Forms the probe field of the steps that wait for it.
@@ -1449,18 +1507,21 @@ mj::AdjArg mj_solver::adj_arg() const
 void mj_solver::run(int n_steps, double *Jout, double *Pout, int j_every)
 {
     if (!waves_set) throw std::logic_error("plane waves not set (mj_set_plane_waves)");
-    events.ensure((size_t)7 * std::max(n_steps, 1));
+    events.ensure((size_t)kStepEvents * std::max(n_steps, 1));
+    transformed = -1;
     double cg_iter_sum = 0, cg_res_max = 0, cg_iter_max = 0;
     bool noconv = false;
-    std::vector<char> step_far(n_steps, 0);
+    std::vector<char> step_far(n_steps, 0), step_probes(n_steps, 0);
     side_ms = 0.0;
     side_done = 0;
     for (int s = 0; s < n_steps; s++) {
         StepIO io;
-        io.ev = &events.ev[(size_t)7 * s];
+        io.ev = &events.ev[(size_t)kStepEvents * s];
+        io.more = s + 1 < n_steps;
         io.Jout = (Jout && (s + 1) % j_every == 0) ? Jout + (size_t)((s + 1) / j_every - 1) * nrhs * 3 * M : nullptr;
         io.Pout = Pout ? Pout + (size_t)s * nrhs * np * 3 : nullptr;
         io.far_kind = &step_far[s];
+        io.probes_ran = &step_probes[s];
         try {
             step(io);
             check_growth();
@@ -1475,27 +1536,35 @@ void mj_solver::run(int n_steps, double *Jout, double *Pout, int j_every)
             if (!cgstat_h[i].done) noconv = true;
         }
     }
+    hipEvent_t *const ev_last = n_steps > 0 ? &events.ev[(size_t)kStepEvents * (n_steps - 1)] : nullptr;
+    if (ev_last && !step_probes[n_steps - 1]) MJ_CHECK(hipEventRecord(ev_last[8], st));
     flush_probes();
-    if (n_steps > 0) MJ_CHECK(hipEventRecord(events.ev[(size_t)7 * n_steps - 1], st));   // with the last probes
+    if (ev_last) {
+        MJ_CHECK(hipEventRecord(ev_last[6], st));   // with the last probes
+        step_probes[n_steps - 1] = 1;
+    }
     MJ_CHECK(hipStreamSynchronize(st));
     double ph[6] = {0, 0, 0, 0, 0, 0}, probe_ms = 0;
     double far_ms = 0, near_ms = 0, mid_ms = 0;
     int nfar = 0, nnear = 0, nmid = 0;
     for (int s = 0; s < n_steps; s++) {
-        hipEvent_t *ev = &events.ev[(size_t)7 * s];
+        hipEvent_t *ev = &events.ev[(size_t)kStepEvents * s];
         for (int k = 0; k < 5; k++) {
             float ms = 0;
-            MJ_CHECK(hipEventElapsedTime(&ms, ev[k], ev[k + 1]));
+            MJ_CHECK(hipEventElapsedTime(&ms, ev[k == 1 ? 7 : k], ev[k + 1]));
             ph[k] += ms;
             if (k == 1 && step_far[s] == 1) { far_ms += ms; nfar++; }
             if (k == 1 && step_far[s] == 2) { near_ms += ms; nnear++; }
             if (k == 1 && step_far[s] == 3) { mid_ms += ms; nmid++; }
         }
-        float pms = 0, tot = 0;
-        MJ_CHECK(hipEventElapsedTime(&pms, ev[5], ev[6]));
+        float pms = 0;
+        if (step_probes[s]) MJ_CHECK(hipEventElapsedTime(&pms, ev[8], ev[6]));
         probe_ms += pms;
-        MJ_CHECK(hipEventElapsedTime(&tot, ev[0], ev[6]));
-        ph[5] += tot;
+    }
+    if (ev_last) {
+        float tot = 0;
+        MJ_CHECK(hipEventElapsedTime(&tot, events.ev[0], ev_last[6]));
+        ph[5] = tot;
     }
     const double ns = std::max(n_steps, 1);
     for (int k = 0; k < 6; k++) stat[k] = ph[k] / ns;
@@ -1976,6 +2045,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
         for (int i = 0; i < nrhs; i++)
             if (!cgstat_h[i].done) noconv = true;
     };
+    transformed = -1;
     try {
         // 1. forward
         const int last0 = starts[C - 1];
@@ -1988,6 +2058,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
             StepIO io;
             io.Pout = Ehist + (size_t)(t - 1) * nrhs * np * 3;
             io.Bout = t >= last0 ? Bbuf + (size_t)(t - last0) * vec : nullptr;
+            io.more = t < N;
             step(io);
             check_growth();
             check_cg();
@@ -2014,6 +2085,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
                 // restart the forward march at s0 from its checkpoint and recompute the segment
                 drop_side();
                 n = s0 - 1;
+                transformed = -1;
                 if (c > 0) {
                     const int j0 = s0 - 1 - ell;   // first stored step
                     for (int j = std::max(1, j0); j <= s0 - 1; j++) {
@@ -2028,6 +2100,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
                 for (int t = s0; t <= s1; t++) {
                     StepIO io;
                     io.Bout = Bbuf + (size_t)(t - s0) * vec;
+                    io.more = t < s1;
                     step(io);
                     check_cg();
                 }
@@ -2041,6 +2114,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
             Lr = lam_r;
             bq = bqb;
             n = n_adj;
+            transformed = -1;
             load_record(rec_adj, C);
             for (int j = s1; j >= s0; j--) {
                 const int at = (s1 - j) % mj::kProbeSteps;   // the source of up to kProbeSteps steps at once
@@ -2058,6 +2132,7 @@ void mj_solver::adjoint_gradient(int N, int ckpt_every, double *phi, double *gra
                 io.G = G + (size_t)at * vec;
                 io.Bj = Bbuf + (size_t)(j - s0) * vec;
                 io.grad = grad_dev;
+                io.more = j > s0;
                 step(io);
                 check_cg();
             }

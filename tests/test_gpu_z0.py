@@ -96,3 +96,39 @@ def test_state_without_solve_record_is_read(torch_cuda):
         s.close()
         out.append(J)
     assert float((out[0] - out[1]).norm()) <= 1e-11 * float(out[0].norm())
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(z0_solver=1), dict(time_block=1),
+                                dict(time_block=4, outer_block=8, outer_overlap=2)])
+def test_one_call_and_single_steps_agree(torch_cuda, kw):
+    """Within a call a step enqueues the next one's forward transform with its own solution, also where the
+    solve then goes on (the waves change at step 30); single steps never do.  Bit for bit the same currents,
+    and a state or a reset between two calls leaves nothing of the march before it."""
+    from paper_2407_03323_amd import motjvie
+    torch = torch_cuda
+    U, V, W, n, m = 13, 12, 11, 60, 30
+    prob = _problem(U, V, W, 2, n)
+    other = [wl.gaussian_wave(U, V, W, k, p, 1.5, 25.0) for k, p in wl.random_directions(2, 99)]
+    out = []
+    for single in (False, True):
+        s = motjvie.solver_for(prob, **kw)
+
+        def go(a, b, J):
+            for i in range(a, b) if single else (a,):
+                s.run(1 if single else b - a, J[i:i + 1] if single else J[a:b])
+        J = torch.zeros((3, n, 2, 3, W, V, U), dtype=torch.float64, device="cuda")
+        go(0, m, J[0])
+        st = s.get_state()
+        s.set_plane_waves(other)
+        go(m, n, J[0])
+        s.set_state(st)          # the same step, other currents after it
+        s.set_plane_waves(other)
+        go(m, n, J[1])
+        s.reset()
+        s.set_plane_waves(other)
+        go(0, n, J[2])
+        s.close()
+        out.append(J)
+    assert torch.equal(out[0], out[1])
+    assert torch.equal(out[0][0, m:], out[0][1, m:])
+    assert float(out[0].abs().max()) > 0
