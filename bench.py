@@ -178,8 +178,8 @@ def main():
     ap.add_argument("--no-extras", action="store_true", help="skip the batched (C3) and adjoint (C4) ratios")
     ap.add_argument("--time-block", type=int, default=0, help="steps per time block (0 = library default)")
     ap.add_argument("--outer-block", type=int, default=0, help="steps per outer time block (three levels; 0 = two)")
-    ap.add_argument("--z0-solver", type=int, default=0, help="0 by size, 1 CG, 2 Chebyshev")
-    ap.add_argument("--z0-graphs", type=int, default=0, help="replay the Chebyshev batches from HIP graphs")
+    ap.add_argument("--z0-solver", type=int, default=0, help="0 replayed CG coefficients, 1 CG, 2 Chebyshev")
+    ap.add_argument("--z0-graphs", type=int, default=0, help="launch the passes of a solve from HIP graphs")
     ap.add_argument("--outer-overlap", type=int, default=0,
                     help="0 library default, 1 outer level in line, 2 on a second stream")
     ap.add_argument("--copy-probe-mib", type=int, default=0,
@@ -262,6 +262,7 @@ def main():
     SJ, SK = 48.0 * half * R, 48.0 * octant
     B2 = info["outer_block"]
     TB = B2 if B2 else B                      # targets of one far launch
+    far = "k_mac_deep" if 10 <= TB <= 16 else "k_mac_win" if B2 else "k_mac_far"
     ov = bool(info["outer_overlap"])
     if ov:
         # the launch on the second stream: lags B2 + 1 .. ell of the next outer block's B2
@@ -269,13 +270,13 @@ def main():
         # is measured on that stream while the march shares the device
         bytes_launch = (ell - B2) * (SJ + SK) + B2 * SJ
         launch_ms = st["side_launch_ms"]
-        kname = "k_mac_win<%d> (outer level of three, on the second stream, history MAC)" % TB
+        kname = "%s<%d> (outer level of three, on the second stream, history MAC)" % (far, TB)
     elif B > 1:
         # per launch: every one of the ell lags once (Jhat and Khat) and TB partial sums written
         bytes_launch = ell * (SJ + SK) + TB * SJ
         launch_ms = st["far_launch_ms"]
-        kname = ("k_mac_win<%d> (outer level of three, history MAC)" % TB if B2 else
-                 "k_mac_win<%d> (time-blocked history MAC, far part)" % TB)
+        kname = ("%s<%d> (outer level of three, history MAC)" % (far, TB) if B2 else
+                 "%s<%d> (time-blocked history MAC, far part)" % (far, TB))
     else:
         bytes_launch = ell * (SJ + SK) + SJ
         launch_ms = st["mac_ms"]
@@ -334,7 +335,8 @@ def main():
                    "phase_ms": {k: round(st[k], 4) for k in ("fft_fwd_ms", "mac_ms", "fft_inv_ms", "epilogue_ms",
                                                               "z0_ms")},
                    "cg_iters": round(st["cg_iters"], 2), "time_block": B, "outer_block": B2,
-                   "z0_solver": "CG" if info["z0_solver"] == 1 else "Chebyshev",
+                   "z0_solver": (("replayed CG coefficients, " if args.z0_solver == 0 else "") +
+                                 ("CG" if info["z0_solver"] == 1 else "Chebyshev")),
                    "mid_launch_ms": round(st["mid_launch_ms"], 4),
                    "fft_pencils": [info["fft_pencils_x"], info["fft_pencils_y"], info["fft_pencils_z"]],
                    "far_launch_ms": round(st["far_launch_ms"], 4), "near_launch_ms": round(st["near_launch_ms"], 4),
