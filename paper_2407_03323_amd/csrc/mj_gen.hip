@@ -38,7 +38,7 @@
 //
 // A foot that lies outside the square by two of its edges or more starts the rays at its distance from
 // the square instead of 0: what lies inside cancels between the four triangles.  That leaves only short
-// cells away from the foot, where few points do (see order_class).
+// cells away from the foot, where few points do (see order_class, and grazed for the exception).
 //
 // One wave takes one offset.  It is bound by FP64 work, about 250 operations a node, so the edges of the
 // squares are cut first, a lane each, and the intervals that contribute go into a list in LDS whose s-nodes
@@ -101,6 +101,30 @@ __host__ __device__ inline int order_class(double dx, double dy, double dz, cons
     int c = 0;
     for (int i = 1; i < kOrderClasses; i++) c = g2 >= kClassGap[i] * kClassGap[i] * hm * hm ? i : c;
     return c;
+}
+
+// Whether a sphere of shell [Ra, Rb) cuts a plane of the offset D (lengths) in a circle about as small as the
+// voxels, next to the squares in that plane.  The rays to an edge then start or end at rho / L, where L, the
+// distance to the foot, bends over an edge that is nearer than its own length, and the few points of a far
+// offset do not follow: at D = (13.6, 1.04, 0.29) with edges 1 x 0.7 x 1.3 and r = 0.7, where the sphere 18 r
+// = 12.6 cuts the plane 12.5958 in a circle of 0.33, 11 points a side gave 3e-8 of the kernel where 16 give
+// 2e-10.  Such a shell takes the points of voxels in contact, whatever its distance.  From 1.5 edges away the
+// bend's nearest singularity leaves 10 points below 1e-15; circles of 3 edges and more pass the squares that
+// are nearer than that.
+__host__ __device__ inline bool grazed(const double D[3], double Ra, double Rb, const double hv[3])
+{
+    const double hm = fmax(hv[0], fmax(hv[1], hv[2])), rho2 = 9.0 * hm * hm;
+    bool g = false;
+    for (int ax = 0; ax < 3; ax++) {
+        const int b1 = (ax + 1) % 3, b2 = (ax + 2) % 3;
+        const double n1 = fmax(0.0, fabs(D[b1]) - hv[b1]), n2 = fmax(0.0, fabs(D[b2]) - hv[b2]);
+        if (n1 * n1 + n2 * n2 >= 2.25 * hm * hm) continue;
+        for (int t = -1; t <= 1; t++) {
+            const double c = D[ax] + t * hv[ax], a2 = Ra * Ra - c * c, b2_ = Rb * Rb - c * c;
+            g = g || (a2 > 0.0 && a2 < rho2) || (b2_ > 0.0 && b2_ < rho2);
+        }
+    }
+    return g;
 }
 
 // Shells a r <= |d| < (a + 1) r, a in [a_lo, a_lo + nsh), that meet the distance range
@@ -412,6 +436,17 @@ __device__ inline void load_rules(GenLds &l, const GenRules &R, int cls)
     __syncthreads();
 }
 
+// The rules of one shell of an offset of order class `far`, loaded unless they are there (cls: the class that is)
+__device__ inline void shell_rules(GenLds &l, const GenRules &R, int far, const double D[3], double Ra, double Rb,
+                                   const double *hv, int &cls)
+{
+    const int want = far > 0 && grazed(D, Ra, Rb, hv) ? 0 : far;
+    if (want == cls) return;
+    __syncthreads();
+    load_rules(l, R, want);
+    cls = want;
+}
+
 // The planes of axis AX, shell [Ra, Rb): each lane's share of the moments (every lane of the wave calls it)
 template <int AX, bool ANI>
 __device__ __attribute__((always_inline)) inline void axis_moments(GenLds &l, int ns, int nt, const double D[3],
@@ -500,7 +535,7 @@ __host__ __device__ inline void stored_offset(int d[3], int pos[3], const int n[
 }
 
 template <bool ANI>
-__global__ void __launch_bounds__(kGenThreads) k_gen_moments(double *__restrict__ mom, GenArg ga)
+__global__ void __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))) k_gen_moments(double *__restrict__ mom, GenArg ga)
 {
     __shared__ GenLds lds;
     const int idx = blockIdx.x;
@@ -511,10 +546,12 @@ __global__ void __launch_bounds__(kGenThreads) k_gen_moments(double *__restrict_
     const double D[3] = {d[0] * ga.hv[0], d[1] * ga.hv[1], d[2] * ga.hv[2]};
     int a_lo, nsh;
     shell_range(d[0], d[1], d[2], ga.hv, ga.r, a_lo, nsh);
-    const int cls = order_class(d[0], d[1], d[2], ga.hv), ns = ga.rules->ns[cls], nt = ga.rules->nt[cls];
-    load_rules(lds, *ga.rules, cls);
+    const int far = order_class(d[0], d[1], d[2], ga.hv);
+    int cls = -1;
     double *out = mom + (size_t)idx * ga.ms * kMoments;
     for (int sh = 0; sh < min(nsh, ga.ms); sh++) {   // the others stay zero
+        shell_rules(lds, *ga.rules, far, D, (a_lo + sh) * ga.r, (a_lo + sh + 1) * ga.r, ga.hv, cls);
+        const int ns = ga.rules->ns[cls], nt = ga.rules->nt[cls];
         double m[kMoments];
         shell_moments<ANI>(lds, ns, nt, D, a_lo + sh, ga.r, ga.hv, ga.ih, m);
         if (threadIdx.x == 0)
@@ -666,7 +703,7 @@ struct OffgridArg {
 // One 64-lane block per (test voxel, source voxel) pair: shell moments by the same face
 // quadrature as the grid kernels, then the pair's window of lags.
 template <bool ANI>
-__global__ void __launch_bounds__(kGenThreads) k_offgrid_table(OffgridArg oa, GenArg ga)
+__global__ void __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(2))) k_offgrid_table(OffgridArg oa, GenArg ga)
 {
     const long i = blockIdx.x;
     const int p = oa.pair_probe[i], vox = oa.pair_vox[i];
@@ -679,9 +716,11 @@ __global__ void __launch_bounds__(kGenThreads) k_offgrid_table(OffgridArg oa, Ge
     const double D[3] = {Dv[0] * oa.hv[0], Dv[1] * oa.hv[1], Dv[2] * oa.hv[2]};
     __shared__ GenLds lds;
     __shared__ double mom[kShellCap * kMoments];
-    const int cls = order_class(Dv[0], Dv[1], Dv[2], oa.hv), ns = ga.rules->ns[cls], nt = ga.rules->nt[cls];
-    load_rules(lds, *ga.rules, cls);
+    const int far = order_class(Dv[0], Dv[1], Dv[2], oa.hv);
+    int cls = -1;
     for (int sh = 0; sh < nsh; sh++) {
+        shell_rules(lds, *ga.rules, far, D, (a_lo + sh) * oa.r, (a_lo + sh + 1) * oa.r, oa.hv, cls);
+        const int ns = ga.rules->ns[cls], nt = ga.rules->nt[cls];
         double m[kMoments];
         shell_moments<ANI>(lds, ns, nt, D, a_lo + sh, oa.r, oa.hv, oa.ih, m);
         if (threadIdx.x == 0)

@@ -58,3 +58,25 @@ def test_edges_cut_around_their_nearest_point(torch_cuda):
         ref = np.array([mot.kernel_entry(k, d, ngl=24, r=0.45) for k in range(n)])
         assert np.abs(ref).max() > 0 and np.abs(got - ref).max() <= 1e-10 * np.abs(ref).max()
     s.close()
+
+
+@pytest.mark.parametrize("hv,r,D", [
+    ((1.0, 0.7, 1.3), 0.7, [(13.595790667296122, 1.0400267473549167, 0.29396812422172935),
+                            (13.595790667296122, 1.0400267473549167, 1.006031875778271),
+                            (6.594792936872352, 1.0397363021375359, 0.2936997818765675),
+                            (12.888234457101511, 1.2429470524374953, 0.16522220916036323)]),
+    ((1.0, 1.0, 1.0), 1.0, [(9.0 + 1.0 - 0.004, 1.31, 0.22), (0.4, 14.0 - 0.006, 1.2), (1.25, 0.1, 30.0 - 0.003)]),
+])
+def test_spheres_that_graze_a_plane(torch_cuda, hv, r, D):
+    """Far probes in front of a voxel whose plane a sphere cuts in a circle smaller than the voxel: the few
+    points of their distance do not follow the rays there, and the shell takes 16.  Against 16 points
+    everywhere, to the rounding of the sums (1e-13 at these distances; 1e-12 with a margin)."""
+    out = []
+    for q in (0, 16):
+        s = _solver(3, 3, 3, hy=hv[1], hz=hv[2], c_dt=r, quad_order=q)
+        s.set_probes(np.array(D) + 0.5 * np.array(hv))   # seen from voxel (0, 0, 0)
+        n = 50   # beyond the last lag that reaches any of these
+        out.append([s.probe_kernel_values([p] * n, [(0, 0, 0)] * n, list(range(n))) for p in range(len(D))])
+        s.close()
+    for a, b in zip(*out):
+        assert np.abs(b).max() > 0 and np.abs(a - b).max() <= 1e-12 * np.abs(b).max()
