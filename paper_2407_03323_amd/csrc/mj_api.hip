@@ -1453,6 +1453,7 @@ void mj_solver::flush_probes()
     pa.nrhs = nrhs;
     pa.n0 = probe_n0;
     pa.ntarget = probe_steps;
+    pa.ell = ell;
     pa.M = M;
     pa.npairs = npairs;
     pa.Jring = Jr;

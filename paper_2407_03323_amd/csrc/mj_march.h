@@ -186,6 +186,7 @@ struct ProbeStepArg {
     const int *pair_vox;     // [npairs]
     const int *pair_kmin;    // [npairs]
     int np, nw, nrhs, n0, ntarget;
+    int ell;                 // last lag
     // chunk c covers pairs [ck_lo[c], ck_hi[c]) of one probe; probe p owns chunks [ck_start[p], ck_start[p + 1])
     const int *ck_lo, *ck_hi, *ck_start;
     long nck;

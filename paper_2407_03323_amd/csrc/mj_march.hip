@@ -1531,17 +1531,21 @@ __global__ void __launch_bounds__(256) k_probe_rows(ProbeStepArg a)
 #pragma unroll
     for (int t = 0; t < T; t++) ax[t] = ay[t] = az[t] = 0.0;
     const int hi = a.ck_hi[c];
+    const int jlo = max(1, a.n0 - a.ell);
     for (int q = a.ck_lo[c] + lane; q < hi; q += 64) {
         const int j0 = a.n0 - a.pair_kmin[q];   // source of step n0 at the first lag
         const double *J = a.Jring + (long)r * 3 * a.M + a.pair_vox[q];
         double jx[T], jy[T], jz[T];
-        // sources before the first step, and those of targets past the last, count as zero
+        // sources before the first step or beyond the last lag of step n0, and those of targets past the last,
+        // count as zero: a window may reach beyond the last lag, where the table is zero, but a march resumed
+        // from a state has nothing in the ring's slots of those steps, and zero times that may be NaN
         auto load = [&](int j, bool ok, double &x, double &y, double &z) __attribute__((always_inline)) {
-            const double *s = J + (long)((ok && j >= 1) ? j % a.rdepth : 0) * a.nrhs * 3 * a.M;
+            const bool there = ok && j >= jlo;
+            const double *s = J + (long)(there ? j % a.rdepth : 0) * a.nrhs * 3 * a.M;
             const double vx = s[0], vy = s[a.M], vz = s[2 * a.M];
-            x = ok && j >= 1 ? vx : 0.0;
-            y = ok && j >= 1 ? vy : 0.0;
-            z = ok && j >= 1 ? vz : 0.0;
+            x = there ? vx : 0.0;
+            y = there ? vy : 0.0;
+            z = there ? vz : 0.0;
         };
 #pragma unroll
         for (int t = 0; t < T; t++) load(j0 + t, t < a.ntarget, jx[t], jy[t], jz[t]);

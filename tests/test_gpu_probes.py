@@ -83,3 +83,55 @@ def test_state_between_probe_groups(torch_cuda):
     s.run(n - m, None, F)
     s.close()
     assert float(E.norm()) > 0 and torch.equal(E[m:], F)
+
+
+@pytest.fixture
+def nan_memory(torch_cuda, monkeypatch):
+    """The library's device memory filled with NaN before it gets it (allocator="torch")."""
+    from paper_2407_03323_amd import motjvie
+    torch, held = torch_cuda, {}
+
+    def alloc(nbytes, ctx):
+        t = torch.full(((int(nbytes) + 7) // 8,), float("nan"), dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        held[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def free(ptr, ctx):
+        torch.cuda.synchronize()
+        del held[ptr]
+
+    monkeypatch.setattr(motjvie, "torch_allocator", lambda stream: (motjvie.ALLOC_FN(alloc), motjvie.FREE_FN(free)))
+
+
+# outside receivers, whose windows reach beyond the last lag: the steps those lags name are not in a state
+@pytest.mark.parametrize("UVW,r,nr,radius", [((6, 5, 4), 1.0, 1, 5.0), ((7, 6, 5), 0.7, 2, 9.0)])
+def test_resumed_probe_field_reads_the_state_alone(torch_cuda, nan_memory, UVW, r, nr, radius):
+    """The first calls after mj_set_state, of 1, 2, 3 and 7 steps, repeat the uninterrupted march bit for bit in
+    memory that held NaN: no sum reads a ring slot that the state does not fill."""
+    from paper_2407_03323_amd import motjvie
+    torch = torch_cuda
+    U, V, W = UVW
+    m, more = 33, 7
+    eps = wl.random_eps(U, V, W, 41, 2.0, 9.0)
+    waves = [wl.gaussian_wave(U, V, W, k, p, 2.0, 3.0) for k, p in wl.random_directions(nr, 4)]
+    prob = wl.Problem("resume", U, V, W, eps, waves, m + more, fir=wl.binomial_highpass(3, 0.01), c_dt=r)
+    pts = wl.fibonacci_sphere(3, radius, (U / 2, V / 2, W / 2))
+    s = motjvie.solver_for(prob)
+    s.set_probes(pts)
+    s.run(m)
+    st = s.get_state()
+    E = torch.zeros((more, nr, 3, 3), dtype=torch.float64, device="cuda")
+    s.run(more, None, E)
+    s.close()
+    assert float(E.norm()) > 0
+    for first in (1, 2, 3, 7):
+        s = motjvie.solver_for(prob, allocator="torch")
+        s.set_probes(pts)
+        s.set_state(st)
+        F = torch.zeros_like(E)
+        s.run(first, None, F[:first])
+        if first < more:
+            s.run(more - first, None, F[first:])
+        s.close()
+        assert torch.equal(E, F), first
