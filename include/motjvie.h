@@ -102,7 +102,10 @@ typedef struct {
                                  coefficients CG took in an earlier step of the march (CG's iteration
                                  count at the Chebyshev iteration's launches), behind which stands 2
                                  up to 2^19 voxels and 1 above.  Every solve is tested on its own residual
-                                 and stops at cg_rtol; cg_maxit bounds the iterations */
+                                 and stops at cg_rtol.  The passes form it anew each time, so it ends at its
+                                 own rounding (about 1e-16 of the right-hand side); where that is above
+                                 cg_rtol, CG follows them, which keeps its residual by recurrence.  cg_maxit
+                                 bounds the passes, and the iterations of a CG that follows them */
     int32_t z0_graphs;        /* != 0: the Chebyshev or replayed passes of a solve (whose arguments depend
                                  only on the pass index) are captured once per batch shape as HIP graphs
                                  and launched on `stream` in later steps; 0: launched one by one */

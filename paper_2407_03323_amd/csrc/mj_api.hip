@@ -1066,6 +1066,8 @@ void mj_solver::estimate_spectrum()
 // coefficients, as many as the last solve needed before the first test, then as many more as the
 // polynomials' convergence factor asks for.  An iteration gains the factor rho, so the next solve takes
 // fewer passes by what this one's residual fell short of the tolerance.
+// A tolerance below the residual's rounding (1e-16 of b on small grids with eps up to 20; more with the condition
+// of Z_0) is left to CG.
 void mj_solver::solve_z0_chebyshev()
 {
     const double kappa = lam_hi / lam_lo;
@@ -1082,15 +1084,26 @@ void mj_solver::solve_z0_chebyshev()
     };
     auto steps = [&](double ratio) { return lrho < 0.0 ? std::log(ratio) / lrho : 1.0; };
     int total = std::max(1, std::min(cg_maxit, cheb_pred > 0 ? cheb_pred : (int)std::ceil(steps(cg_rtol)) + 1));
-    bool done = passes(0, total + 1);
-    while (!done && total < cg_maxit) {
+    bool done = passes(0, total + 1), stalled = false;
+    while (!done && !stalled && total < cg_maxit) {
         const double res = worst();
         if (!(res > cg_rtol)) break;   // not finite
         const int K = std::max(1, std::min(cg_maxit - total, (int)std::ceil(steps(cg_rtol / res)) + 1));
         done = passes(total + 1, K);
+        // less than half of what the polynomials promise (on a logarithmic scale): the residual, formed anew in
+        // every pass, has come down to its own rounding, and no pass will lower it
+        stalled = !done && worst() > res * std::exp(0.5 * lrho * K);
+        cheb_pred = total;   // of a solve that stalls: what it took to get there
         total += K;
     }
     w_end = wbuf[(total + 1) & 1];
+    if (stalled) {   // CG keeps its residual by recurrence, so any tolerance ends it
+        mj::CgArg a = cg_arg();
+        a.w = w_end;
+        run_cg(a, 2);
+        for (int i = 0; i < nrhs; i++) cgstat_h[i].iters += total;
+        return;
+    }
     const double res = worst();
     cheb_pred = total;
     if (done && res > 0.0 && res < 0.5 * cg_rtol)

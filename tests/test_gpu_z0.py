@@ -132,3 +132,27 @@ def test_one_call_and_single_steps_agree(torch_cuda, kw):
     assert torch.equal(out[0], out[1])
     assert torch.equal(out[0][0, m:], out[0][1, m:])
     assert float(out[0].abs().max()) > 0
+
+
+@pytest.mark.parametrize("z0", [0, 2])
+@pytest.mark.parametrize("hi,rtol", [(12.0, 1e-15), (12.0, 1e-16), (12.0, 1e-18), (1e4, 1e-13)])
+def test_tolerances_at_the_rounding_of_the_residual(torch_cuda, z0, hi, rtol):
+    """A residual formed anew cannot fall below its own rounding, which a tight tolerance or a high contrast puts
+    above cg_rtol: the solve then ends by CG, whose residual is kept by recurrence, as it does with z0_solver 1."""
+    U, V, W, n = 7, 6, 5, 40
+    eps = wl.random_eps(U, V, W, 5, 1.5 if hi < 100 else 1e3, hi)
+    k, p = wl.XPOL_PLUS_Z
+    prob = wl.Problem("tight", U, V, W, eps, [wl.gaussian_wave(U, V, W, k, p, 3.0, 3.0)], n,
+                      fir=wl.binomial_highpass(17, 0.01))
+    print("tolerance", z0, hi, rtol, flush=True)
+    out = []
+    from paper_2407_03323_amd import motjvie
+    for solver in (z0, 1):
+        s = motjvie.solver_for(prob, z0_solver=solver, cg_rtol=rtol)
+        J = torch_cuda.zeros((n, 1, 3, W, V, U), dtype=torch_cuda.float64, device="cuda")
+        s.run(n, J)
+        assert s.stats()["cg_res_max"] <= rtol
+        s.close()
+        out.append(J)
+    # 40 solves, each within max(rtol, rounding) of the current times the condition of Z_0 (about eps)
+    assert float((out[0] - out[1]).norm()) <= 40 * max(rtol, 1e-15) * max(hi, 100.0) * float(out[1].norm())
