@@ -443,6 +443,7 @@ struct mj_solver {
     bool run_cg(const mj::CgArg &a, int batch);
     void solve_cg();
     void learn();
+    void cg_after_passes(int total, int batch);
     void replay();
     int group_size() const;
     void enqueue_passes(bool recorded, int g0, int g1, int T, int K);
@@ -930,6 +931,21 @@ void mj_solver::learn()
     }
 }
 
+// CG from where `total` passes ended, or from zero for a right-hand side that they left further off than that:
+// CG tests the residual of its recurrence, which hides what cancels from the first one, about 1e-16 of it (and
+// coefficients that do not fit a spectrum can take the iterate anywhere, also out of the finite range).
+void mj_solver::cg_after_passes(int total, int batch)
+{
+    double *w = wbuf[(total + 1) & 1];
+    const size_t v = (size_t)3 * (U + 2) * (V + 2) * (W + 2);
+    for (int i = 0; i < nrhs; i++)
+        if (!(cgstat_h[i].res <= 1.0)) MJ_CHECK(hipMemsetAsync(w + i * v, 0, sizeof(double) * v, st));
+    mj::CgArg a = cg_arg();
+    a.w = w;
+    run_cg(a, batch);
+    for (int i = 0; i < nrhs; i++) cgstat_h[i].iters += total;
+}
+
 void mj_solver::replay()
 {
     const int G = group_size(), K = rp.K;
@@ -961,10 +977,7 @@ void mj_solver::replay()
         if (!std::isfinite(cgstat_h[i].bb) || cgstat_h[i].bb > 1e200) return;   // the march ends (check_growth)
     // the record does not fit any more: CG from where the passes ended, and a new record in the next step;
     // after several misses in a row, some steps without replays
-    mj::CgArg a = cg_arg();
-    a.w = w_end;
-    run_cg(a, cg_guess);
-    for (int i = 0; i < nrhs; i++) cgstat_h[i].iters += total;
+    cg_after_passes(total, cg_guess);
     rp.learn = 1;
     rp.fails = std::min(rp.fails + 1, 6);
     if (rp.fails >= 2) rp.hold = 4 << rp.fails;
@@ -1098,10 +1111,7 @@ void mj_solver::solve_z0_chebyshev()
     }
     w_end = wbuf[(total + 1) & 1];
     if (stalled) {   // CG keeps its residual by recurrence, so any tolerance ends it
-        mj::CgArg a = cg_arg();
-        a.w = w_end;
-        run_cg(a, 2);
-        for (int i = 0; i < nrhs; i++) cgstat_h[i].iters += total;
+        cg_after_passes(total, 2);
         return;
     }
     const double res = worst();

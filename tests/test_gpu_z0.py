@@ -156,3 +156,67 @@ def test_tolerances_at_the_rounding_of_the_residual(torch_cuda, z0, hi, rtol):
         out.append(J)
     # 40 solves, each within max(rtol, rounding) of the current times the condition of Z_0 (about eps)
     assert float((out[0] - out[1]).norm()) <= 40 * max(rtol, 1e-15) * max(hi, 100.0) * float(out[1].norm())
+
+
+_HEAD = 8 + 14 * 4 + 5 * 8   # bytes before the solve's record in a state
+_MAXCOEF = 192               # passes a record holds
+
+
+def _record(st):
+    """The solve's record in a state: its counters and the coefficients (copies)."""
+    import struct
+    names = ("K", "K0", "L", "learn", "fails", "hold")
+    nr = struct.unpack_from("<i", st.tobytes(), 8 + 4 * 4)[0]
+    c = np.frombuffer(st[_HEAD + 32:_HEAD + 32 + 16 * _MAXCOEF * nr].tobytes()).reshape(nr, _MAXCOEF, 2).copy()
+    return dict(zip(names, struct.unpack_from("<6i", st.tobytes(), _HEAD))), c
+
+
+def _with_coefficients(st, c):
+    st = st.copy()
+    st[_HEAD + 32:_HEAD + 32 + c.nbytes] = np.frombuffer(c.tobytes(), dtype=np.uint8)
+    return st
+
+
+def _resume(torch, prob, st, n, **kw):
+    from paper_2407_03323_amd import motjvie
+    s = motjvie.solver_for(prob, **kw)
+    s.set_state(st)
+    J = torch.zeros((n, len(prob.waves), 3, prob.W, prob.V, prob.U), dtype=torch.float64, device="cuda")
+    try:
+        s.run(n, J)
+        return J, s.stats(), s.get_state()
+    finally:
+        s.close()
+
+
+def _state_at(prob, n, **kw):
+    from paper_2407_03323_amd import motjvie
+    s = motjvie.solver_for(prob, **kw)
+    s.run(n)
+    st = s.get_state()
+    s.close()
+    return st
+
+
+# factors on the recorded coefficients: residuals that pass 1 / eps of the right-hand side, that overflow (a march
+# that is sound must not be reported as unstable), that stay as they are, and no numbers
+@pytest.mark.parametrize("factor", [8.0, 1e30, 0.0, float("nan")])
+@pytest.mark.parametrize("UVW,nr", [((7, 6, 5), 2), ((20, 21, 19), 1)])
+def test_a_record_that_does_not_fit_costs_no_accuracy(torch_cuda, UVW, nr, factor):
+    """Replays of coefficients that blow the residual up: the CG that follows starts from something better, so
+    the currents are CG's to the solve tolerance."""
+    prob = _problem(*UVW, nr, 40)
+    st = _state_at(prob, 30)
+    rec, c = _record(st)
+    assert rec["K"] >= 4 and rec["learn"] == 0 and rec["fails"] == 0 and rec["hold"] == 0
+    c[-1] *= factor   # the last right-hand side; any other's record still fits
+    print("record of %dx%dx%d times %g" % (UVW + (factor,)), flush=True)
+    J, stats, end = _resume(torch_cuda, prob, _with_coefficients(st, c), 1)
+    ref = _resume(torch_cuda, prob, st, 1, z0_solver=1)[0]
+    assert _record(end)[0]["fails"] == 1 and stats["cg_res_max"] <= 1e-13
+    for r in range(nr):
+        assert float((J[:, r] - ref[:, r]).norm()) <= 1e-11 * float(ref[:, r].norm())
+    J, _, end = _resume(torch_cuda, prob, _with_coefficients(st, c), 6)
+    ref = _resume(torch_cuda, prob, st, 6, z0_solver=1)[0]
+    assert float((J - ref).norm()) <= 1e-11 * float(ref.norm())
+    assert _record(end)[0]["fails"] == 0   # recorded anew, and replayed
