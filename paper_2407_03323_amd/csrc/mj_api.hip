@@ -897,7 +897,8 @@ void mj_solver::solve_z0()
         base();
         return;
     }
-    if (rp.learn || n == 1 || n == 4 || n == 16 || n == 64 || n % 128 == 0) learn();
+    // (a resumed state's record may ask for more passes than this solver is allowed)
+    if (rp.learn || rp.K > cg_maxit || n == 1 || n == 4 || n == 16 || n == 64 || n % 128 == 0) learn();
     else replay();
 }
 

@@ -220,3 +220,17 @@ def test_a_record_that_does_not_fit_costs_no_accuracy(torch_cuda, UVW, nr, facto
     ref = _resume(torch_cuda, prob, st, 6, z0_solver=1)[0]
     assert float((J - ref).norm()) <= 1e-11 * float(ref.norm())
     assert _record(end)[0]["fails"] == 0   # recorded anew, and replayed
+
+
+def test_iteration_limit_after_a_resume(torch_cuda):
+    """cg_maxit holds for a resumed solver too, whatever number of passes the state's record asks for."""
+    from paper_2407_03323_amd.motjvie import MJ_ENOCONV, MotJvieError
+    prob = _problem(7, 6, 5, 1, 40)
+    st = _state_at(prob, 30)
+    K = _record(st)[0]["K"]
+    assert K > 3
+    with pytest.raises(MotJvieError) as ei:
+        _resume(torch_cuda, prob, st, 1, cg_maxit=3)
+    assert ei.value.code == MJ_ENOCONV
+    ref = _resume(torch_cuda, prob, st, 1)[0]
+    assert torch_cuda.equal(_resume(torch_cuda, prob, st, 1, cg_maxit=60)[0], ref)   # nothing it reaches
