@@ -27,6 +27,9 @@ constexpr long kChebMaxUnknowns = 1L << 19;
 // from one pass to the next
 constexpr size_t kPassGroupBytes = 190000000;
 
+// entries of the Chebyshev iteration's coefficient table, at most (cg_maxit may be any number)
+constexpr int kChebCoefMax = 65536;
+
 constexpr int kStepEvents = 9;   // events of a timed step (see StepIO)
 
 // whether outer_overlap = 0 runs the outer level of three on the second stream
@@ -265,7 +268,7 @@ struct mj_solver {
     } rp;
     double *coef = nullptr;         // recorded coefficients [nrhs][kMaxCoef][2]
     double *rhist = nullptr;        // and relative residuals [nrhs][kMaxCoef]
-    double *ccoef = nullptr;        // coefficients of the Chebyshev iteration [cg_maxit + 2][2]
+    double *ccoef = nullptr;        // coefficients of the Chebyshev iteration [ccoef_len()][2]
     double lam_lo = 0.0, lam_hi = 0.0;   // bounds of the eigenvalues of M^-1 A (0: not estimated)
     int cheb_pred = 0;                   // passes predicted for the next Chebyshev solve (0: none yet)
     bool use_graphs = false;             // launch batches of passes from captured HIP graphs
@@ -450,6 +453,9 @@ struct mj_solver {
     bool read_status(const double *w = nullptr);
     void solve_z0_chebyshev();
     void estimate_spectrum();
+    // Passes with Chebyshev coefficients of their own; later ones take the last.  They approach their limit as
+    // ((sqrt(kappa) - 1) / (sqrt(kappa) + 1))^2k, so up to a condition number kappa of 1e7 the last is the limit
+    int ccoef_len() const { return std::min(cg_maxit, kChebCoefMax - 2) + 2; }
     size_t coef_count() const { return (size_t)nrhs * 2 * mj::kMaxCoef; }
     void clear_graphs()
     {
@@ -584,7 +590,7 @@ void mj_solver::create(const mj_config &c)
     }
     coef = dalloc<double>(coef_count(), "recorded coefficients");
     rhist = dalloc<double>((size_t)nrhs * mj::kMaxCoef, "recorded residuals");
-    ccoef = dalloc<double>(2 * ((size_t)cg_maxit + 2), "Chebyshev coefficients");
+    ccoef = dalloc<double>(2 * (size_t)ccoef_len(), "Chebyshev coefficients");
     nblk = (int)((M + 255) / 256);
     part_cap = 3 * nblk;
     {
@@ -827,7 +833,7 @@ void mj_solver::enqueue_passes(bool recorded, int g0, int g1, int T, int K)
         a.k0 = k0_d;
         a.coef = recorded ? coef : ccoef;
         a.coef_stride = recorded ? 2 * mj::kMaxCoef : 0;
-        a.coef_len = recorded ? mj::kMaxCoef : cg_maxit + 2;
+        a.coef_len = recorded ? mj::kMaxCoef : ccoef_len();
         a.rhs0 = g0;
         a.nr = g1 - g0;
         a.part = parts;
@@ -835,6 +841,7 @@ void mj_solver::enqueue_passes(bool recorded, int g0, int g1, int T, int K)
         a.stat = cgstat;
         for (int k = T; k < T + K; k++) {
             a.k = k;
+            a.ck = recorded ? k : std::min(k, a.coef_len - 1);
             a.first = k == 0;
             a.want_norm = k == T + K - 1;
             a.w = wbuf[k & 1];
@@ -1066,7 +1073,7 @@ void mj_solver::estimate_spectrum()
     lam_hi = 1.05 * emax;
     // the three-term coefficients of the Chebyshev iteration for these bounds
     const double theta = 0.5 * (lam_hi + lam_lo), rho = (lam_hi - lam_lo) / (lam_hi + lam_lo);
-    std::vector<double> cc(2 * ((size_t)cg_maxit + 2));
+    std::vector<double> cc(2 * (size_t)ccoef_len());
     double om = 1.0;
     for (size_t j = 0; j < cc.size() / 2; j++) {
         om = j == 0 ? 1.0 : j == 1 ? 1.0 / (1.0 - 0.5 * rho * rho) : 1.0 / (1.0 - 0.25 * om * rho * rho);

@@ -158,9 +158,10 @@ struct PassArg {
     const double *w;         // w_k
     double *v;               // w_{k-1} in, w_{k+1} out
     const double *k0;
-    const double *coef;      // (a_k, b_k) of right-hand side r at coef + r coef_stride + 2 k
+    const double *coef;      // (a, b) of right-hand side r and entry j at coef + r coef_stride + 2 j
     long coef_stride;
-    int coef_len;            // passes that coef holds
+    int coef_len;            // entries that coef holds
+    int ck;                  // this pass's entry
     int k;
     int first;               // the first pass of a solve: there is no w_{k-1}
     int want_norm;           // sums |r_k|^2 and |b|^2 of w_k, and the test follows the pass

@@ -1323,7 +1323,7 @@ __global__ void __launch_bounds__(64 * WB) k_z0_pass(PassArg a)
     const bool mine = iq < tl.nq && lane >= 1 && lane <= 62 && q <= plane - px - 2;
     const long base = (long)r * 3 * a.Mp;
     const double *w0 = a.w + base, *w1 = w0 + a.Mp, *w2 = w1 + a.Mp;
-    const double ca = kconst(a.coef)[r * a.coef_stride + 2 * a.k], cb = kconst(a.coef)[r * a.coef_stride + 2 * a.k + 1];
+    const double ca = kconst(a.coef)[r * a.coef_stride + 2 * a.ck], cb = kconst(a.coef)[r * a.coef_stride + 2 * a.ck + 1];
     kconst_t *K = kconst(a.k0);
     // K^{c}(dx, dy, dz), dx, dy, dz in {0, 1}
     auto k = [&](int dx, int dy, int dz, int c) __attribute__((always_inline)) {
@@ -1461,7 +1461,7 @@ int z0_pass_blocks(int U, int V, int W, int nr) { return pass_shape(U + 2, V + 2
 void launch_z0_pass(const PassArg &a, hipStream_t st)
 {
     const PassShape sh = pass_shape(a.px, a.py, a.pz, a.nr);
-    if (a.nr < 1 || a.k < 0 || a.k >= a.coef_len || (a.want_norm && 2L * sh.blocks > a.part_cap))
+    if (a.nr < 1 || a.ck < 0 || a.ck >= a.coef_len || (a.want_norm && 2L * sh.blocks > a.part_cap))
         throw std::logic_error("Z_0 pass outside its buffers");
     const dim3 grid((unsigned)((long)sh.blocks * a.nr)), blk(64 * sh.wb);
     auto go = [&]<int ZT, int WB>() {

@@ -234,3 +234,19 @@ def test_iteration_limit_after_a_resume(torch_cuda):
     assert ei.value.code == MJ_ENOCONV
     ref = _resume(torch_cuda, prob, st, 1)[0]
     assert torch_cuda.equal(_resume(torch_cuda, prob, st, 1, cg_maxit=60)[0], ref)   # nothing it reaches
+
+
+def test_iteration_limit_costs_no_memory(torch_cuda):
+    """A limit that nothing reaches changes neither the currents nor, beyond a megabyte, the memory."""
+    from paper_2407_03323_amd import motjvie
+    prob = _problem(7, 6, 5, 1, 20)
+    held, out = [], []
+    for maxit in (200, 10 ** 7, 2 ** 31 - 1):
+        s = motjvie.solver_for(prob, cg_maxit=maxit)
+        held.append(s.info()["device_bytes"])
+        assert held[-1] - held[0] <= 1 << 20
+        J = torch_cuda.zeros((20, 1, 3, 5, 6, 7), dtype=torch_cuda.float64, device="cuda")
+        s.run(20, J)
+        s.close()
+        out.append(J)
+    assert all(torch_cuda.equal(out[0], J) for J in out[1:])
