@@ -173,7 +173,7 @@ static void plan_wave(mj::WaveArg &w, double h, double hy, double hz)
     for (; ns > 0; ns--) {
         long double root = 1.0865L;   // sqrt(2^2j (2j)!)
         for (int i = 1; i <= 2 * ns; i++) root *= std::sqrt(2.0L * i);
-        if (left + c[ns] * root > std::ldexp(1.0L, -53)) break;
+        if (!(left + c[ns] * root <= std::ldexp(1.0L, -53))) break;   // also where c overflows (no number)
         left += c[ns] * root;
     }
     if (ns <= mj::kMaxSeries) {

@@ -60,3 +60,17 @@ def test_series_and_forms_beyond_it(torch_cuda, case, prism):
         size = np.abs(ref).reshape(n, -1).max(axis=1)
         t = int(np.argmax(size >= 0.1 * size.max()))
         assert np.linalg.norm(J[t, r] - ref[t]) <= 1e-11 * np.linalg.norm(ref[t]), r
+
+def test_pulse_far_narrower_than_a_voxel(torch_cuda):
+    """A pulse of 1e-60 voxels, whose series does not exist in any number format: the average is what the pulse
+    covers of a voxel, nothing beside its peak."""
+    from paper_2407_03323_amd import motjvie
+    U, V, W, n = 5, 4, 3, 8
+    waves = [wl.PlaneWave(khat=k, pol=(0.0, 0.0, 1.0), width=1e-60, t0=0.5, amp=1.0, r_ref=(0.0, 0.0, 0.0))
+             for k in ((1.0, 0.0, 0.0), (0.6, 0.8, 0.0))]   # the first passes a voxel's centre at every step
+    prob = wl.Problem("narrow", U, V, W, wl.random_eps(U, V, W, 8, 2.0, 6.0), waves, n)
+    s = motjvie.solver_for(prob)
+    J = torch_cuda.zeros((n, 2, 3, W, V, U), dtype=torch_cuda.float64, device="cuda")
+    s.run(n, J)
+    s.close()
+    assert float(J.abs().max()) <= 1e-50
