@@ -575,9 +575,6 @@ void mj_solver::create(const mj_config &c)
     y = dalloc<double>((size_t)nrhs * 3 * M, "cg y");
     p = dalloc<double>((size_t)nrhs * 3 * M, "cg p");
     q = dalloc<double>((size_t)nrhs * 3 * M, "cg q");
-    // the first iteration of every solve scales p and q by beta = 0: they must be finite
-    MJ_CHECK(hipMemset(p, 0, sizeof(double) * nrhs * 3 * M));
-    MJ_CHECK(hipMemset(q, 0, sizeof(double) * nrhs * 3 * M));
     const size_t Mp = (size_t)(U + 2) * (V + 2) * (W + 2);
     u = dalloc<double>((size_t)nrhs * 3 * Mp, "cg u");
     bh = dalloc<double>((size_t)nrhs * 3 * Mp, "solve rhs");
@@ -1615,16 +1612,12 @@ void mj_solver::run(int n_steps, double *Jout, double *Pout, int j_every)
     if (noconv) throw std::range_error("Z_0 solve did not converge");
 }
 
-// Back to n = 0 with every past current zero.  The search directions p and q enter the first
-// iteration of each Z_0 solve multiplied by beta = 0, so they must be finite: a march that ended
-// on non-finite values (MJ_EUNSTABLE) would otherwise turn every later solve into NaN through
-// 0 * Inf.  They are cleared here, as at mj_create.
+// Back to n = 0 with every past current zero.  (CG's p and q need no clearing: a solve's first iteration takes
+// neither, see k_cg_a.)
 void mj_solver::restart()
 {
     drop_side();
     const size_t v = sizeof(double) * (size_t)nrhs * 3 * M;
-    MJ_CHECK(hipMemsetAsync(p, 0, v, st));
-    MJ_CHECK(hipMemsetAsync(q, 0, v, st));
     MJ_CHECK(hipMemsetAsync(y, 0, v, st));
     // voxels whose eps changed to 1 must read as zero in the stencil
     const size_t vp = sizeof(double) * (size_t)nrhs * 3 * (U + 2) * (V + 2) * (W + 2);

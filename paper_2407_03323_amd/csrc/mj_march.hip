@@ -1156,13 +1156,14 @@ __global__ void __launch_bounds__(256) k_cg_a(CgArg a, int it, int finish)
             for (int c = 0; c < 3; c++) {
                 const long o = base + c * M + i;
                 const double zv = uc[c] * inv_s;
-                // at it = 0, alpha = beta = 0 and p, q hold finite values of the previous solve
-                // (the update stays unconditional: a branch here makes the compiler duplicate
-                // the loop body)
-                const double po = a.p[o];
+                // at it = 0, p and q hold what the previous solve left there, which need not be finite;
+                // they count as zero (a select: a branch here makes the compiler duplicate the loop
+                // body)
+                const double pl = a.p[o], ql = a.q[o];
+                const double po = it > 0 ? pl : 0.0, qo = it > 0 ? ql : 0.0;
                 a.y[o] += alpha * po;
                 const double pv = zv + beta * po;
-                const double qv = (c0 * zv - s * Ku[c]) + beta * a.q[o];
+                const double qv = (c0 * zv - s * Ku[c]) + beta * qo;
                 a.p[o] = pv;
                 a.q[o] = qv;
                 v[0] += pv * qv;

@@ -250,3 +250,29 @@ def test_iteration_limit_costs_no_memory(torch_cuda):
         s.close()
         out.append(J)
     assert all(torch_cuda.equal(out[0], J) for J in out[1:])
+
+
+@pytest.mark.parametrize("z0", [0, 1])
+@pytest.mark.parametrize("m", [15, 20])
+def test_a_state_read_after_a_nonfinite_march(torch_cuda, z0, m):
+    """A march that ended on values that are no numbers, in CG's vectors among them (step 16 records CG), leaves
+    nothing in the solver that a state read after it could meet."""
+    from paper_2407_03323_amd import motjvie
+    from paper_2407_03323_amd.motjvie import MJ_EUNSTABLE, MotJvieError
+    torch = torch_cuda
+    prob = _problem(7, 6, 5, 1, 40)
+    st = _state_at(prob, m, z0_solver=z0)
+    ref = _resume(torch, prob, st, 40 - m, z0_solver=z0)[0]
+    s = motjvie.solver_for(prob, z0_solver=z0)
+    bad = st.copy()
+    jr = s.info()["real_depth"] * 3 * prob.M * 8
+    bad[len(bad) - jr:] = np.frombuffer(np.full(jr // 8, np.nan).tobytes(), dtype=np.uint8)
+    s.set_state(bad)
+    with pytest.raises(MotJvieError) as ei:
+        s.run(5)
+    assert ei.value.code == MJ_EUNSTABLE
+    s.set_state(st)
+    J = torch.zeros_like(ref)
+    s.run(40 - m, J)
+    s.close()
+    assert torch.equal(J, ref)
