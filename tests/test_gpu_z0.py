@@ -276,3 +276,17 @@ def test_a_state_read_after_a_nonfinite_march(torch_cuda, z0, m):
     s.run(40 - m, J)
     s.close()
     assert torch.equal(J, ref)
+
+
+def test_most_steps_replay(torch_cuda):
+    """From step 16 on the default solve replays: no miss over 100 steps, and as many passes as CG takes
+    iterations, give or take two, where the Chebyshev iteration takes more."""
+    prob = _problem(20, 21, 19, 2, 100)
+    iters = []
+    for z0 in (0, 1, 2):
+        st = _state_at(prob, 70, z0_solver=z0)
+        rec = _record(st)[0]
+        if z0 == 0:
+            assert rec["K"] >= 4 and rec["learn"] == 0 and rec["fails"] == 0 and rec["hold"] == 0
+        iters.append(_resume(torch_cuda, prob, st, 30, z0_solver=z0)[1]["cg_iters"])
+    assert abs(iters[0] - iters[1]) <= 2.0 and iters[2] >= iters[1] + 2.0, iters
