@@ -837,13 +837,12 @@ void mj_solver::enqueue_passes(bool recorded, int g0, int g1, int T, int K)
         a.part_cap = part_cap;
         a.stat = cgstat;
         for (int k = T; k < T + K; k++) {
-            a.k = k;
-            a.ck = recorded ? k : std::min(k, a.coef_len - 1);
+            a.k = recorded ? k : std::min(k, a.coef_len - 1);
             a.first = k == 0;
             a.want_norm = k == T + K - 1;
             a.w = wbuf[k & 1];
             a.v = wbuf[(k + 1) & 1];
-            mj::launch_z0_pass(a, s_);
+            mj::launch_z0_pass(a, k, s_);
         }
     };
     if (!use_graphs) {

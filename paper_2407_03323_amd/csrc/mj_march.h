@@ -158,11 +158,10 @@ struct PassArg {
     const double *w;         // w_k
     double *v;               // w_{k-1} in, w_{k+1} out
     const double *k0;
-    const double *coef;      // (a, b) of right-hand side r and entry j at coef + r coef_stride + 2 j
+    const double *coef;      // (a_k, b_k) of right-hand side r at coef + r coef_stride + 2 k
     long coef_stride;
     int coef_len;            // entries that coef holds
-    int ck;                  // this pass's entry
-    int k;
+    int k;                   // this pass's entry
     int first;               // the first pass of a solve: there is no w_{k-1}
     int want_norm;           // sums |r_k|^2 and |b|^2 of w_k, and the test follows the pass
     int rhs0, nr;            // the right-hand sides rhs0 .. rhs0 + nr - 1
@@ -172,7 +171,8 @@ struct PassArg {
 };
 // blocks that a pass over nr right-hand sides takes for each of them
 int z0_pass_blocks(int U, int V, int W, int nr);
-void launch_z0_pass(const PassArg &a, hipStream_t st);
+// passes: those taken before this one, for the status that the test leaves
+void launch_z0_pass(const PassArg &a, int passes, hipStream_t st);
 // pseudo-random right-hand side (zero where sqrt(chi) = 0), haloed
 void launch_fill_trial(const double *schi, int U, int V, int W, double *b, hipStream_t st);
 

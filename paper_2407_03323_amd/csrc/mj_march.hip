@@ -1324,7 +1324,7 @@ __global__ void __launch_bounds__(64 * WB) k_z0_pass(PassArg a)
     const bool mine = iq < tl.nq && lane >= 1 && lane <= 62 && q <= plane - px - 2;
     const long base = (long)r * 3 * a.Mp;
     const double *w0 = a.w + base, *w1 = w0 + a.Mp, *w2 = w1 + a.Mp;
-    const double ca = kconst(a.coef)[r * a.coef_stride + 2 * a.ck], cb = kconst(a.coef)[r * a.coef_stride + 2 * a.ck + 1];
+    const double ca = kconst(a.coef)[r * a.coef_stride + 2 * a.k], cb = kconst(a.coef)[r * a.coef_stride + 2 * a.k + 1];
     kconst_t *K = kconst(a.k0);
     // K^{c}(dx, dy, dz), dx, dy, dz in {0, 1}
     auto k = [&](int dx, int dy, int dz, int c) __attribute__((always_inline)) {
@@ -1417,7 +1417,7 @@ __global__ void __launch_bounds__(64 * WB) k_z0_pass(PassArg a)
 }
 
 // One block per right-hand side adds the partials of |r_k|^2 and |b|^2 in block order and takes the test.
-__global__ void __launch_bounds__(1024) k_z0_test(PassArg a, int nb)
+__global__ void __launch_bounds__(1024) k_z0_test(PassArg a, int nb, int passes)
 {
     __shared__ double sm[16];
     const int r = blockIdx.x + a.rhs0;
@@ -1432,7 +1432,7 @@ __global__ void __launch_bounds__(1024) k_z0_test(PassArg a, int nb)
     if (threadIdx.x != 0) return;
     const double rr = acc[0], bb = acc[1];
     const bool pass = rr <= a.tol2 * bb || bb == 0.0;
-    a.stat[r] = CgStatus{pass ? 1 : 0, pass ? 1 : 0, a.k, bb > 0.0 ? sqrt(rr / bb) : 0.0, bb};
+    a.stat[r] = CgStatus{pass ? 1 : 0, pass ? 1 : 0, passes, bb > 0.0 ? sqrt(rr / bb) : 0.0, bb};
 }
 
 // Planes per thread and waves per block.  More planes spend less on the two they share with their
@@ -1459,10 +1459,10 @@ static PassShape pass_shape(int px, int py, int pz, int nr)
 
 int z0_pass_blocks(int U, int V, int W, int nr) { return pass_shape(U + 2, V + 2, W + 2, nr).blocks; }
 
-void launch_z0_pass(const PassArg &a, hipStream_t st)
+void launch_z0_pass(const PassArg &a, int passes, hipStream_t st)
 {
     const PassShape sh = pass_shape(a.px, a.py, a.pz, a.nr);
-    if (a.nr < 1 || a.ck < 0 || a.ck >= a.coef_len || (a.want_norm && 2L * sh.blocks > a.part_cap))
+    if (a.nr < 1 || a.k < 0 || a.k >= a.coef_len || (a.want_norm && 2L * sh.blocks > a.part_cap))
         throw std::logic_error("Z_0 pass outside its buffers");
     const dim3 grid((unsigned)((long)sh.blocks * a.nr)), blk(64 * sh.wb);
     auto go = [&]<int ZT, int WB>() {
@@ -1481,7 +1481,7 @@ void launch_z0_pass(const PassArg &a, hipStream_t st)
     }
     MJ_CHECK(hipGetLastError());
     if (a.want_norm) {
-        hipLaunchKernelGGL(k_z0_test, dim3(a.nr), dim3(1024), 0, st, a, sh.blocks);
+        hipLaunchKernelGGL(k_z0_test, dim3(a.nr), dim3(1024), 0, st, a, sh.blocks, passes);
         MJ_CHECK(hipGetLastError());
     }
 }
