@@ -1516,14 +1516,10 @@ mj::AdjArg mj_solver::adj_arg() const
     a.V = V;
     a.W = W;
     a.nrhs = nrhs;
-    a.table = ptable;
-    a.pair_kmin = pair_kmin;
-    a.inv = pinv;
     a.table_v = ptable_v;
     a.kmin_v = pkmin_v;
     a.np = np;
     a.nw = nw;
-    a.npairs = npairs;
     a.schi = schi;
     a.c0 = c0;
     a.inv_eps = inv_eps;

@@ -86,16 +86,12 @@ struct AdjArg {
     long M;
     int U, V, W, nrhs;
     // adjoint source from the stored probe field
-    const double *table;     // probe kernel table [nw][npairs][6]
-    const int *pair_kmin;    // [npairs]
-    const int *inv;          // [np][M] pair of (probe, voxel), -1 if none
-    const double *table_v;   // the same table by voxel: [nw][np][M][6] (zeros where inv < 0)
+    const double *table_v;   // probe kernel table by voxel: [nw][np][M][6] (zeros where there is no pair)
     const int *kmin_v;       // [np][M] first lag of the pair's window, -1 if no pair
     const double *Ehist;     // [N][nrhs][np][3]
     int np, nw, N, j;        // j: forward step of this adjoint step (the source: the first of ntarget,
                              // j, j - 1, ...)
     int ntarget;             // steps the source is formed for, at most kProbeSteps
-    long npairs;
     double *G;               // out [nrhs][3][M]; the source: [ntarget][nrhs][3][M]
     // lambda from the solve
     const double *schi, *c0, *bq, *nu;   // nu: [nrhs][3][M] of this step
@@ -118,7 +114,8 @@ struct CgStatus {
     int done;                // the last test passed
     int ended;               // CG: no further iteration runs (the stopping residual is reached)
     int iters;               // iterations taken
-    double res;              // relative residual |r| / |b| at the last test
+    double res;              // relative residual |r| / |b| at the last test (passes: of the iterate before the
+                             // one they leave)
     double bb;               // |b|^2 of the solve's right-hand side (growth detector)
 };
 

@@ -787,20 +787,12 @@ __device__ inline double wave_average(const WaveArg *wp, const EpiArg &e, int u,
         }
         return w.amp * sum * (0.8862269254527580 * w.width / w.kh[0]);   // sqrt(pi) / 2
     }
-    const int nx = w.k[0] != 0.0 ? 8 : 1, ny = w.k[1] != 0.0 ? 8 : 1, nz = w.k[2] != 0.0 ? 8 : 1;
+    // form 0: one axis
+    const double hk = w.k[0] != 0.0 ? e.h * w.k[0] : w.k[1] != 0.0 ? e.hy * w.k[1] : e.hz * w.k[2];
     double sum = 0.0;
-    for (int i = 0; i < nx; i++) {
-        const double ox = nx > 1 ? e.glx8[i] * e.h * w.k[0] : 0.0, wx = nx > 1 ? e.glw8[i] : 1.0;
-        for (int j = 0; j < ny; j++) {
-            const double oy = ny > 1 ? e.glx8[j] * e.hy * w.k[1] : 0.0, wy = ny > 1 ? e.glw8[j] : 1.0;
-            double sl = 0.0;
-            for (int l = 0; l < nz; l++) {
-                const double oz = nz > 1 ? e.glx8[l] * e.hz * w.k[2] : 0.0, wz = nz > 1 ? e.glw8[l] : 1.0;
-                const double x = (tc - ox - oy - oz) * iw;
-                sl += wz * exp(-x * x);
-            }
-            sum += wx * wy * sl;
-        }
+    for (int i = 0; i < 8; i++) {
+        const double x = (tc - e.glx8[i] * hk) * iw;
+        sum += e.glw8[i] * exp(-x * x);
     }
     return w.amp * sum;
 }
