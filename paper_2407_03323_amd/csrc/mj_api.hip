@@ -266,6 +266,7 @@ struct mj_solver {
         int hold = 0;               // steps left without replays
         int unused[2] = {};
     } rp;
+    static constexpr int kMaxFails = 6;   // misses that lengthen the pause (to 4 << kMaxFails steps)
     double *coef = nullptr;         // recorded coefficients [nrhs][kMaxCoef][2]
     double *rhist = nullptr;        // and relative residuals [nrhs][kMaxCoef]
     double *ccoef = nullptr;        // coefficients of the Chebyshev iteration [ccoef_len()][2]
@@ -983,7 +984,7 @@ void mj_solver::replay()
     // after several misses in a row, some steps without replays
     cg_after_passes(total, cg_guess);
     rp.learn = 1;
-    rp.fails = std::min(rp.fails + 1, 6);
+    rp.fails = std::min(rp.fails + 1, kMaxFails);
     if (rp.fails >= 2) rp.hold = 4 << rp.fails;
 }
 
@@ -1943,8 +1944,9 @@ void mj_solver::set_state(const void *buf, size_t bytes)
     Replay rp_new;
     if (h.version != 2) {
         std::memcpy(&rp_new, p, sizeof rp_new);
-        if (rp_new.K < 0 || rp_new.K >= mj::kMaxCoef || rp_new.L < 0 || rp_new.L > mj::kMaxCoef || rp_new.fails < 0 ||
-            rp_new.hold < 0 || (rp_new.K < 1 && !rp_new.learn))
+        auto in = [](int x, int most) { return x >= 0 && x <= most; };
+        if (!in(rp_new.K, mj::kMaxCoef - 1) || !in(rp_new.K0, mj::kMaxCoef - 1) || !in(rp_new.L, mj::kMaxCoef) ||
+            !in(rp_new.fails, kMaxFails) || !in(rp_new.hold, 4 << kMaxFails) || (rp_new.K < 1 && !rp_new.learn))
             throw ArgError("bad solve record in the state");
     }
     drop_side();
