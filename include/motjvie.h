@@ -76,8 +76,9 @@ typedef struct {
                                  of eq:PnMOT differently, so results then vary with it at rounding level */
     void *stream;             /* hipStream_t to enqueue on; NULL = the null stream */
     int32_t quad_order;       /* Gauss-Legendre points per cell of the kernel quadrature (4 .. 24); 0 selects 16
-                                 for voxels within 3.5 edges of each other and, falling to 9 x 8
-                                 beyond 24, what keeps the cells' error below rounding */
+                                 for voxels within 3.5 edges of each other (and shells that graze a
+                                 voxel's plane) and, falling to 10 x 8 beyond 24, what keeps the cells'
+                                 error below rounding */
     int32_t fft_pencils;      /* pencils per block of the FFT passes: 0 = pick per pass by timing at
                                  mj_create; > 0 = at most this many (capped by what one LDS tile holds).
                                  The transforms are bit-identical for every choice. < 0: MJ_EINVAL */
@@ -317,7 +318,8 @@ int mj_kernel_values_noalloc(mj_solver *s, int32_t n, const int32_t *lag, const 
  * mj_stats -- per-phase device times of the last mj_run (HIP events on the solver's stream),
  *   in ms per step, and CG statistics.  out (host, n <= 21): [0] forward FFT  [1] history
  *   MAC  [2] inverse FFT  [3] epilogue (excitation, FIR, RHS)  [4] Z_0 solve  [5] total
- *   [6] mean CG iterations  [7] max final relative residual  [8] steps timed
+ *   [6] mean iterations of the Z_0 solve  [7] max relative residual at its last test (of passes: that of
+ *   the iterate before the one they return, which is one update further)  [8] steps timed
  *   [9] max CG iterations  [10] mean duration of one far-part MAC launch (time-blocked,
  *   once per block)  [11] far-part launches  [12] mean duration of one near-part launch
  *   [13] probes.  [5] includes [13].  After mj_adjoint_gradient: [14] forward pass (ms,

@@ -880,8 +880,11 @@ void mj_solver::enqueue_passes(bool recorded, int g0, int g1, int T, int K)
 // most as the wave enters, and one CG solve in 128 costs little), and after a replay that
 // missed the tolerance; on small grids, where a CG solve costs six of the Chebyshev iteration (32^3: 0.8 ms
 // against 0.13), that one takes the first 15 steps.  Every solve is tested on its own residual, so a record that
-// no longer fits costs passes, never accuracy.  What decides which steps run CG, and how many passes a
-// replay takes before its test, depends on the march alone and travels with its state.
+// no longer fits costs passes, never accuracy.  (The test is that of the last pass's input; its output, one update
+// further, is the solution.  Over 540 solves, with a change of waves among them and eps up to 1e4, that one's
+// residual was 0.29 to 0.55 of the tested one at the median, at most 0.95 of it after Chebyshev passes, and never
+// above 6.6e-14 with the test at 1e-13.)  What decides which steps run CG, and how many passes a replay takes
+// before its test, depends on the march alone and travels with its state.
 void mj_solver::solve_z0()
 {
     auto base = [&] {
@@ -1307,8 +1310,10 @@ void mj_solver::collect_side_timers(bool wait)
 
 // Default time division when the caller sets neither block: three levels, blocks of 4 in
 // outer blocks of 16, once the kernel reaches far enough back in time (ell >= 64) for the
-// outer level to pay; else two levels with blocks of 8.  At 104^3 (ell = 182) per step:
-// 2.85 ms against 3.39 ms for blocks of 8 alone.
+// outer level to pay; else two levels with blocks of 8.  The history sum per step, blocks of 8 against
+// 4 in 16: 16^3 (ell 29) 7.9 and 8.7 us, 24^3 (43) 10.6 and 10.5, 32^3 (57) 24.8 and 20.8, 36^3 (64) 37.1 and
+// 28.4, 48^3 (85) 96 and 70, 64^3 (112) 279 and 188, 104^3 (182) 1740 and 1119.  (They meet at ell = 43: the line
+// was drawn with an outer kernel that took longer.)
 void mj_solver::default_time_division()
 {
     if (ell >= 64) {
@@ -1371,10 +1376,6 @@ void mj_solver::mac_autotune()
     t_mac_tune_ms = best;
 }
 
-// One step n -> n + 1 of the march on the current track: FFT of the newest source, spectral
-// history sum (plain or time-blocked), inverse FFT, right-hand side, Z_0 solve, and the
-// outputs asked for.  io.adjoint runs the transposed march instead (sources nu, local
-// history lambda in Lr, right-hand side from io.G).
 // What follows the solve of step n whatever comes next: J_n = w (haloed; NULL: s y) into the real ring, and
 // the forward transform that the next step starts with.
 void mj_solver::follow(const StepIO &io, const double *w)
@@ -1395,6 +1396,10 @@ void mj_solver::transform(int j, hipEvent_t *ev)
     transformed = j;
 }
 
+// One step n -> n + 1 of the march on the current track: FFT of the newest source, spectral
+// history sum (plain or time-blocked), inverse FFT, right-hand side, Z_0 solve, and the
+// outputs asked for.  io.adjoint runs the transposed march instead (sources nu, local
+// history lambda in Lr, right-hand side from io.G).
 // `transformed` holds the last step whose transform was enqueued by the step itself; a call that starts
 // or moves the march forgets it, so it never outlives the rings' contents.
 void mj_solver::step(const StepIO &io)

@@ -383,7 +383,7 @@ __global__ void __launch_bounds__(kThreads) k_fft_strided(const double2 *__restr
 // The strided passes of a length N = R1 R2 with both factors at most 16 keep a butterfly of 16 points a thread
 // in registers and exchange once: a thread loads the R1 points j + r R2 of its pencil straight from memory,
 // transforms them, leaves them in LDS at j R1 + q, and after one barrier takes the R2 points j + r R1,
-// twiddles, transforms and stores j + q R1.  The stage-by-stage kernel below moves every point through LDS
+// twiddles, transforms and stores j + q R1.  The stage-by-stage kernel above moves every point through LDS
 // once for the load, once per stage (three or four) and once for the store, with a barrier each time, and that,
 // not its arithmetic, kept it at 3 TB/s.  Neighbouring lanes hold neighbouring pencils, so every
 // access of memory and LDS is a run of the pencils' values.  The inverse is the forward transform with real
@@ -792,7 +792,7 @@ void fft3d_free(Fft3D &f)
 }
 
 // Radix set of a plan, and the stage-by-stage kernel instance that serves it where no two-radix pass does
-// (lengths below 32 and above 256, and those with a factor that does not split): powers of two and 3 2^k
+// (lengths 2 to 6 and above 256, and those that are no product of two radices of at most 16): powers of two and 3 2^k
 // have their own instances, any other plan the generic one.
 static int plan_mask(const FftPlan1D &p)
 {
