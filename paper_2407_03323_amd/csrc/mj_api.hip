@@ -1941,8 +1941,11 @@ void mj_solver::set_state(const void *buf, size_t bytes)
     if (h.rdepth != sdepth) throw ArgError("state of a solver with another history depth (probes differ)");
     const size_t solve_bytes = sizeof(Replay) + sizeof(double) * coef_count();
     const size_t need = state_bytes() - (h.version == 2 ? solve_bytes : 0);
-    if (bytes < need || (size_t)h.ring_bytes + (size_t)h.far_bytes + (size_t)h.jr_bytes + (size_t)h.outer_bytes +
-                                (h.version == 2 ? 0 : solve_bytes) + sizeof h != need)
+    const size_t v3 = (size_t)nrhs * 3, spec = sizeof(double2) * v3 * (size_t)spec_plane();
+    // each part by itself: the copies below trust these sizes
+    if (bytes < need || (size_t)h.ring_bytes != spec * (size_t)ell || (size_t)h.far_bytes != (farbuf ? spec * (size_t)B : 0) ||
+        (size_t)h.jr_bytes != sizeof(double) * (size_t)sdepth * v3 * (size_t)M ||
+        (size_t)h.outer_bytes != (gbuf ? spec * (size_t)B2 : 0))
         throw ArgError("state buffer has the wrong size");
     if (h.n < 0 || h.n > INT32_MAX) throw ArgError("bad step count in the state");
     const char *p = (const char *)buf + sizeof h;

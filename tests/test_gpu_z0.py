@@ -312,3 +312,24 @@ def test_a_damaged_record_is_refused(torch_cuda, field, value):
     s.run(5, J)
     s.close()
     assert torch_cuda.equal(J, _resume(torch_cuda, prob, st, 5)[0])
+
+
+def test_parts_of_a_state_have_their_own_sizes(torch_cuda):
+    """A header whose part sizes add up but are not this solver's is refused before anything is copied."""
+    import struct
+    from paper_2407_03323_amd import motjvie
+    from paper_2407_03323_amd.motjvie import MJ_EINVAL, MotJvieError
+    prob = _problem(7, 6, 5, 1, 40)
+    st = _state_at(prob, 20)
+    ring, far, jr, outer = struct.unpack_from("<4q", st.tobytes(), _HEAD - 32)
+    s = motjvie.solver_for(prob)
+    for parts in ((ring + 4096, far, jr - 4096, outer), (ring, far + 4096, jr - 4096, outer),
+                  (ring - 4096, far, jr + 4096, outer), (ring, far, jr - 4096, outer + 4096)):
+        bad = st.copy()
+        bad[_HEAD - 32:_HEAD] = np.frombuffer(struct.pack("<4q", *parts), dtype=np.uint8)
+        with pytest.raises(MotJvieError) as ei:
+            s.set_state(bad)
+        assert ei.value.code == MJ_EINVAL
+    s.set_state(st)
+    s.run(3)
+    s.close()
