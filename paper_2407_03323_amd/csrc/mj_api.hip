@@ -441,6 +441,8 @@ struct mj_solver {
     void get_state(void *buf) const;
     void set_state(const void *buf, size_t bytes);
     void set_probes(int n_probes, const double *pos);
+    void build_probes(int n_probes, const double *pos);
+    void drop_probes();
     void offgrid_values(int n, const int *probe, const int *vox, const int *lag, double *out);
     void solve_z0();
     mj::CgArg cg_arg() const;
@@ -1692,7 +1694,19 @@ void mj_solver::set_probes(int n_probes, const double *pos)
     if (n_probes > 0 && !pos) throw ArgError("probe positions are NULL");
     for (int i = 0; i < 3 * n_probes; i++)
         if (!std::isfinite(pos[i])) throw ArgError("probe positions must be finite");
-    // drop a previous set
+    drop_probes();
+    if (n_probes == 0) return;
+    try {
+        build_probes(n_probes, pos);
+    } catch (...) {   // out of memory: no probes rather than some of their tables
+        (void)hipStreamSynchronize(st);
+        drop_probes();
+        throw;
+    }
+}
+
+void mj_solver::drop_probes()
+{
     dfree((void *&)probe_pos);
     dfree((void *&)ptable);
     dfree((void *&)ppart);
@@ -1708,7 +1722,10 @@ void mj_solver::set_probes(int n_probes, const double *pos)
     np = 0;
     nw = 0;
     npairs = 0;
-    if (n_probes == 0) return;
+}
+
+void mj_solver::build_probes(int n_probes, const double *pos)
+{
     // probe points in voxel steps per axis; distances in units of the x edge
     const double r = c_dt / h;
     const double edge[3] = {h, hy, hz}, hv[3] = {1.0, hy / h, hz / h};
@@ -1806,13 +1823,15 @@ void mj_solver::set_probes(int n_probes, const double *pos)
     ptable_v = dalloc<double>((size_t)nw * n_probes * M * 6, "probe kernel table by voxel");
     pkmin_v = dalloc<int>((size_t)n_probes * M, "probe windows by voxel");
     mj::launch_probe_table_by_voxel(ptable, pair_kmin, pinv, npairs, n_probes, nw, M, ptable_v, pkmin_v, st);
-    sdepth = std::max(sdepth, ell + 1);
     // the probe sums of kProbeSteps steps read J_{n-k} for k = 0..ell from the real-space ring
     if (rdepth < ell + mj::kProbeSteps) {
+        const int depth = ell + mj::kProbeSteps;
+        double *ring_r = dalloc<double>((size_t)depth * nrhs * 3 * M, "current history");
         dfree((void *&)Jr);
-        rdepth = ell + mj::kProbeSteps;
-        Jr = dalloc<double>((size_t)rdepth * nrhs * 3 * M, "current history");
+        Jr = ring_r;
+        rdepth = depth;
     }
+    sdepth = std::max(sdepth, ell + 1);
     MJ_CHECK(hipStreamSynchronize(st));
 }
 

@@ -135,3 +135,68 @@ def test_resumed_probe_field_reads_the_state_alone(torch_cuda, nan_memory, UVW, 
             s.run(more - first, None, F[first:])
         s.close()
         assert torch.equal(E, F), first
+
+
+def test_probes_that_do_not_fit_leave_a_solver_without_them(torch_cuda, monkeypatch):
+    """mj_set_probes out of memory at each of its allocations: MJ_ENOMEM, no probes, and the march, and probes
+    that fit, work as in a solver that never met it."""
+    from paper_2407_03323_amd import motjvie
+    from paper_2407_03323_amd.motjvie import MJ_ENOMEM, MJ_ESTATE, MotJvieError
+    torch, held, left = torch_cuda, {}, [10 ** 6]
+
+    def alloc(nbytes, ctx):
+        left[0] -= 1
+        if left[0] < 0:
+            return None
+        t = torch.zeros(((int(nbytes) + 7) // 8,), dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        held[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def free(ptr, ctx):
+        torch.cuda.synchronize()
+        del held[ptr]
+
+    monkeypatch.setattr(motjvie, "torch_allocator", lambda stream: (motjvie.ALLOC_FN(alloc), motjvie.FREE_FN(free)))
+    U, V, W, n = 6, 5, 4, 12
+    k, p = wl.XPOL_PLUS_Z
+    prob = wl.Problem("full", U, V, W, wl.random_eps(U, V, W, 41, 2.0, 9.0), [wl.gaussian_wave(U, V, W, k, p, 2.0, 2.0)], n)
+    pts = wl.fibonacci_sphere(3, 5.0, (U / 2, V / 2, W / 2))
+
+    def march(s):
+        J = torch.zeros((n, 1, 3, W, V, U), dtype=torch.float64, device="cuda")
+        s.reset()
+        s.run(n, J)
+        return J
+
+    s = motjvie.solver_for(prob, allocator="torch")
+    plain = march(s)
+    s.reset()
+    s.set_probes(pts)
+    E = torch.zeros((n, 1, 3, 3), dtype=torch.float64, device="cuda")
+    s.run(n, None, E)
+    s.close()
+    s = motjvie.solver_for(prob, allocator="torch")
+    fits = 0
+    while True:
+        s.reset()
+        left[0] = fits
+        try:
+            s.set_probes(pts)
+        except MotJvieError as e:
+            assert e.code == MJ_ENOMEM
+        else:
+            break
+        finally:
+            left[0] = 10 ** 6
+        fits += 1
+        assert s.info()["n_probes"] == 0
+        with pytest.raises(MotJvieError) as ei:
+            s.adjoint_gradient(n, torch.zeros((W, V, U), dtype=torch.float64, device="cuda"))
+        assert ei.value.code == MJ_ESTATE
+        assert torch.equal(march(s), plain)
+    assert fits >= 10
+    F = torch.zeros_like(E)
+    s.run(n, None, F)
+    s.close()
+    assert torch.equal(E, F) and float(E.norm()) > 0 and not held
